@@ -1053,7 +1053,7 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
     Buf<uint64_t> kfp = alloc<uint64_t>(ctx, c), klen = alloc<uint64_t>(ctx, c),
                   klm = alloc<uint64_t>(ctx, c);
     Buf<uint32_t> kslot = alloc<uint32_t>(ctx, c);
-    Buf<uint64_t> oddb = alloc<uint64_t>(ctx, 7 * (uint64_t)T);
+    Buf<uint64_t> oddb = alloc<uint64_t>(ctx, 8 * (uint64_t)T);
     Buf<uint64_t> woff = alloc<uint64_t>(ctx, E_ent + 1);
     Buf<uint64_t> seg_ws = alloc<uint64_t>(ctx, E_ent), seg_re = alloc<uint64_t>(ctx, E_ent);
     Buf<uint32_t> seg_text = alloc<uint32_t>(ctx, E_ent);
@@ -1064,8 +1064,8 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
     Buf<uint64_t> vbest = alloc<uint64_t>(ctx, c), rlb = alloc<uint64_t>(ctx, c),
                   vcnt = alloc<uint64_t>(ctx, 2);
     Buf<uint8_t> marked = alloc<uint8_t>(ctx, c);
-    // LDS key filter of up to 2^19 bits, sized per phase from the key count
-    Buf<uint32_t> filt = alloc<uint32_t>(ctx, (1ull << 19) / 32);
+    // LDS key filter of up to 2^20 bits, sized per phase from the key count
+    Buf<uint32_t> filt = alloc<uint32_t>(ctx, (1ull << 20) / 32);
     // second key filter (global memory, at most 2^24 bits = 2 MiB: stays in L2)
     Buf<uint32_t> filt2 = alloc<uint32_t>(ctx, (1ull << ctx->tune.filter2_max_log2) / 32);
     int scan_mode = 1;
@@ -1086,7 +1086,7 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
     a.lv = lv;
     a.k = KeysDev{kfp.p, klen.p, kslot.p, klm.p};
     a.odd = OddDev{oddb.p,         oddb.p + T,     oddb.p + 2 * T, oddb.p + 3 * T,
-                   oddb.p + 4 * T, oddb.p + 5 * T, oddb.p + 6 * T};
+                   oddb.p + 4 * T, oddb.p + 5 * T, oddb.p + 6 * T, oddb.p + 7 * T};
     a.x32 = x32;
     a.tab = TableDev{tab.p, cap - 1};
     a.x = x;
@@ -1161,8 +1161,9 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
       if (ctx->profile) phase_host.push_back({step, b, (uint64_t)phase, c});
       a.Lmain = phase == 1 ? 2 * b : b;
       a.xLmain = host_pow61(x, a.Lmain);
-      // LDS filter: about 32 bits per key, at most 2^19 (64 KiB), two bits per
-      // key while there are at least 8 bits per key.  The scan tests the
+      // LDS filter: 32 bits per key or more, at most 2^19 bits (64 KiB; 2^20 in
+      // scans of dense hashes, which run one workgroup per CU), two bits per key
+      // while there are at least 8 bits per key.  The scan tests the
       // 32-bit pre-filter hash and queues its candidates (mode 1); from 2^14
       // keys on, where the LDS filter starts to pass a sizeable share of the
       // windows, those also test a blocked second filter in global memory of
@@ -1172,7 +1173,9 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
       // 61-bit fingerprints without queues (mode 2), whose passes probe the
       // table at once.
       fbits = 12;
-      while (fbits < 19 && (1ull << fbits) < 32 * nkeys) ++fbits;
+      // (128 bits per key where the scan is long against the filter's copying)
+      const uint64_t per_key = !lean && c * b >= (1ull << 26) ? 128 : 32;
+      while (fbits < (lean ? 19u : 20u) && (1ull << fbits) < per_key * nkeys) ++fbits;
       uint32_t f2words = 0;
       const bool can_queue = T <= (1u << 24) && offs[T] < (1ull << 40) &&
                              !(prm.debug_flags & BT_DBG_NO_QUEUE);
@@ -1227,7 +1230,7 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
       {
         FillList f;
         f.add(tab.p, 4 * cap, ~0u);  // empty slots: fp = best = ~0
-        f.add(oddb.p, 14 * (uint64_t)T, 0);
+        f.add(oddb.p, 16 * (uint64_t)T, 0);
         f.add(vcnt.p, 4, 0);
         f.add(filt.p, (1ull << (byte_scan ? bbits : fbits)) / 32, 0);
         if (f2words) f.add(filt2.p, 2ull << f2words, 0);
@@ -1321,6 +1324,10 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
         span_chunks = std::min<uint64_t>(256, std::max<uint64_t>(16, span_chunks & ~15ull));
         if (ctx->tune.span_chunks) span_chunks = ctx->tune.span_chunks;
         Buf<uint64_t> span_info;
+        // with many segments, the tiles' segments from a pass of their own
+        Buf<uint32_t> tseg;
+        if (!text_local && scan_mode == 1 && !lean && as.lv.R >= kTileSegsMin)
+          tseg = alloc<uint32_t>(ctx, c * b / kProbeTile + 2);
         if (text_local) {
           span_info = alloc<uint64_t>(ctx, 3 * probe_text_spans(c * b, span_chunks));
           HIPCHK(ctx, launch_span_info(as, swoff, c * b, span_chunks, span_info.p, s));
@@ -1330,7 +1337,8 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
           // earlier) are short against a tile at the lowest levels
           return text_local ? launch_probe_text(as, swoff, has_odd, c * b, span_chunks, span_ctr.p,
                                                 span_info.p, phase == 2 && b <= 64, s)
-                            : launch_probe_scan(as, swoff, has_odd, has_salt, c * b, scan_mode, s);
+                            : launch_probe_scan(as, swoff, has_odd, has_salt, c * b, scan_mode,
+                                                tseg.p, s);
         }, a.Lmain);
       }
       HIPCHK(ctx, launch_resolve(a, vb, s));

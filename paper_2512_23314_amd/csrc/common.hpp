@@ -78,13 +78,16 @@ __device__ __forceinline__ uint64_t filter_bit2(uint64_t fp, uint32_t bits) {
   return ((fp >> 17) ^ (fp >> 41) ^ (fp * 0x9E3779B1ull >> 20)) & ((1ull << bits) - 1);
 }
 
-// The two bits of a 32-bit window hash (mod 2^32 polynomial hash, whose high
-// bits depend on every byte) in a filter of 2^bits bits.
-__device__ __forceinline__ uint32_t filter_bit32(uint32_t h, uint32_t bits) {
-  return h >> (32 - bits);
+// A 32-bit window hash (mod 2^32 polynomial hash, whose high bits depend on
+// every byte) in a filter of 2^bits bits (12..20): its word from the top bits
+// and one or two bits of that word from the ten below, so that a test is one
+// LDS read and no multiplication.
+__device__ __forceinline__ uint32_t filter32_word(uint32_t h, uint32_t bits) {
+  return h >> (37 - bits);
 }
-__device__ __forceinline__ uint32_t filter_bit32b(uint32_t h, uint32_t bits) {
-  return (h * 0x9E3779B1u) >> (32 - bits);
+__device__ __forceinline__ uint32_t filter32_mask(uint32_t h, uint32_t bits, bool two) {
+  const uint32_t u = h << (bits - 5);
+  return (1u << (u >> 27)) | (two ? 1u << ((u >> 22) & 31) : 0u);
 }
 
 // Second (global, L2-resident) filter of a 32-bit window hash: blocked, three

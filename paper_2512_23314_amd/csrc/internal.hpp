@@ -74,6 +74,12 @@ struct KeysDev {
 
 // Keys whose length differs from the phase's main length (at most one per
 // text: the one ending at the text's end).  Indexed by text.
+// The scans test it by its first min(L, kOddAnchor) bytes (its anchor): the
+// hash of those needs H[i] and H[i + 64], two values the main test of nearby
+// windows reads anyway, where the whole key's would be a third stream through
+// memory (H[i + L]).  A window that matches the anchor, rare but at copies of
+// the text's end, then compares the whole key's 32-bit hash, then its 61-bit one.
+constexpr uint64_t kOddAnchor = 64;
 struct OddDev {
   uint64_t* L;      // [T] 0 = none
   uint64_t* xp;     // [T] x^L
@@ -82,6 +88,7 @@ struct OddDev {
   uint64_t* pos;    // [T]
   uint64_t* nkeys;  // [T] keys of this text in this phase (main + odd)
   uint64_t* h32;    // [T] the key's 32-bit hash (low half) and x32^L (high half)
+  uint64_t* anc;    // [T] the same of its first min(L, kOddAnchor) bytes
 };
 
 struct Slot {
@@ -266,10 +273,17 @@ hipError_t launch_sort_groups(const PhaseArgs& a, const uint64_t* fp, const uint
 // prefix filter; windows that pass form their fingerprint and probe the table.
 hipError_t launch_byte_scan(const PhaseArgs& a, const uint64_t* woff, bool has_odd, bool has_salt,
                             uint64_t max_windows, hipStream_t s);
-// The sliding-window probe.  max_windows bounds the grid; mode 0: no filter,
-// 1: LDS key filter and per-wave candidate queues, 2: LDS key filter, inline probe.
+// From this many segments on (a search of eight dependent loads) a dense scan
+// gets its tiles' segments from a launch before it.
+constexpr uint64_t kTileSegsMin = 256;
+// The sliding-window probe.  max_windows bounds the grid; mode 1: LDS key filter
+// on 32-bit hashes and per-wave candidate queues (dense or sampled hashes),
+// 2: LDS key filter on 61-bit fingerprints, inline probe.  tseg: null, or one
+// word per tile of kProbeTile windows and one more (scratch of dense scans, for
+// the tiles' segments; without it every tile searches for its segment).
 hipError_t launch_probe_scan(const PhaseArgs& a, const uint64_t* woff, bool has_odd,
-                             bool has_salt, uint64_t max_windows, int mode, hipStream_t s);
+                             bool has_salt, uint64_t max_windows, int mode, uint32_t* tseg,
+                             hipStream_t s);
 // The probe scan of a batch with text-local filters (probe_text.hip): resident
 // workgroups take spans of span_chunks * kProbeTile windows from *span_ctr
 // (zeroed by the caller); a window is tested against its own text's filter,

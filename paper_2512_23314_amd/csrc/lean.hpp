@@ -9,8 +9,9 @@
 // the byte that leaves and the byte that enters,
 //   h(i+1) = (h(i) - T[i] x^(L-1)) x + T[i+L]   (mod 2^32),
 // reading the two runs of bytes with three 8-byte loads each.  The short final
-// key of a text (shorter than the main windows) rolls its own hash the same
-// way from the same start.
+// key of a text (shorter than the main windows) is tested by its first eight
+// bytes, which the lane holds; the rare windows that agree in those form its
+// 32-bit hash from the samples, then its 61-bit one.
 #pragma once
 #include "common.hpp"
 #include "internal.hpp"
@@ -57,23 +58,25 @@ __device__ __forceinline__ void lean_chunk(const PhaseArgs& a, const uint64_t* _
   uint32_t t = (TEXT && w0 < W) ? a.lv.rtext[r] : 0;
   uint64_t salt = SALT ? a.tx.tsalt[t] : 0;
   on_text(t);
-  // the text's short final key, if any: length, position, 32-bit hash, x^oL
-  // and x^(oL-1)
-  uint64_t oL = 0, opos = 0;
-  uint32_t oh = 0, ox = 0, oxm1 = 0;
+  // the text's short final key, if any: length, position, and its first eight
+  // bytes (fewer when it is shorter) as a word and a mask
+  uint64_t oL = 0, opos = 0, okey = 0, omask = 0;
   const auto load_odd = [&]() {
     oL = a.odd.L[t];
     if (oL) {
       opos = a.odd.pos[t];
-      const uint64_t hx = a.odd.h32[t];
-      oh = (uint32_t)hx;
-      ox = (uint32_t)(hx >> 32);
-      oxm1 = ox * a.x32inv;
+      omask = oL < 8 ? (1ull << (8 * oL)) - 1 : ~0ull;
+      uint64_t hi;
+      bytes16_at(T, end, opos, okey, hi);
+      okey &= omask;
     }
   };
   if (ODD && w0 < W) load_odd();
-  // the short key's 61-bit fingerprint at i, against the key's
+  // a window at i that agrees in those bytes: the whole key's 32-bit hash, then
+  // its 61-bit fingerprint
   const auto odd61 = [&](uint64_t i) {
+    const uint64_t hx = a.odd.h32[t];
+    if (h32(i + oL) - h32(i) * (uint32_t)(hx >> 32) + (uint32_t)salt != (uint32_t)hx) return;
     uint64_t g = win61<true>(a, i, oL, a.odd.xp[t]);
     if (SALT) g = add61(g, salt);
     if ((g & fmask) == a.odd.fp[t] && i < a.odd.best[t])
@@ -92,16 +95,17 @@ __device__ __forceinline__ void lean_chunk(const PhaseArgs& a, const uint64_t* _
       bytes16_at(T, end, i0, olo, ohi);
       if (ODD && oL) {
         // the short key first (its windows fit wherever the main ones do,
-        // oL < L): a mask of the starts whose 32-bit hash matches, then the
-        // rare 61-bit checks
-        uint32_t ho = h32(i0 + oL) - hA * ox;
-        uint64_t plo, phi;
-        bytes16_at(T, end, i0 + oL, plo, phi);
+        // oL < L): a mask of the starts whose first bytes agree, then the rare
+        // whole checks
+        uint64_t nlo, nhi;  // the bytes after those that leave
+        bytes16_at(T, end, i0 + kLeanK, nlo, nhi);
         uint32_t om = 0;
 #pragma unroll
         for (int k = 0; k < kLeanK; ++k) {
-          if (k) ho = roll32(ho, byte_of16(olo, ohi, k - 1), byte_of16(plo, phi, k - 1), oxm1, x32);
-          if (i0 + k < opos && ho + s32 == oh) om |= 1u << k;
+          const uint64_t lo = k < 8 ? olo : ohi, hi = k < 8 ? ohi : nlo;
+          const int sh = 8 * (k & 7);
+          const uint64_t w = sh ? (lo >> sh) | (hi << (64 - sh)) : lo;
+          if (i0 + k < opos && (w & omask) == okey) om |= 1u << k;
         }
         while (om) {
           const int k = __builtin_ctz(om);
@@ -133,10 +137,10 @@ __device__ __forceinline__ void lean_chunk(const PhaseArgs& a, const uint64_t* _
 
   // per step, following the lane across segment (and text) boundaries: roll
   // while the windows stay consecutive, else start afresh from the samples.
-  // pi, opi: start of the hash held plus one, 0 = none (window starts can be
-  // 0, so "start + 1 == i" with a sentinel start would wrap onto them)
-  uint64_t pi = 0, opi = 0;
-  uint32_t h = 0, ho = 0;
+  // pi: start of the hash held plus one, 0 = none (window starts can be 0, so
+  // "start + 1 == i" with a sentinel start would wrap onto them)
+  uint64_t pi = 0;
+  uint32_t h = 0;
   for (int k = 0; k < kLeanK; ++k) {
     const uint64_t w = w0 + (uint64_t)k;
     const bool live = w < W;  // every lane stays in the loop (the queue is wave-wide)
@@ -154,10 +158,7 @@ __device__ __forceinline__ void lean_chunk(const PhaseArgs& a, const uint64_t* _
           t = nt;
           if (SALT) salt = a.tx.tsalt[t];
           on_text(t);
-          if (ODD) {
-            load_odd();
-            opi = 0;
-          }
+          if (ODD) load_odd();
         }
       }
     }
@@ -171,10 +172,9 @@ __device__ __forceinline__ void lean_chunk(const PhaseArgs& a, const uint64_t* _
     }
     push(cand, i, t);
     if (ODD && live && oL && i + oL <= re && i < opos) {
-      ho = (opi && i == opi) ? roll32(ho, T[i - 1], T[i - 1 + oL], oxm1, x32)
-                             : h32(i + oL) - h32(i) * ox;
-      opi = i + 1;
-      if (ho + (uint32_t)salt == oh) odd61(i);
+      uint64_t lo, hi;
+      bytes16_at(T, end, i, lo, hi);
+      if ((lo & omask) == okey) odd61(i);
     }
   }
 }

@@ -122,20 +122,17 @@ __global__ void k_keys(PhaseArgs a) {
         atomicOr(a.tf_words + a.tf_off[t] + tfilter_word(h, a.tf_wl[t]), tfilter_mask(h));
       }
       if (a.filt_bits) {
-        uint64_t f1, f2;
         if (a.pre32) {
           const uint32_t h = win32_any(a, st, L, a.x32L) + (uint32_t)a.tx.tsalt[t];
-          f1 = filter_bit32(h, a.filt_bits);
-          f2 = filter_bit32b(h, a.filt_bits);
+          atomicOr(&a.filt[filter32_word(h, a.filt_bits)], filter32_mask(h, a.filt_bits, a.filt_two));
           if (a.filt2_words)
             atomicOr(reinterpret_cast<unsigned long long*>(a.filt2) + filter2_word(h, a.filt2_words),
                      (unsigned long long)filter2_mask(h));
         } else {
-          f1 = filter_bit(fp, a.filt_bits);
-          f2 = filter_bit2(fp, a.filt_bits);
+          const uint64_t f1 = filter_bit(fp, a.filt_bits), f2 = filter_bit2(fp, a.filt_bits);
+          atomicOr(&a.filt[f1 >> 5], 1u << (f1 & 31));
+          if (a.filt_two) atomicOr(&a.filt[f2 >> 5], 1u << (f2 & 31));
         }
-        atomicOr(&a.filt[f1 >> 5], 1u << (f1 & 31));
-        if (a.filt_two) atomicOr(&a.filt[f2 >> 5], 1u << (f2 & 31));
       }
       if (a.bfilt_bits) set_prefix_bit(a, st);
     } else {
@@ -146,13 +143,17 @@ __global__ void k_keys(PhaseArgs a) {
       a.odd.fp[t] = fp;
       a.odd.pos[t] = st;
       a.odd.best[t] = st;
-      uint32_t x32p = 1, base = a.x32;  // x32^L
-      for (uint64_t e = L; e; e >>= 1) {
-        if (e & 1) x32p *= base;
-        base *= base;
-      }
-      const uint32_t h = win32_any(a, st, L, x32p) + (uint32_t)a.tx.tsalt[t];
-      a.odd.h32[t] = (uint64_t)h | ((uint64_t)x32p << 32);
+      const auto hash_of = [&](uint64_t len) {  // its first len bytes: hash, x32^len
+        uint32_t xp32 = 1, base = a.x32;
+        for (uint64_t e = len; e; e >>= 1) {
+          if (e & 1) xp32 *= base;
+          base *= base;
+        }
+        const uint32_t h = win32_any(a, st, len, xp32) + (uint32_t)a.tx.tsalt[t];
+        return (uint64_t)h | ((uint64_t)xp32 << 32);
+      };
+      a.odd.h32[t] = hash_of(L);
+      a.odd.anc[t] = hash_of(L < kOddAnchor ? L : kOddAnchor);
       if (a.bfilt_bits) set_prefix_bit(a, st);
     }
   }
@@ -488,96 +489,34 @@ __device__ __forceinline__ bool filter_has(const uint32_t* s_filt, uint64_t b1, 
 }
 
 
-// MODE 0 (kept in the template, not launched): no filter, every window probes
-// the table.  MODE 1: filter, and the
-// windows that pass go to a per-wave LDS queue; 64 queued windows at a time
-// then form their fingerprints and probe together, so a wave waits for one
-// round of loads per 64 candidates rather than per step.  MODE 2: filter,
-// candidates probe at once (no queue; texts beyond the queue's packing).
+// The queued scans: filter, and the windows that pass go to a per-wave LDS
+// queue; 64 queued windows at a time then form their fingerprints and probe
+// together, so a wave waits for one round of loads per 64 candidates rather
+// than per step.  The filter holds bits of the keys' 32-bit hashes (H[i+L] -
+// H[i] x32^L mod 2^32), and the scan reads only H for every window; the 61-bit
+// fingerprint is formed for queued windows alone.  Equal strings have equal
+// hashes of both kinds, so every occurrence of a key still reaches the table; a
+// window that agrees with a key in both hashes without being an occurrence is
+// a collision, caught by the same verification as before.
 //
-// PRE (MODE 1 only): the filter holds bits of the keys' 32-bit hashes
-// (H[i+L] - H[i] x32^L mod 2^32), and the scan reads only H for every window;
-// the 61-bit fingerprint is formed for queued windows alone.  Equal strings
-// have equal hashes of both kinds, so every occurrence of a key still reaches
-// the table; a window that agrees with a key in both hashes without being an
-// occurrence is a collision, caught by the same verification as before.
-//
-// A chunk in which every lane's 16 windows lie inside that lane's current
-// segment (the usual case on long runs) takes a straight-line path that issues
-// eight windows' hash loads together, before using any of them.
-//
-// LEAN: the 32-bit hashes are sampled (memory-lean builds) and lanes roll them
-// along consecutive windows (lean.hpp).  Queued windows form their 61-bit
-// fingerprints from dense prefix fingerprints when the build keeps them, else
-// from the samples.
-//
-// Instances without a short final key hold their registers (SGPRs included)
-// to two 1024-thread workgroups per CU, 8 waves per SIMD.  Instances with one
-// carry more live values (and load the short key's hashes with the main ones):
-// they run one workgroup per CU with up to 128 VGPRs, which measured faster
-// than spilling at 64.
-template <int MODE, bool ODD, bool SALT, bool PRE, bool LEAN>
-__global__ __launch_bounds__(kProbeThreads) __attribute__((amdgpu_waves_per_eu(ODD ? 4 : 8)))
-void k_probe_scan(PhaseArgs a, const uint64_t* __restrict__ woff) {
-  constexpr bool FILTER = MODE != 0;
-  static_assert(!PRE || MODE == 1, "the 32-bit hash feeds the queued filter only");
-  static_assert(!LEAN || MODE == 1, "sampled prefixes serve queued candidates only");
-  extern __shared__ uint64_t s_lds[];
-  const uint32_t fbits = a.filt_bits;
-  const bool two = a.filt_two != 0;
-  uint32_t* s_filt = reinterpret_cast<uint32_t*>(s_lds);
-  if (FILTER) {
-    const uint32_t nq = (uint32_t)(1ull << (fbits - 7));  // uint4 words
-    const uint4* src = reinterpret_cast<const uint4*>(a.filt);
-    uint4* dst = reinterpret_cast<uint4*>(s_filt);
-    for (uint32_t q = threadIdx.x; q < nq; q += blockDim.x) dst[q] = src[q];
-    __syncthreads();
-  }
-  const int lane = lane_id();
-  uint64_t* q = s_lds + (FILTER ? (1ull << (fbits - 6)) : 0) + (uint64_t)(threadIdx.x >> 6) * kQueue;
-  uint32_t qn = 0;  // wave-uniform queue length
-
-  const uint64_t R = a.lv.R;
-  const uint64_t W = woff[R];
-  const uint64_t gw = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-  const uint64_t nw = ((uint64_t)gridDim.x * blockDim.x) >> 6;
-  const uint64_t* __restrict__ P = a.P;
-  const uint32_t* __restrict__ H = a.P32;
-  const uint64_t* __restrict__ rs_ = a.lv.rs;
-  const uint64_t* __restrict__ re_ = a.lv.re;
-  const uint64_t L = a.Lmain, xL = a.xLmain, fmask = a.fpmask;
-  const uint32_t x32L = a.x32L;
-  Slot* __restrict__ slots = a.tab.slots;
-  const uint64_t mask = a.tab.mask;
-
-  const auto fp61 = [&](uint64_t i, uint64_t salt) {
-    uint64_t f = P ? sub61(P[i + L], mul61(P[i], xL)) : win61<true>(a, i, L, xL);
-    if (SALT) f = add61(f, salt);
-    return f & fmask;
-  };
-  const auto pass32 = [&](uint32_t h) {
-    const uint32_t b1 = filter_bit32(h, fbits);
-    return filter_has(s_filt, b1, two ? filter_bit32b(h, fbits) : b1);
-  };
-  const uint64_t* __restrict__ filt2 = reinterpret_cast<const uint64_t*>(a.filt2);
-  const uint32_t f2words = a.filt2_words;
-  const auto pass2 = [&](uint32_t h) {
-    const uint64_t m = filter2_mask(h);
-    return (filt2[filter2_word(h, f2words)] & m) == m;
-  };
-  const auto pass61 = [&](uint64_t f) {
-    const uint64_t b1 = filter_bit(f, fbits);
-    return filter_has(s_filt, b1, two ? filter_bit2(f, fbits) : b1);
-  };
-  // the entry this lane holds: form its fingerprint and probe
-  const auto probe_entry = [&](uint64_t e) {
-    const uint64_t i = e & kQPosMask;
-    const uint64_t salt = SALT ? a.tx.tsalt[e >> kQPosBits] : 0;
-    probe(slots, mask, fp61(i, salt), i);
-  };
-  // whole wave: append the lanes' candidates; probe 64 once 64 are waiting
+// One wave's queue and what a queued window does.
+template <bool SALT>
+struct ProbeQueue {
+  const PhaseArgs& a;
+  uint64_t* q;
+  const int lane;
+  uint32_t qn = 0;     // wave-uniform queue length
   uint64_t ncand = 0;  // wave-uniform: windows that passed the filters
-  const auto push = [&](bool cand, uint64_t i, uint32_t t) {
+  __device__ ProbeQueue(const PhaseArgs& args, uint64_t* queue) : a(args), q(queue), lane(lane_id()) {}
+  // the entry this lane holds: form its fingerprint and probe
+  __device__ __forceinline__ void probe_entry(uint64_t e) const {
+    const uint64_t i = e & kQPosMask;
+    uint64_t f = a.P ? sub61(a.P[i + a.Lmain], mul61(a.P[i], a.xLmain)) : win61<true>(a, i, a.Lmain, a.xLmain);
+    if (SALT) f = add61(f, a.tx.tsalt[e >> kQPosBits]);
+    probe(a.tab.slots, a.tab.mask, f & a.fpmask, i);
+  }
+  // whole wave: append the lanes' candidates; probe 64 once 64 are waiting
+  __device__ __forceinline__ void push(bool cand, uint64_t i, uint32_t t) {
     const uint64_t bal = __ballot(cand);
     if (!bal) return;
     const uint32_t my = (uint32_t)__popcll(bal & ((1ull << lane) - 1));
@@ -595,153 +534,276 @@ void k_probe_scan(PhaseArgs a, const uint64_t* __restrict__ woff) {
       probe_entry(e);
       wave_sync();
     }
+  }
+  __device__ __forceinline__ void finish() {
+    if (qn) {
+      wave_sync();
+      if ((uint32_t)lane < qn) probe_entry(q[lane]);
+    }
+    if (a.pc && lane == 0 && ncand) atomicAdd((unsigned long long*)(a.pc + kPcCand), (unsigned long long)ncand);
+  }
+};
+
+// Copy the phase's key filter into LDS.
+__device__ __forceinline__ void load_filter(const PhaseArgs& a, uint32_t* s_filt) {
+  const uint32_t nq = 1u << (a.filt_bits - 7);  // uint4 words
+  const uint4* src = reinterpret_cast<const uint4*>(a.filt);
+  uint4* dst = reinterpret_cast<uint4*>(s_filt);
+  for (uint32_t q = threadIdx.x; q < nq; q += blockDim.x) dst[q] = src[q];
+  __syncthreads();
+}
+
+// The segment of each tile's first window (tile ch: window number ch kScanChunk),
+// one thread per tile, so that a wave of the scan reads it with one load instead
+// of searching for it in log2(R) dependent ones.
+__global__ void k_tile_segs(const uint64_t* __restrict__ woff, uint64_t R, uint32_t* __restrict__ tseg) {
+  const uint64_t W = woff[R];
+  GRID_STRIDE(ch, (W + kScanChunk - 1) / kScanChunk) tseg[ch] = (uint32_t)segment_of(woff, R, ch * kScanChunk);
+}
+
+// The scan of a single text with dense 32-bit hashes (SALT: of a batch with
+// shared filters).
+//
+// What bounds it: at the upper levels the hash streams, at the lower ones (many
+// candidates) random reads.  Measured on 2^28 windows of the 256 MiB text,
+// reading H[i] and H[i+L] for every window ran at the fabric's 5.5 TB/s, 0.39 ms,
+// whatever L: the second stream is the first one L later, and few lines survive
+// in an XCD's L2 until then.  So where L is a multiple of the tile, a wave walks
+// a column: the tiles at i, i+L, i+2L, ..., `rows` of them, and the H[i+L] of one
+// row is the H[i] of the next, kept in registers.  That reads (rows + 1) / rows
+// streams in place of two.  Tiles are taken by their window numbers (units of
+// rows x stride tiles, stride = L / tile); a tile whose windows do not lie in one
+// segment, or do not continue the row above, loads both values as any tile did.
+// Measured, kernel time before and after (with the filter test of one LDS read
+// and candidates popped per lane): 2^28 windows at L = 2^21 0.393 -> 0.244 ms, at
+// L = 2^17 0.417 -> 0.265 ms; 2^31 windows at L = 2^19 3.32 -> 1.75 ms; 10^8
+// windows of a text with a short final key at L = 2^18 0.256 -> 0.150 ms.
+//
+// One 1024-thread workgroup per CU at up to 128 VGPRs: a lane's sixteen hashes of
+// a row and of the row before stay in registers and its loads leave together; the
+// LDS holds a 128 KiB filter (2^20 bits).  A text's short final key is tested by
+// its anchor, H[i + 64] (the value the lane holds for the next step).
+template <bool ODD, bool SALT>
+__global__ __launch_bounds__(kProbeThreads) __attribute__((amdgpu_waves_per_eu(4)))
+void k_probe_dense(PhaseArgs a, const uint64_t* __restrict__ woff, const uint32_t* __restrict__ tseg,
+                   uint64_t stride, uint64_t rows) {
+  extern __shared__ uint64_t s_lds[];
+  uint32_t* s_filt = reinterpret_cast<uint32_t*>(s_lds);
+  load_filter(a, s_filt);
+  const uint32_t fbits = a.filt_bits;
+  const bool two = a.filt_two != 0;
+  const int lane = lane_id();
+  ProbeQueue<SALT> queue(a, s_lds + (1ull << (fbits - 6)) + (uint64_t)(threadIdx.x >> 6) * kQueue);
+
+  const uint64_t R = a.lv.R;
+  const uint64_t W = woff[R];
+  const uint64_t tiles = (W + kScanChunk - 1) / kScanChunk;
+  // wave-uniform (all of a wave's lanes share threadIdx.x / 64)
+  const uint64_t gw = (uint64_t)blockIdx.x * (kProbeThreads / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint64_t nw = (uint64_t)gridDim.x * (kProbeThreads / 64);
+  const uint32_t* __restrict__ H = a.P32;
+  const uint64_t* __restrict__ rs_ = a.lv.rs;
+  const uint64_t* __restrict__ re_ = a.lv.re;
+  const uint64_t L = a.Lmain;
+  const uint32_t x32L = a.x32L;
+  const uint64_t* __restrict__ filt2 = reinterpret_cast<const uint64_t*>(a.filt2);
+  const uint32_t f2words = a.filt2_words;
+  const auto pass32 = [&](uint32_t h) {
+    const uint32_t m = filter32_mask(h, fbits, two);
+    return (s_filt[filter32_word(h, fbits)] & m) == m;
+  };
+  const auto pass2 = [&](uint32_t h) {
+    const uint64_t m = filter2_mask(h);
+    return (filt2[filter2_word(h, f2words)] & m) == m;
   };
 
-  for (uint64_t ch = gw; ch * kScanChunk < W; ch += nw) {
-    if constexpr (LEAN) {
-      // sampled hashes: consecutive windows per lane, rolled (lean.hpp)
-      const auto test8 = [&](const uint32_t* hv, bool* ok) {
-#pragma unroll
-        for (int k = 0; k < 8; ++k) ok[k] = pass32(hv[k]);
-        if (f2words) {
-          uint64_t wv[8];
-#pragma unroll
-          for (int k = 0; k < 8; ++k) wv[k] = ok[k] ? filt2[filter2_word(hv[k], f2words)] : ~0ull;
-#pragma unroll
-          for (int k = 0; k < 8; ++k) {
-            const uint64_t m = filter2_mask(hv[k]);
-            ok[k] = ok[k] && (wv[k] & m) == m;
-          }
-        }
-      };
-      const auto test1 = [&](uint32_t h) { return pass32(h) && (!f2words || pass2(h)); };
-      lean_chunk<ODD, ODD || SALT, SALT>(a, woff, 0, R, W, ch * kScanChunk + (uint64_t)lane * kLeanK,
-                                         [](uint32_t) {}, test8, test1, push);
-      continue;
-    }
-    const uint64_t w0 = ch * kScanChunk + lane;
-    uint64_t lo = 0, hi = R;
-    while (hi - lo > 1) {
-      const uint64_t mid = (lo + hi) >> 1;
-      if (woff[mid] <= w0) lo = mid; else hi = mid;
-    }
-    uint64_t r = lo;
-    uint64_t wo = woff[r], wn = woff[r + 1], rs = rs_[r], re = re_[r];
-    // lanes past the last window hold no segment: they read no text entry
-    uint32_t t = ((ODD || SALT) && w0 < W) ? a.lv.rtext[r] : 0;
-    uint64_t salt = SALT ? a.tx.tsalt[t] : 0;
-    // the text's short final key, if any (kept in registers while t holds)
-    uint64_t oL = 0, opos = 0;
-    uint32_t oh = 0, ox = 0;
-    const auto load_odd = [&]() {
+  // the text t's short final key, if any: its length, its position, and the
+  // length, hash and power of its anchor
+  uint32_t t = 0;
+  uint64_t salt = 0, oL = 0, opos = 0;
+  uint32_t oA = 0, oh = 0, ox = 0;
+  const auto load_text = [&](uint32_t nt) {
+    t = nt;
+    if (SALT) salt = a.tx.tsalt[t];
+    if (ODD) {
       oL = a.odd.L[t];
       if (oL) {
+        oA = (uint32_t)(oL < kOddAnchor ? oL : kOddAnchor);
         opos = a.odd.pos[t];
-        const uint64_t hx = a.odd.h32[t];
+        const uint64_t hx = a.odd.anc[t];
         oh = (uint32_t)hx;
         ox = (uint32_t)(hx >> 32);
       }
-    };
-    if (ODD && w0 < W) load_odd();
-    // the short key's 61-bit fingerprint at i, against the key's (text t)
-    const auto odd61 = [&](uint64_t i, uint64_t sl) {
-      uint64_t g = P ? sub61(P[i + oL], mul61(P[i], a.odd.xp[t])) : win61<true>(a, i, oL, a.odd.xp[t]);
-      if (SALT) g = add61(g, sl);
-      if ((g & fmask) == a.odd.fp[t] && i < a.odd.best[t])
-        atomicMin((unsigned long long*)&a.odd.best[t], (unsigned long long)i);
-    };
+    }
+  };
+  // a window at i that matches the anchor: the whole key's 32-bit hash, then
+  // its 61-bit fingerprint
+  const auto odd61 = [&](uint64_t i) {
+    const uint64_t hx = a.odd.h32[t];
+    if (H[i + oL] - H[i] * (uint32_t)(hx >> 32) + (uint32_t)salt != (uint32_t)hx) return;
+    uint64_t g = a.P ? sub61(a.P[i + oL], mul61(a.P[i], a.odd.xp[t])) : win61<true>(a, i, oL, a.odd.xp[t]);
+    if (SALT) g = add61(g, salt);
+    if ((g & a.fpmask) == a.odd.fp[t] && i < a.odd.best[t])
+      atomicMin((unsigned long long*)&a.odd.best[t], (unsigned long long)i);
+  };
 
-    // (the short final key's windows, shorter than the main ones, fit wherever
-    // a main window does; the unqueued scan tests it on the per-step path)
-    if (!ODD || PRE) {
-      const uint64_t wl = w0 + 64ull * (kScanK - 1);
-      const bool lane_ok = wl < wn && rs + (wl - wo) + L <= re;
-      if (__ballot(lane_ok) == ~0ull) {
-        const uint64_t i0 = rs + (w0 - wo);
+  const uint64_t units = (tiles + rows * stride - 1) / (rows * stride) * stride;
+  for (uint64_t u = gw; u < units; u += nw) {
+    uint32_t hp[kScanK];     // H[i + L] of the row above
+    uint64_t next = ~0ull;   // the position whose H they are (of lane 0, step 0)
+    uint64_t ch = u / stride * (rows * stride) + u % stride;
+    for (uint64_t row = 0; row < rows && ch < tiles; ++row, ch += stride) {
+      const uint64_t wb = ch * kScanChunk;
+      const uint64_t r0 = tseg ? tseg[ch] : segment_of(woff, R, wb);
+      const uint64_t wo0 = woff[r0], wn0 = woff[r0 + 1], rs0 = rs_[r0], re0 = re_[r0];
+      if (wb + kScanChunk <= wn0 && rs0 + (wb + kScanChunk - 1 - wo0) + L <= re0) {
+        // the tile's windows are consecutive positions of one segment
+        if (ODD || SALT) load_text(a.lv.rtext[r0]);
+        const uint64_t ib = rs0 + (wb - wo0);
+        const uint64_t i0 = ib + lane;
+        uint32_t ha[kScanK], hb[kScanK];
+        const bool keep = ib == next;
 #pragma unroll
-        for (int k0 = 0; k0 < kScanK; k0 += 8) {
-          if (PRE) {
-            const uint32_t s32 = SALT ? (uint32_t)salt : 0u;
-            // the sixteen loads leave together: the scheduler would otherwise
-            // pair each load with its use and wait out every latency in turn
-            uint32_t ha[8], hb[8], hc[8];
-            // (and the short key's, H[i + oL], where the text has one)
-            const bool oddk = ODD && oL;
+        for (int k = 0; k < kScanK; ++k) hb[k] = H[i0 + L + 64ull * k];
+        if (keep) {
 #pragma unroll
-            for (int k = 0; k < 8; ++k) {
-              const uint64_t i = i0 + 64ull * (k0 + k);
-              hb[k] = H[i + L];
-              ha[k] = H[i];
-              if (oddk) hc[k] = H[i + oL];
+          for (int k = 0; k < kScanK; ++k) ha[k] = hp[k];
+        } else {
+#pragma unroll
+          for (int k = 0; k < kScanK; ++k) ha[k] = H[i0 + 64ull * k];
+        }
+        const uint32_t s32 = SALT ? (uint32_t)salt : 0u;
+        if (ODD && oL) {
+          uint32_t om = 0;
+          if (oA == kOddAnchor) {  // H[i + 64] is the next step's H[i]
+            const uint32_t hl = H[i0 + 64ull * kScanK];
+#pragma unroll
+            for (int k = 0; k < kScanK; ++k) {
+              const uint32_t hc = k + 1 < kScanK ? ha[k + 1 < kScanK ? k + 1 : k] : hl;
+              if (hc - ha[k] * ox + s32 == oh) om |= 1u << k;
             }
-            __builtin_amdgcn_sched_barrier(0);
-            uint32_t hv[8];
-#pragma unroll
-            for (int k = 0; k < 8; ++k) hv[k] = hb[k] - ha[k] * x32L + s32;
-            if (oddk) {
-              // the short key's 32-bit hashes (loaded with the others); the rare
-              // matches form their 61-bit fingerprints one at a time
-              uint32_t om = 0;
-#pragma unroll
-              for (int k = 0; k < 8; ++k) {
-                const uint64_t i = i0 + 64ull * (k0 + k);
-                if (i < opos && hc[k] - ha[k] * ox + s32 == oh) om |= 1u << k;
-              }
-              while (om) {
-                const int k = __builtin_ctz(om);
-                om &= om - 1;
-                odd61(i0 + 64ull * (k0 + k), salt);
-              }
-            }
-            bool ok[8];
-#pragma unroll
-            for (int k = 0; k < 8; ++k) ok[k] = pass32(hv[k]);
-            if (f2words) {
-              // second filter: the eight steps' loads are issued together
-              uint64_t wv[8];
-#pragma unroll
-              for (int k = 0; k < 8; ++k) wv[k] = ok[k] ? filt2[filter2_word(hv[k], f2words)] : ~0ull;
-#pragma unroll
-              for (int k = 0; k < 8; ++k) {
-                const uint64_t m = filter2_mask(hv[k]);
-                ok[k] = ok[k] && (wv[k] & m) == m;
-              }
-            }
-#pragma unroll
-            for (int k = 0; k < 8; ++k) push(ok[k], i0 + 64ull * (k0 + k), t);
           } else {
-            uint64_t fv[8];
 #pragma unroll
-            for (int k = 0; k < 8; ++k) fv[k] = fp61(i0 + 64ull * (k0 + k), salt);
-#pragma unroll
-            for (int k = 0; k < 8; ++k) {
-              const uint64_t i = i0 + 64ull * (k0 + k);
-              const bool cand = FILTER ? pass61(fv[k]) : true;
-              if (MODE == 1) {
-                push(cand, i, t);
-              } else {
-                ncand += (uint64_t)__popcll(__ballot(cand));
-                if (cand) probe(slots, mask, fv[k], i);
-              }
-            }
+            for (int k = 0; k < kScanK; ++k)
+              if (H[i0 + 64ull * k + oA] - ha[k] * ox + s32 == oh) om |= 1u << k;
           }
+          while (om) {
+            const int k = __builtin_ctz(om);
+            om &= om - 1;
+            if (i0 + 64ull * k < opos) odd61(i0 + 64ull * k);
+          }
+        }
+        uint32_t hv[kScanK];
+        uint32_t okm = 0;  // bit k: the lane's window of step k passes
+#pragma unroll
+        for (int k = 0; k < kScanK; ++k) {
+          hv[k] = hb[k] - ha[k] * x32L + s32;
+          hp[k] = hb[k];
+          okm |= pass32(hv[k]) ? 1u << k : 0u;
+        }
+        next = ib + L;
+        if (!__ballot(okm != 0)) continue;
+        if (f2words) {
+          // second filter: the steps' loads are issued together
+          uint64_t wv[kScanK];
+#pragma unroll
+          for (int k = 0; k < kScanK; ++k)
+            wv[k] = (okm >> k) & 1 ? filt2[filter2_word(hv[k], f2words)] : 0ull;
+#pragma unroll
+          for (int k = 0; k < kScanK; ++k) {
+            const uint64_t m = filter2_mask(hv[k]);
+            if ((wv[k] & m) != m) okm &= ~(1u << k);
+          }
+        }
+        // as many rounds as the lane with the most candidates has
+        while (__ballot(okm != 0)) {
+          queue.push(okm != 0, i0 + 64ull * (okm ? __builtin_ctz(okm) : 0), t);
+          okm &= okm - 1;
         }
         continue;
       }
-    }
 
-    if constexpr (PRE && !SALT) {
-      // One text (its short key stays): the chunk crosses segments.  Per group
-      // of steps each lane first follows its windows across the segments, then
-      // the group's loads leave together.
+      // the tile crosses segments (or holds windows that do not fit, or ends
+      // the scan): each lane finds its first window's segment
+      next = ~0ull;
+      const uint64_t w0 = wb + lane;
+      const uint64_t rh = tseg && wb + kScanChunk < W ? (uint64_t)tseg[ch + 1] + 1 : R;
+      uint64_t r = segment_in(woff, r0, rh, w0);
+      uint64_t wo = woff[r], wn = woff[r + 1], rs = rs_[r], re = re_[r];
+      // lanes past the last window hold no segment: they read no text entry
+      if (ODD || SALT) {
+        oL = 0;
+        if (w0 < W) load_text(a.lv.rtext[r]);
+      }
+      if constexpr (!SALT) {
+        // One text (its short key stays).  Per group of steps each lane first
+        // follows its windows across the segments, then the group's loads
+        // leave together.
 #pragma unroll
-      for (int k0 = 0; k0 < kScanK; k0 += kScanSlowGroup) {
-        uint64_t ik[kScanSlowGroup];
-        uint32_t vm = 0, om = 0;  // steps with a main-length window, with a short-key window
+        for (int k0 = 0; k0 < kScanK; k0 += kScanSlowGroup) {
+          uint64_t ik[kScanSlowGroup];
+          uint32_t vm = 0, om = 0;  // steps with a main-length window, with a short-key window
 #pragma unroll
-        for (int k = 0; k < kScanSlowGroup; ++k) {
-          const uint64_t w = w0 + 64ull * (k0 + k);
-          const bool live = w < W;
+          for (int k = 0; k < kScanSlowGroup; ++k) {
+            const uint64_t w = w0 + 64ull * (k0 + k);
+            const bool live = w < W;
+            if (live && w >= wn) {
+              do {
+                ++r;
+                wo = wn;
+                wn = woff[r + 1];
+              } while (w >= wn);
+              rs = rs_[r];
+              re = re_[r];
+            }
+            const uint64_t i = rs + (w - wo);
+            ik[k] = i;
+            if (live && i + L <= re) vm |= 1u << k;
+            if (ODD && live && oL && i + oL <= re && i < opos) om |= 1u << k;
+          }
+          uint32_t ha[kScanSlowGroup], hb[kScanSlowGroup], hc[kScanSlowGroup];
+#pragma unroll
+          for (int k = 0; k < kScanSlowGroup; ++k) {
+            hb[k] = ((vm >> k) & 1) ? H[ik[k] + L] : 0u;
+            ha[k] = (((vm | om) >> k) & 1) ? H[ik[k]] : 0u;
+            if (ODD) hc[k] = ((om >> k) & 1) ? H[ik[k] + oA] : 0u;
+          }
+          __builtin_amdgcn_sched_barrier(0);
+          if (ODD) {
+            uint32_t mm = 0;
+#pragma unroll
+            for (int k = 0; k < kScanSlowGroup; ++k)
+              if (((om >> k) & 1) && hc[k] - ha[k] * ox == oh) mm |= 1u << k;
+            while (mm) {
+              const int k = __builtin_ctz(mm);
+              mm &= mm - 1;
+              odd61(ik[k]);
+            }
+          }
+          uint32_t hv[kScanSlowGroup];
+          bool ok[kScanSlowGroup];
+#pragma unroll
+          for (int k = 0; k < kScanSlowGroup; ++k) {
+            hv[k] = hb[k] - ha[k] * x32L;
+            ok[k] = ((vm >> k) & 1) && pass32(hv[k]);
+          }
+          if (f2words) {
+            uint64_t wv[kScanSlowGroup];
+#pragma unroll
+            for (int k = 0; k < kScanSlowGroup; ++k) wv[k] = ok[k] ? filt2[filter2_word(hv[k], f2words)] : ~0ull;
+#pragma unroll
+            for (int k = 0; k < kScanSlowGroup; ++k) {
+              const uint64_t m = filter2_mask(hv[k]);
+              ok[k] = ok[k] && (wv[k] & m) == m;
+            }
+          }
+#pragma unroll
+          for (int k = 0; k < kScanSlowGroup; ++k) queue.push(ok[k], ik[k], t);
+        }
+      } else {
+        for (int k = 0; k < kScanK; ++k) {
+          const uint64_t w = w0 + (uint64_t)k * 64;
+          const bool live = w < W;  // every lane stays in the loop (the queue is wave-wide)
           if (live && w >= wn) {
             do {
               ++r;
@@ -750,96 +812,129 @@ void k_probe_scan(PhaseArgs a, const uint64_t* __restrict__ woff) {
             } while (w >= wn);
             rs = rs_[r];
             re = re_[r];
+            load_text(a.lv.rtext[r]);
           }
           const uint64_t i = rs + (w - wo);
-          ik[k] = i;
-          if (live && i + L <= re) vm |= 1u << k;
-          if (ODD && live && oL && i + oL <= re && i < opos) om |= 1u << k;
-        }
-        uint32_t ha[kScanSlowGroup], hb[kScanSlowGroup], hc[kScanSlowGroup];
-#pragma unroll
-        for (int k = 0; k < kScanSlowGroup; ++k) {
-          hb[k] = ((vm >> k) & 1) ? H[ik[k] + L] : 0u;
-          ha[k] = (((vm | om) >> k) & 1) ? H[ik[k]] : 0u;
-          if (ODD) hc[k] = ((om >> k) & 1) ? H[ik[k] + oL] : 0u;
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        if (ODD) {
-          uint32_t mm = 0;
-#pragma unroll
-          for (int k = 0; k < kScanSlowGroup; ++k)
-            if (((om >> k) & 1) && hc[k] - ha[k] * ox == oh) mm |= 1u << k;
-          while (mm) {
-            const int k = __builtin_ctz(mm);
-            mm &= mm - 1;
-            odd61(ik[k], 0);
+          bool cand = false;
+          if (live && i + L <= re) {
+            const uint32_t h = H[i + L] - H[i] * x32L + (uint32_t)salt;
+            cand = pass32(h) && (!f2words || pass2(h));
+          }
+          queue.push(cand, i, t);
+          if (ODD && live && oL && i + oL <= re && i < opos) {
+            if (H[i + oA] - H[i] * ox + (uint32_t)salt == oh) odd61(i);
           }
         }
-        uint32_t hv[kScanSlowGroup];
-        bool ok[kScanSlowGroup];
-#pragma unroll
-        for (int k = 0; k < kScanSlowGroup; ++k) {
-          hv[k] = hb[k] - ha[k] * x32L;
-          ok[k] = ((vm >> k) & 1) && pass32(hv[k]);
-        }
-        if (f2words) {
-          uint64_t wv[kScanSlowGroup];
-#pragma unroll
-          for (int k = 0; k < kScanSlowGroup; ++k) wv[k] = ok[k] ? filt2[filter2_word(hv[k], f2words)] : ~0ull;
-#pragma unroll
-          for (int k = 0; k < kScanSlowGroup; ++k) {
-            const uint64_t m = filter2_mask(hv[k]);
-            ok[k] = ok[k] && (wv[k] & m) == m;
-          }
-        }
-#pragma unroll
-        for (int k = 0; k < kScanSlowGroup; ++k) push(ok[k], ik[k], t);
       }
-      continue;
     }
+  }
+  queue.finish();
+}
 
+// The scan of memory-lean builds (LEAN: the 32-bit hashes are sampled and lanes
+// roll them along consecutive windows, lean.hpp; queued windows form their
+// 61-bit fingerprints from the samples), and the scan without queues (every
+// window's 61-bit fingerprint against the filter, candidates probe at once) for
+// texts beyond the queue's packing.
+//
+// Instances without a short final key hold their registers (SGPRs included)
+// to two 1024-thread workgroups per CU, 8 waves per SIMD.  Instances with one
+// carry more live values: they run one workgroup per CU with up to 128 VGPRs,
+// which measured faster than spilling at 64.
+template <bool ODD, bool SALT, bool LEAN>
+__global__ __launch_bounds__(kProbeThreads) __attribute__((amdgpu_waves_per_eu(ODD ? 4 : 8)))
+void k_probe_scan(PhaseArgs a, const uint64_t* __restrict__ woff) {
+  extern __shared__ uint64_t s_lds[];
+  uint32_t* s_filt = reinterpret_cast<uint32_t*>(s_lds);
+  load_filter(a, s_filt);
+  const uint32_t fbits = a.filt_bits;
+  const bool two = a.filt_two != 0;
+  const int lane = lane_id();
+  const uint64_t R = a.lv.R;
+  const uint64_t W = woff[R];
+  const uint64_t gw = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+  const uint64_t nw = ((uint64_t)gridDim.x * blockDim.x) >> 6;
+
+  if constexpr (LEAN) {
+    ProbeQueue<SALT> queue(a, s_lds + (1ull << (fbits - 6)) + (uint64_t)(threadIdx.x >> 6) * kQueue);
+    const uint64_t* __restrict__ filt2 = reinterpret_cast<const uint64_t*>(a.filt2);
+    const uint32_t f2words = a.filt2_words;
+    const auto pass32 = [&](uint32_t h) {
+      const uint32_t m = filter32_mask(h, fbits, two);
+      return (s_filt[filter32_word(h, fbits)] & m) == m;
+    };
+    const auto test8 = [&](const uint32_t* hv, bool* ok) {
+#pragma unroll
+      for (int k = 0; k < 8; ++k) ok[k] = pass32(hv[k]);
+      if (f2words) {
+        uint64_t wv[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) wv[k] = ok[k] ? filt2[filter2_word(hv[k], f2words)] : ~0ull;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+          const uint64_t m = filter2_mask(hv[k]);
+          ok[k] = ok[k] && (wv[k] & m) == m;
+        }
+      }
+    };
+    const auto test1 = [&](uint32_t h) {
+      const uint64_t m = filter2_mask(h);
+      return pass32(h) && (!f2words || (filt2[filter2_word(h, f2words)] & m) == m);
+    };
+    const auto push = [&](bool cand, uint64_t i, uint32_t t) { queue.push(cand, i, t); };
+    for (uint64_t ch = gw; ch * kScanChunk < W; ch += nw)
+      lean_chunk<ODD, ODD || SALT, SALT>(a, woff, 0, R, W, ch * kScanChunk + (uint64_t)lane * kLeanK,
+                                         [](uint32_t) {}, test8, test1, push);
+    queue.finish();
+    return;
+  }
+
+  uint64_t ncand = 0;
+  const uint64_t* __restrict__ P = a.P;
+  const uint64_t L = a.Lmain, xL = a.xLmain, fmask = a.fpmask;
+  for (uint64_t ch = gw; ch * kScanChunk < W; ch += nw) {
+    const uint64_t w0 = ch * kScanChunk + lane;
+    uint64_t r = segment_of(woff, R, w0);
+    uint64_t wo = woff[r], wn = woff[r + 1], rs = a.lv.rs[r], re = a.lv.re[r];
+    // lanes past the last window hold no segment: they read no text entry
+    uint32_t t = ((ODD || SALT) && w0 < W) ? a.lv.rtext[r] : 0;
+    uint64_t salt = SALT ? a.tx.tsalt[t] : 0;
+    uint64_t oL = (ODD && w0 < W) ? a.odd.L[t] : 0;
+    const auto fp_of = [&](uint64_t i, uint64_t len, uint64_t xp) {
+      uint64_t f = sub61(P[i + len], mul61(P[i], xp));
+      if (SALT) f = add61(f, salt);
+      return f & fmask;
+    };
     for (int k = 0; k < kScanK; ++k) {
       const uint64_t w = w0 + (uint64_t)k * 64;
-      const bool live = w < W;  // every lane stays in the loop (the queue is wave-wide)
-      if (live && w >= wn) {
+      if (w >= W) break;
+      if (w >= wn) {
         do {
           ++r;
           wo = wn;
           wn = woff[r + 1];
         } while (w >= wn);
-        rs = rs_[r];
-        re = re_[r];
+        rs = a.lv.rs[r];
+        re = a.lv.re[r];
         if (ODD || SALT) t = a.lv.rtext[r];
         if (SALT) salt = a.tx.tsalt[t];
-        if (ODD) load_odd();
+        if (ODD) oL = a.odd.L[t];
       }
       const uint64_t i = rs + (w - wo);
-      bool cand = false;
-      if (live && i + L <= re) {
-        if (PRE) {
-          const uint32_t h = H[i + L] - H[i] * x32L + (SALT ? (uint32_t)salt : 0u);
-          cand = pass32(h) && (!f2words || pass2(h));
-        } else {
-          const uint64_t f = fp61(i, salt);
-          cand = FILTER ? pass61(f) : true;
-          if (MODE != 1 && cand) probe(slots, mask, f, i);
+      if (i + L <= re) {
+        const uint64_t f = fp_of(i, L, xL);
+        const uint64_t b1 = filter_bit(f, fbits);
+        if (filter_has(s_filt, b1, two ? filter_bit2(f, fbits) : b1)) {
+          ++ncand;
+          probe(a.tab.slots, a.tab.mask, f, i);
         }
       }
-      if (MODE == 1) push(cand, i, t);
-      else ncand += (uint64_t)__popcll(__ballot(cand));
-      // the short key: its 32-bit hash first (equal strings always agree),
-      // the 61-bit fingerprint only where that matches
-      if (ODD && live && oL && i + oL <= re && i < opos) {
-        const uint32_t ho = H[i + oL] - H[i] * ox + (SALT ? (uint32_t)salt : 0u);
-        if (ho == oh) odd61(i, salt);
-      }
+      if (ODD && oL && i + oL <= re && i < a.odd.pos[t] && fp_of(i, oL, a.odd.xp[t]) == a.odd.fp[t] &&
+          i < a.odd.best[t])
+        atomicMin((unsigned long long*)&a.odd.best[t], (unsigned long long)i);
     }
   }
-  if (MODE == 1 && qn) {
-    wave_sync();
-    if ((uint32_t)lane < qn) probe_entry(q[lane]);
-  }
-  if (a.pc && lane == 0 && ncand) atomicAdd((unsigned long long*)(a.pc + kPcCand), (unsigned long long)ncand);
+  if (a.pc) wave_count(a.pc + kPcCand, ncand);
 }
 
 // Dynamic LDS beyond 64 KiB has to be allowed per kernel.
@@ -847,60 +942,56 @@ static hipError_t allow_lds(const void* fn, size_t bytes) {
   return hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
 }
 
+// Rows of a column walk: as many as leave every resident wave (256 workgroups of
+// 16) four units, at most 16 (17/16 streams).
+static uint64_t column_rows(uint64_t tiles, uint64_t stride) {
+  uint64_t rows = tiles / (4 * 256 * (kProbeThreads / 64));
+  if (rows > 16) rows = 16;
+  if (rows * stride > tiles) rows = tiles / stride;
+  return rows ? rows : 1;
+}
+
 hipError_t launch_probe_scan(const PhaseArgs& a, const uint64_t* woff, bool has_odd,
-                             bool has_salt, uint64_t max_windows, int mode, hipStream_t s) {
+                             bool has_salt, uint64_t max_windows, int mode, uint32_t* tseg,
+                             hipStream_t s) {
   if (a.lv.R == 0) return hipSuccess;
-  const uint64_t waves = (max_windows + kScanChunk - 1) / kScanChunk;
-  // two 1024-thread workgroups per CU: LDS of at most 80 KiB each (mode 1:
-  // filter up to 64 KiB + queues 16 KiB; mode 2: filter up to 64 KiB)
-  const unsigned grid = grid_for(waves * 64, kProbeThreads, 512);
-  size_t lds = 0;
-  if (mode == 1)
-    lds = ((size_t)1 << (a.filt_bits - 3)) + (size_t)(kProbeThreads / 64) * kQueue * 8;
-  else if (mode == 2)
-    lds = (size_t)1 << (a.filt_bits - 3);
-  // the keys filled the filter from the hash kind that pre32 names
-  if (a.pre32 && mode != 1) return hipErrorInvalidValue;
-  const bool pre = a.pre32 != 0;
-#define BT_PROBE_LAUNCH(M, O, S, Q, LN)                                                  \
-  do {                                                                                   \
-    if (lds > 65536) {                                                                   \
-      const hipError_t e = allow_lds(reinterpret_cast<const void*>(&k_probe_scan<M, O, S, Q, LN>), lds); \
-      if (e != hipSuccess) return e;                                                     \
-    }                                                                                    \
-    k_probe_scan<M, O, S, Q, LN><<<grid, kProbeThreads, lds, s>>>(a, woff);              \
-  } while (0)
-#define BT_PROBE_SALT(M, O, Q, LN) \
-  if (has_salt) BT_PROBE_LAUNCH(M, O, true, Q, LN); else BT_PROBE_LAUNCH(M, O, false, Q, LN);
-  // sampled fingerprints serve queued candidates only; sampled 32-bit hashes
-  // take the rolled window loop (the LEAN instances)
-  if (a.P == nullptr && mode != 1) return hipErrorInvalidValue;
+  const uint64_t tiles = (max_windows + kScanChunk - 1) / kScanChunk;
+  // the filter, and in queued scans 16 KiB of queues
+  const size_t lds = ((size_t)1 << (a.filt_bits - 3)) +
+                     (mode == 1 ? (size_t)(kProbeThreads / 64) * kQueue * 8 : 0);
   const bool lean = a.P32 == nullptr;
-  if (mode == 1) {
-    if (!pre) return hipErrorInvalidValue;  // queued scans always pre-filter
-    if (lean) {
-      if (has_odd) {
-        BT_PROBE_SALT(1, true, true, true)
-      } else {
-        BT_PROBE_SALT(1, false, true, true)
-      }
-    } else if (has_odd) {
-      BT_PROBE_SALT(1, true, true, false)
-    } else {
-      BT_PROBE_SALT(1, false, true, false)
+  // queued scans pre-filter on 32-bit hashes; sampled fingerprints serve queued
+  // candidates only
+  if ((mode == 1) != (a.pre32 != 0) || (mode != 1 && mode != 2) || (a.P == nullptr && mode != 1))
+    return hipErrorInvalidValue;
+  const auto launch = [&](auto* fn, unsigned grid, auto... args) {
+    if (lds > 65536) {
+      const hipError_t e = allow_lds(reinterpret_cast<const void*>(fn), lds);
+      if (e != hipSuccess) return e;
     }
-  } else if (mode == 2) {
-    if (has_odd) {
-      BT_PROBE_SALT(2, true, false, false)
-    } else {
-      BT_PROBE_SALT(2, false, false, false)
-    }
-  } else {
-    return hipErrorInvalidValue;  // every scan filters (mode 1 or 2)
+    fn<<<grid, kProbeThreads, lds, s>>>(a, woff, args...);
+    return hipGetLastError();
+  };
+  if (mode == 1 && !lean) {
+    if (tseg) k_tile_segs<<<grid_for(tiles, 256), 256, 0, s>>>(woff, a.lv.R, tseg);
+    const uint64_t stride = a.Lmain % kScanChunk == 0 && a.Lmain / kScanChunk < tiles ? a.Lmain / kScanChunk : 1;
+    const uint64_t rows = stride * kScanChunk == a.Lmain ? column_rows(tiles, stride) : 1;
+    const unsigned grid = grid_for(tiles * 64, kProbeThreads, 256);
+    const uint32_t* ts = tseg;
+    if (has_odd)
+      return has_salt ? launch(&k_probe_dense<true, true>, grid, ts, stride, rows)
+                      : launch(&k_probe_dense<true, false>, grid, ts, stride, rows);
+    return has_salt ? launch(&k_probe_dense<false, true>, grid, ts, stride, rows)
+                    : launch(&k_probe_dense<false, false>, grid, ts, stride, rows);
   }
-#undef BT_PROBE_SALT
-#undef BT_PROBE_LAUNCH
-  return hipGetLastError();
+  // two 1024-thread workgroups per CU: LDS of at most 80 KiB each
+  const unsigned grid = grid_for(tiles * 64, kProbeThreads, 512);
+  if (mode == 1) {
+    if (has_odd) return has_salt ? launch(&k_probe_scan<true, true, true>, grid) : launch(&k_probe_scan<true, false, true>, grid);
+    return has_salt ? launch(&k_probe_scan<false, true, true>, grid) : launch(&k_probe_scan<false, false, true>, grid);
+  }
+  if (has_odd) return has_salt ? launch(&k_probe_scan<true, true, false>, grid) : launch(&k_probe_scan<true, false, false>, grid);
+  return has_salt ? launch(&k_probe_scan<false, true, false>, grid) : launch(&k_probe_scan<false, false, false>, grid);
 }
 
 // ---------------------------------------------------------------- byte scan (a4)

@@ -180,21 +180,26 @@ void k_probe_text(PhaseArgs a, const uint64_t* __restrict__ woff, uint64_t span_
     const auto pass_word = [&](uint32_t h) -> uint32_t {
       return LDS ? s_filt[tfilter_word(h, lwl)] : tfw[toff + tfilter_word(h, twl)];
     };
-    // the text's short final key, if any (kept in registers while t holds)
+    // the text's short final key, if any (kept in registers while t holds):
+    // its length, the length, hash and power of its anchor
     uint64_t oL = 0, opos = 0;
-    uint32_t oh = 0, ox = 0;
+    uint32_t oA = 0, oh = 0, ox = 0;
     const auto load_odd = [&]() {
       oL = a.odd.L[t];
       if (oL) {
+        oA = (uint32_t)(oL < kOddAnchor ? oL : kOddAnchor);
         opos = a.odd.pos[t];
-        const uint64_t hx = a.odd.h32[t];
+        const uint64_t hx = a.odd.anc[t];
         oh = (uint32_t)hx;
         ox = (uint32_t)(hx >> 32);
       }
     };
     if (ODD && w0 < W) load_odd();
-    // the short key's 61-bit fingerprint at i, against the key's (text t)
+    // a window at i that matches the anchor: the whole key's 32-bit hash, then
+    // its 61-bit fingerprint (text t)
     const auto odd61 = [&](uint64_t i, uint64_t sl) {
+      const uint64_t hx = a.odd.h32[t];
+      if (H[i + oL] - H[i] * (uint32_t)(hx >> 32) + (uint32_t)sl != (uint32_t)hx) return;
       uint64_t g = P ? sub61(P[i + oL], mul61(P[i], a.odd.xp[t])) : win61<true>(a, i, oL, a.odd.xp[t]);
       g = add61(g, sl);
       if ((g & fmask) == a.odd.fp[t] && i < a.odd.best[t])
@@ -214,22 +219,22 @@ void k_probe_text(PhaseArgs a, const uint64_t* __restrict__ woff, uint64_t span_
           // together: the scheduler would otherwise pair each load with its
           // use and wait out every latency in turn
           uint32_t ha[kTlGroup], hb[kTlGroup], hc[kTlGroup];
-          // (and the short key's, H[i + oL], where the text has one)
+          // (and the short key's anchor's, H[i + oA], where the text has one)
           const bool oddk = ODD && oL;
 #pragma unroll
           for (int k = 0; k < kTlGroup; ++k) {
             const uint64_t i = i0 + 64ull * (k0 + k);
             hb[k] = H[i + L];
             ha[k] = H[i];
-            if (oddk) hc[k] = H[i + oL];
+            if (oddk) hc[k] = H[i + oA];
           }
           __builtin_amdgcn_sched_barrier(0);
           uint32_t hv[kTlGroup];
 #pragma unroll
           for (int k = 0; k < kTlGroup; ++k) hv[k] = hb[k] - ha[k] * x32L + s32;
           if (oddk) {
-            // the short key's 32-bit hashes (loaded with the others); the rare
-            // matches form their 61-bit fingerprints one at a time
+            // the short key's anchor hashes; the rare matches compare the
+            // whole key one at a time
             uint32_t om = 0;
 #pragma unroll
             for (int k = 0; k < kTlGroup; ++k) {
@@ -339,7 +344,7 @@ void k_probe_text(PhaseArgs a, const uint64_t* __restrict__ woff, uint64_t span_
         for (int k = 0; k < kTlSlowGroup; ++k) {
           hb[k] = ((vm >> k) & 1) ? H[ik[k] + L] : 0u;
           ha[k] = (((vm | om) >> k) & 1) ? H[ik[k]] : 0u;
-          if (ODD) hc[k] = ((om >> k) & 1) ? H[ik[k] + oL] : 0u;
+          if (ODD) hc[k] = ((om >> k) & 1) ? H[ik[k] + oA] : 0u;
         }
         __builtin_amdgcn_sched_barrier(0);
         if (ODD) {
@@ -409,10 +414,10 @@ void k_probe_text(PhaseArgs a, const uint64_t* __restrict__ woff, uint64_t span_
         if (LDS && big && cand) cand = (tfw[toff + tfilter_word(h, twl)] & m) == m;
       }
       push(cand, i, t);
-      // the short key: its 32-bit hash first (equal strings always agree),
-      // the 61-bit fingerprint only where that matches
+      // the short key: its anchor's hash first (equal strings always agree),
+      // the whole key only where that matches
       if (ODD && live && oL && i + oL <= re && i < opos) {
-        const uint32_t ho = H[i + oL] - H[i] * ox + (uint32_t)salt;
+        const uint32_t ho = H[i + oA] - H[i] * ox + (uint32_t)salt;
         if (ho == oh) odd61(i, salt);
       }
     }
