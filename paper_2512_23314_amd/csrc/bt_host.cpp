@@ -608,6 +608,15 @@ uint64_t pow2_at_least(uint64_t v) {
 }
 
 
+// Single-text scans of at least this many keys and windows go in rounds: a round
+// costs two launches, its filters' clearing and a pass over the keys (about 0.1 ms
+// at 2^19 keys), and what it saves grows with both.  At 256 MiB (2^18 to 2^20
+// keys, below 2^28 windows) rounds lost, 12.0 -> 12.1 ms per build against 10.5
+// without; at 2 GiB (2^19 to 2^24 keys) they took the scans of L = 2048, 512, 256,
+// 128 and 64 from 12.2, 36.8, 18.0, 15.3 and 6.5 ms to 8.6, 14.0, 6.4, 7.5 and 3.0.
+constexpr uint64_t kRoundKeys = 1ull << 19;
+constexpr uint64_t kRoundWindows = 1ull << 28;
+
 // Per-text, per-level bookkeeping collected on the host.
 struct TextLevelRec {
   uint64_t b, c, u, word_off, ptr_off, first;
@@ -1084,7 +1093,7 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
     a.x32inv = host_inv32(x32);
     a.tx = tx;
     a.lv = lv;
-    a.k = KeysDev{kfp.p, klen.p, kslot.p, klm.p};
+    a.k = KeysDev{kfp.p, klen.p, kslot.p, klm.p, nullptr};
     a.odd = OddDev{oddb.p,         oddb.p + T,     oddb.p + 2 * T, oddb.p + 3 * T,
                    oddb.p + 4 * T, oddb.p + 5 * T, oddb.p + 6 * T, oddb.p + 7 * T};
     a.x32 = x32;
@@ -1227,6 +1236,36 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
       a.bfilt_bits = bbits;
       a.x32L = host_pow32(x32, a.Lmain);
       a.x32Lm1 = host_pow32(x32, a.Lmain ? a.Lmain - 1 : 0);
+      // Scans of many windows for many keys of one text go in rounds (see
+      // k_refilter).  The first is short (the first copies of most keys lie in
+      // it, and it alone pays for all of them), the others even; other splits
+      // (1 4 16 32 48, 1 4 16, doubling ones, nine) measured 1 to 10% slower.
+      std::vector<uint32_t> rounds{64};
+      if (!text_local && !byte_scan && scan_mode == 1 && !has_salt && nkeys >= kRoundKeys &&
+          c * b >= kRoundWindows && !(prm.debug_flags & BT_DBG_SORT_PHASES))
+        rounds = {2, 16, 32, 48, 64};
+      Buf<uint32_t> kh32;
+      if (rounds.size() > 1) kh32 = alloc<uint32_t>(ctx, c);
+      a.k.h32 = kh32.p;
+      const auto scan_rounds = [&](const PhaseArgs& as, const uint64_t* swoff,
+                                   const std::vector<uint32_t>& ends, uint32_t* tseg) {
+        uint32_t from = 0;
+        for (uint32_t to : ends) {
+          if (from) {
+            FillList f;
+            f.add(filt.p, (1ull << a.filt_bits) / 32, 0);
+            if (a.filt2_words) f.add(filt2.p, 2ull << a.filt2_words, 0);
+            hipError_t e = launch_fill_many(f, s);
+            if (e == hipSuccess) e = launch_refilter(as, swoff, from, s);
+            if (e != hipSuccess) return e;
+          }
+          const hipError_t e = launch_probe_scan(as, swoff, has_odd, has_salt, c * b, scan_mode,
+                                                 tseg, from, to, s);
+          if (e != hipSuccess) return e;
+          from = to;
+        }
+        return hipSuccess;
+      };
       {
         FillList f;
         f.add(tab.p, 4 * cap, ~0u);  // empty slots: fp = best = ~0
@@ -1337,8 +1376,7 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
           // earlier) are short against a tile at the lowest levels
           return text_local ? launch_probe_text(as, swoff, has_odd, c * b, span_chunks, span_ctr.p,
                                                 span_info.p, phase == 2 && b <= 64, s)
-                            : launch_probe_scan(as, swoff, has_odd, has_salt, c * b, scan_mode,
-                                                tseg.p, s);
+                            : scan_rounds(as, swoff, rounds, tseg.p);
         }, a.Lmain);
       }
       HIPCHK(ctx, launch_resolve(a, vb, s));

@@ -70,6 +70,7 @@ struct KeysDev {
   uint64_t* len;    // [c]
   uint32_t* slot;   // [c] table slot, kNoKey, kOddKey or kCopyKey
   uint64_t* lm;     // [c] leftmost occurrence (result)
+  uint32_t* h32;    // [c] 32-bit hash of a main-length key, for launch_refilter; or null
 };
 
 // Keys whose length differs from the phase's main length (at most one per
@@ -281,9 +282,13 @@ constexpr uint64_t kTileSegsMin = 256;
 // 2: LDS key filter on 61-bit fingerprints, inline probe.  tseg: null, or one
 // word per tile of kProbeTile windows and one more (scratch of dense scans, for
 // the tiles' segments; without it every tile searches for its segment).
+// Queued scans may go in rounds: [f0, f1) are 64ths of the tiles (0, 64: all).
 hipError_t launch_probe_scan(const PhaseArgs& a, const uint64_t* woff, bool has_odd,
                              bool has_salt, uint64_t max_windows, int mode, uint32_t* tseg,
-                             hipStream_t s);
+                             uint32_t f0, uint32_t f1, hipStream_t s);
+// Between rounds (filters cleared by the caller): sets the filter bits of the
+// keys that windows from tile 64ths f0 on can still improve.
+hipError_t launch_refilter(const PhaseArgs& a, const uint64_t* woff, uint32_t f0, hipStream_t s);
 // The probe scan of a batch with text-local filters (probe_text.hip): resident
 // workgroups take spans of span_chunks * kProbeTile windows from *span_ctr
 // (zeroed by the caller); a window is tested against its own text's filter,

@@ -124,6 +124,7 @@ __global__ void k_keys(PhaseArgs a) {
       if (a.filt_bits) {
         if (a.pre32) {
           const uint32_t h = win32_any(a, st, L, a.x32L) + (uint32_t)a.tx.tsalt[t];
+          if (a.k.h32) a.k.h32[j] = h;
           atomicOr(&a.filt[filter32_word(h, a.filt_bits)], filter32_mask(h, a.filt_bits, a.filt_two));
           if (a.filt2_words)
             atomicOr(reinterpret_cast<unsigned long long*>(a.filt2) + filter2_word(h, a.filt2_words),
@@ -553,6 +554,44 @@ __device__ __forceinline__ void load_filter(const PhaseArgs& a, uint32_t* s_filt
   __syncthreads();
 }
 
+// The first tile of 64th f of the scan (f = 64: past the last).
+__device__ __forceinline__ uint64_t round_tile(uint64_t W, uint32_t f) {
+  const uint64_t tiles = (W + kScanChunk - 1) / kScanChunk;
+  return tiles / 64 * f + tiles % 64 * f / 64;
+}
+
+// Rounds.  Windows are numbered in the order of their positions, so once the
+// tiles below some tile are scanned, a key whose smallest position lies below
+// that tile's first one has its leftmost occurrence: no later window can improve
+// it.  The filters of the next round hold the other keys only.  In a repetitive
+// text most keys occur in its first copies, and the windows of all later copies,
+// true occurrences that would each read a slot and two prefix values for
+// nothing, now fail the filter; and of the keys that occur nowhere earlier, those
+// that start before the round drop out.
+__global__ void k_refilter(PhaseArgs a, const uint64_t* __restrict__ woff, uint32_t f0) {
+  const uint64_t R = a.lv.R, W = woff[R];
+  const uint64_t w = round_tile(W, f0) * kScanChunk;
+  if (w >= W) return;
+  const uint64_t r = segment_of(woff, R, w);
+  const uint64_t from = a.lv.rs[r] + (w - woff[r]);
+  GRID_STRIDE(j, a.lv.c) {
+    const uint32_t s = a.k.slot[j];
+    if (s == kNoKey || s == kOddKey || s == kCopyKey || a.lv.st[j] < from) continue;
+    if (a.tab.slots[s].best < from) continue;
+    const uint32_t h = a.k.h32[j];
+    atomicOr(&a.filt[filter32_word(h, a.filt_bits)], filter32_mask(h, a.filt_bits, a.filt_two));
+    if (a.filt2_words)
+      atomicOr(reinterpret_cast<unsigned long long*>(a.filt2) + filter2_word(h, a.filt2_words),
+               (unsigned long long)filter2_mask(h));
+  }
+}
+
+hipError_t launch_refilter(const PhaseArgs& a, const uint64_t* woff, uint32_t f0, hipStream_t s) {
+  if (!a.pre32 || !a.filt_bits || !a.k.h32) return hipErrorInvalidValue;
+  k_refilter<<<grid_for(a.lv.c, 256), 256, 0, s>>>(a, woff, f0);
+  return hipGetLastError();
+}
+
 // The segment of each tile's first window (tile ch: window number ch kScanChunk),
 // one thread per tile, so that a wave of the scan reads it with one load instead
 // of searching for it in log2(R) dependent ones.
@@ -585,8 +624,8 @@ __global__ void k_tile_segs(const uint64_t* __restrict__ woff, uint64_t R, uint3
 // its anchor, H[i + 64] (the value the lane holds for the next step).
 template <bool ODD, bool SALT>
 __global__ __launch_bounds__(kProbeThreads) __attribute__((amdgpu_waves_per_eu(4)))
-void k_probe_dense(PhaseArgs a, const uint64_t* __restrict__ woff, const uint32_t* __restrict__ tseg,
-                   uint64_t stride, uint64_t rows) {
+void k_probe_dense(PhaseArgs a, const uint64_t* __restrict__ woff, uint32_t f0, uint32_t f1,
+                   const uint32_t* __restrict__ tseg, uint64_t stride, uint64_t rows) {
   extern __shared__ uint64_t s_lds[];
   uint32_t* s_filt = reinterpret_cast<uint32_t*>(s_lds);
   load_filter(a, s_filt);
@@ -597,7 +636,7 @@ void k_probe_dense(PhaseArgs a, const uint64_t* __restrict__ woff, const uint32_
 
   const uint64_t R = a.lv.R;
   const uint64_t W = woff[R];
-  const uint64_t tiles = (W + kScanChunk - 1) / kScanChunk;
+  const uint64_t t0 = round_tile(W, f0), t1 = round_tile(W, f1);
   // wave-uniform (all of a wave's lanes share threadIdx.x / 64)
   const uint64_t gw = (uint64_t)blockIdx.x * (kProbeThreads / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint64_t nw = (uint64_t)gridDim.x * (kProbeThreads / 64);
@@ -647,12 +686,12 @@ void k_probe_dense(PhaseArgs a, const uint64_t* __restrict__ woff, const uint32_
       atomicMin((unsigned long long*)&a.odd.best[t], (unsigned long long)i);
   };
 
-  const uint64_t units = (tiles + rows * stride - 1) / (rows * stride) * stride;
+  const uint64_t units = (t1 - t0 + rows * stride - 1) / (rows * stride) * stride;
   for (uint64_t u = gw; u < units; u += nw) {
     uint32_t hp[kScanK];     // H[i + L] of the row above
     uint64_t next = ~0ull;   // the position whose H they are (of lane 0, step 0)
-    uint64_t ch = u / stride * (rows * stride) + u % stride;
-    for (uint64_t row = 0; row < rows && ch < tiles; ++row, ch += stride) {
+    uint64_t ch = t0 + u / stride * (rows * stride) + u % stride;
+    for (uint64_t row = 0; row < rows && ch < t1; ++row, ch += stride) {
       const uint64_t wb = ch * kScanChunk;
       const uint64_t r0 = tseg ? tseg[ch] : segment_of(woff, R, wb);
       const uint64_t wo0 = woff[r0], wn0 = woff[r0 + 1], rs0 = rs_[r0], re0 = re_[r0];
@@ -843,7 +882,7 @@ void k_probe_dense(PhaseArgs a, const uint64_t* __restrict__ woff, const uint32_
 // which measured faster than spilling at 64.
 template <bool ODD, bool SALT, bool LEAN>
 __global__ __launch_bounds__(kProbeThreads) __attribute__((amdgpu_waves_per_eu(ODD ? 4 : 8)))
-void k_probe_scan(PhaseArgs a, const uint64_t* __restrict__ woff) {
+void k_probe_scan(PhaseArgs a, const uint64_t* __restrict__ woff, uint32_t f0, uint32_t f1) {
   extern __shared__ uint64_t s_lds[];
   uint32_t* s_filt = reinterpret_cast<uint32_t*>(s_lds);
   load_filter(a, s_filt);
@@ -882,7 +921,8 @@ void k_probe_scan(PhaseArgs a, const uint64_t* __restrict__ woff) {
       return pass32(h) && (!f2words || (filt2[filter2_word(h, f2words)] & m) == m);
     };
     const auto push = [&](bool cand, uint64_t i, uint32_t t) { queue.push(cand, i, t); };
-    for (uint64_t ch = gw; ch * kScanChunk < W; ch += nw)
+    const uint64_t t1 = round_tile(W, f1);
+    for (uint64_t ch = round_tile(W, f0) + gw; ch < t1; ch += nw)
       lean_chunk<ODD, ODD || SALT, SALT>(a, woff, 0, R, W, ch * kScanChunk + (uint64_t)lane * kLeanK,
                                          [](uint32_t) {}, test8, test1, push);
     queue.finish();
@@ -953,9 +993,11 @@ static uint64_t column_rows(uint64_t tiles, uint64_t stride) {
 
 hipError_t launch_probe_scan(const PhaseArgs& a, const uint64_t* woff, bool has_odd,
                              bool has_salt, uint64_t max_windows, int mode, uint32_t* tseg,
-                             hipStream_t s) {
+                             uint32_t f0, uint32_t f1, hipStream_t s) {
   if (a.lv.R == 0) return hipSuccess;
-  const uint64_t tiles = (max_windows + kScanChunk - 1) / kScanChunk;
+  if (f0 >= f1 || f1 > 64 || (mode != 1 && (f0 != 0 || f1 != 64))) return hipErrorInvalidValue;
+  const uint64_t all = (max_windows + kScanChunk - 1) / kScanChunk;
+  const uint64_t tiles = (all * (f1 - f0) + 63) / 64;
   // the filter, and in queued scans 16 KiB of queues
   const size_t lds = ((size_t)1 << (a.filt_bits - 3)) +
                      (mode == 1 ? (size_t)(kProbeThreads / 64) * kQueue * 8 : 0);
@@ -969,11 +1011,11 @@ hipError_t launch_probe_scan(const PhaseArgs& a, const uint64_t* woff, bool has_
       const hipError_t e = allow_lds(reinterpret_cast<const void*>(fn), lds);
       if (e != hipSuccess) return e;
     }
-    fn<<<grid, kProbeThreads, lds, s>>>(a, woff, args...);
+    fn<<<grid, kProbeThreads, lds, s>>>(a, woff, f0, f1, args...);
     return hipGetLastError();
   };
   if (mode == 1 && !lean) {
-    if (tseg) k_tile_segs<<<grid_for(tiles, 256), 256, 0, s>>>(woff, a.lv.R, tseg);
+    if (tseg && f0 == 0) k_tile_segs<<<grid_for(all, 256), 256, 0, s>>>(woff, a.lv.R, tseg);
     const uint64_t stride = a.Lmain % kScanChunk == 0 && a.Lmain / kScanChunk < tiles ? a.Lmain / kScanChunk : 1;
     const uint64_t rows = stride * kScanChunk == a.Lmain ? column_rows(tiles, stride) : 1;
     const unsigned grid = grid_for(tiles * 64, kProbeThreads, 256);
