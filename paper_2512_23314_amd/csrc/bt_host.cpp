@@ -679,22 +679,51 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
   const uint64_t fpmask = (prm.debug_flags & BT_DBG_WEAK_HASH) ? 0xFFFull : ~0ull;
   const bool has_salt = T > 1;
 
-  // ---- texts
-  std::vector<uint64_t> h_tx(3 * (size_t)T), h_n(T);
-  uint64_t sm = prm.hash_seed ^ 0x5A17ull;
-  for (uint32_t t = 0; t < T; ++t) {
-    h_tx[t] = offs[t];
-    h_tx[T + t] = offs[t + 1];
-    h_tx[2 * T + t] = has_salt ? splitmix64(sm) % kP61Host : 0;
-    h_n[t] = offs[t + 1] - offs[t];
+  // ---- texts (one upload: starts, ends, salts, level-0 block counts and their
+  // prefix, entry steps, and the non-empty texts in the order they enter)
+  const auto b_at = [&](uint32_t step) {
+    uint64_t b = prm.leaf_len;
+    for (uint32_t k = step + 1; k < H; ++k) b *= prm.tau;
+    return b;
+  };
+  std::vector<uint64_t> h_n(T), h_tcount(T, 0), h_tfirst(T + 1, 0);
+  std::vector<uint32_t> id_first(H + 1, 0);  // entering texts of step k: ids [id_first[k], id_first[k+1])
+  const uint64_t tx_words = 5 * (uint64_t)T + 1 + (T + 1);
+  Buf<uint64_t> d_tx = alloc<uint64_t>(ctx, tx_words);
+  {
+    std::vector<uint64_t> up(tx_words, 0);
+    uint32_t* estep = reinterpret_cast<uint32_t*>(up.data() + 5 * (uint64_t)T + 1);
+    uint32_t* ids = estep + T;
+    uint64_t sm = prm.hash_seed ^ 0x5A17ull;
+    for (uint32_t t = 0; t < T; ++t) {
+      up[t] = offs[t];
+      up[T + t] = offs[t + 1];
+      up[2 * (uint64_t)T + t] = has_salt ? splitmix64(sm) % kP61Host : 0;
+      h_n[t] = offs[t + 1] - offs[t];
+      estep[t] = H - plan[t].h;
+      if (estep[t] == 0) h_tcount[t] = (h_n[t] + b_at(0) - 1) / b_at(0);
+      h_tfirst[t + 1] = h_tfirst[t] + h_tcount[t];
+      if (h_n[t]) ++id_first[estep[t] + 1];
+    }
+    for (uint32_t k = 0; k < H; ++k) id_first[k + 1] += id_first[k];
+    std::vector<uint32_t> at(id_first.begin(), id_first.end());
+    for (uint32_t t = 0; t < T; ++t)
+      if (h_n[t]) ids[at[estep[t]]++] = t;
+    std::memcpy(up.data() + 3 * (uint64_t)T, h_tcount.data(), T * 8);
+    std::memcpy(up.data() + 4 * (uint64_t)T, h_tfirst.data(), (T + 1) * 8);
+    upload(ctx, d_tx.p, up.data(), tx_words);
   }
-  Buf<uint64_t> d_tx = alloc<uint64_t>(ctx, 3 * (uint64_t)T);
-  upload(ctx, d_tx.p, h_tx.data(), 3 * (uint64_t)T);
-  TextsDev tx{T, d_tx.p, d_tx.p + T, d_tx.p + 2 * T};
+  TextsDev tx{T, d_tx.p, d_tx.p + T, d_tx.p + 2 * (uint64_t)T};
+  const uint32_t* d_estep = reinterpret_cast<const uint32_t*>(d_tx.p + 5 * (uint64_t)T + 1);
+  const uint32_t* d_ids = d_estep + T;
 
-  // ---- which byte values occur (read back after the prefix scan is queued)
-  Buf<uint64_t> d_seen = alloc<uint64_t>(ctx, 4);
-  HIPCHK(ctx, launch_fill_u64(d_seen.p, 0, 4, s));
+  // ---- small device words, zero at first: which byte values occur (4), the
+  // pointer check's error word, a level's totals (3) and segment counts (2)
+  Buf<uint64_t> d_small = alloc<uint64_t>(ctx, 10);
+  HIPCHK(ctx, launch_fill_u64(d_small.p, 0, 10, s));
+  struct {
+    uint64_t* p;
+  } d_seen{d_small.p}, d_err{d_small.p + 4}, lvl_totals{d_small.p + 5}, segn{d_small.p + 8};
   HIPCHK(ctx, launch_byte_presence(d_base + o0, N, reinterpret_cast<uint32_t*>(d_seen.p), s));
 
   // ---- step a2: prefix fingerprints of the concatenation, once, and in the
@@ -729,22 +758,30 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
   // P[i] belongs to text position i (never read below o0); null when sampled
   const uint64_t* P = (sample_p || quarter_p) ? nullptr : d_P.p - o0;
 
-  // ---- distinct byte values must not exceed sigma; dense symbols for rank/select
-  std::vector<uint64_t> seen;
-  read_words(ctx, {{d_seen.p, 4}}, seen);
+  // ---- distinct byte values must not exceed sigma (read with the first level's
+  // counts; rank/select needs them now, for its dense symbols)
   uint32_t S = 0;
   std::vector<int16_t> h_sym(256, -1);
   std::vector<uint8_t> h_byte_of;
-  for (int ch = 0; ch < 256; ++ch)
-    if ((seen[ch >> 6] >> (ch & 63)) & 1) {
-      h_sym[ch] = (int16_t)S++;
-      h_byte_of.push_back((uint8_t)ch);
+  bool seen_read = false;
+  const auto check_seen = [&](const uint64_t* seen) {
+    seen_read = true;
+    for (int ch = 0; ch < 256; ++ch)
+      if ((seen[ch >> 6] >> (ch & 63)) & 1) {
+        h_sym[ch] = (int16_t)S++;
+        h_byte_of.push_back((uint8_t)ch);
+      }
+    if (S > sigma) {
+      ctx->err = "the text has " + std::to_string(S) + " distinct byte values, more than sigma";
+      throw Fail{BT_E_INVAL};
     }
-  if (S > sigma) {
-    ctx->err = "the text has " + std::to_string(S) + " distinct byte values, more than sigma";
-    return BT_E_INVAL;
-  }
+  };
   const bool with_rank = (prm.flags & BT_WITH_RANK_SELECT) != 0;
+  if (with_rank) {
+    std::vector<uint64_t> seen;
+    read_words(ctx, {{d_seen.p, 4}}, seen);
+    check_seen(seen.data());
+  }
   if (with_rank)
     for (uint32_t t = 0; t < T; ++t)
       if (h_n[t] >= (1ull << 32)) {
@@ -792,9 +829,7 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
   for (uint32_t t = 0; t < T; ++t) rec[t].resize(plan[t].h);
   std::vector<LevelBufs> lbufs(H);  // by step
   uint8_t* leaves = nullptr;
-  std::vector<uint64_t> leaf_off(T, 0), leaf_bytes(T, 0);
-  Buf<uint64_t> d_err = alloc<uint64_t>(ctx, 1);
-  HIPCHK(ctx, launch_fill_u64(d_err.p, 0, 1, s));
+  std::vector<uint64_t> leaf_off(T, 0);
   Buf<uint64_t> wstats = alloc<uint64_t>(ctx, 2 * (uint64_t)H + 2);
   // per (step, phase) device counters while profiling (PhaseArgs.pc)
   Buf<uint64_t> pstats;
@@ -809,35 +844,39 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
   Buf<uint64_t> st;
   Buf<uint32_t> text;
   // scan entries of the current level (from the previous level's split; see
-  // "scan segments" in level.hip); E_ent = 0 means "one entry per run"
+  // "scan segments" in level_pass.hip), and its blocks' parent facts
   uint64_t E_ent = 0;
   Buf<uint64_t> ent_a, ent_e, ent_child;
-  Buf<uint8_t> ent_f;
-  bool have_entries = false;
-  std::vector<uint64_t> h_tcount(T, 0), h_tfirst(T + 1, 0);
-  Buf<uint64_t> d_tcount = alloc<uint64_t>(ctx, T + 1), d_tfirst = alloc<uint64_t>(ctx, T + 1);
+  Buf<uint8_t> ent_f, cflag;
+  // per text, this level's blocks and their prefix (level 0: in d_tx)
+  Buf<uint64_t> d_tcount, d_tfirst;
+  const uint64_t *tcp = d_tx.p + 3 * (uint64_t)T, *tfp = d_tx.p + 4 * (uint64_t)T;
   Buf<uint64_t> scan_tmp;
   auto scan = [&](uint64_t* a, uint64_t n) {
     const uint64_t w = scan_tmp_words(n);
     if (!scan_tmp.p || scan_tmp.n < w) scan_tmp = alloc<uint64_t>(ctx, std::max<uint64_t>(w, 1024));
     HIPCHK(ctx, scan_excl_u64(a, n, scan_tmp.p, s));
   };
-  const auto b_at = [&](uint32_t step) {
-    uint64_t b = prm.leaf_len;
-    for (uint32_t k = step + 1; k < H; ++k) b *= prm.tau;
-    return b;
+  // the level passes' prefix sums (scan_pass.hpp)
+  Buf<uint64_t> pass_words;
+  uint64_t pass_tiles = 0, pass_tickets = 0, pass_epoch = 0;
+  const auto next_scan = [&](uint64_t n) {
+    const uint64_t tiles = scan_pass_tiles(n);
+    if (tiles > pass_tiles || pass_epoch + 1 >= (1ull << 22)) {
+      pass_tiles = std::max<uint64_t>(tiles, std::max<uint64_t>(64, 2 * pass_tiles));
+      pass_words = alloc<uint64_t>(ctx, 3 * pass_tiles + 1);
+      HIPCHK(ctx, launch_fill_u64(pass_words.p, 0, 3 * pass_tiles + 1, s));
+      pass_tickets = pass_epoch = 0;
+    }
+    ScanDev sd{pass_words.p, pass_tiles, pass_words.p + 3 * pass_tiles, pass_tickets, ++pass_epoch};
+    pass_tickets += tiles;
+    return sd;
   };
-  // texts whose level 1 is the level of `step`, and their level-1 block counts
-  auto entering = [&](uint32_t step, std::vector<uint32_t>& ids, std::vector<uint64_t>& cnt,
-                      uint64_t b) {
-    ids.clear();
-    cnt.assign(T, 0);
-    for (uint32_t t = 0; t < T; ++t)
-      if (H - plan[t].h == step) {
-        ids.push_back(t);
-        cnt[t] = (h_n[t] + b - 1) / b;
-      }
-  };
+  // pinned words the level's counts are written to (k_texts)
+  constexpr uint64_t kHostTotals = 8;
+  uint64_t* const h_lvl = small_host(ctx, kHostTotals + 2 * (uint64_t)T);
+  uint64_t* d_lvl = nullptr;
+  HIPCHK(ctx, hipHostGetDevicePointer((void**)&d_lvl, h_lvl, 0));
   const auto check_runs = [&](uint64_t device_R, uint64_t R) {
     if (device_R != R) {
       ctx->err = "internal: predicted run count differs from the device's";
@@ -893,21 +932,21 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
                          Buf<uint64_t>& spb, Buf<uint64_t>& spo, uint64_t u,
                          const std::vector<uint64_t>& tcount, const std::vector<uint64_t>& tfirst,
                          const std::vector<uint64_t>& tu, const uint64_t* d_tf,
-                         const uint64_t* d_tc) {
+                         const uint64_t* d_tc, const uint64_t* d_wo) {
     std::vector<uint64_t> h_woff(T + 1, 0), h_poff(T + 1, 0);
     for (uint32_t t = 0; t < T; ++t) {
       h_woff[t + 1] = h_woff[t] + (tcount[t] + 63) / 64;
       h_poff[t + 1] = h_poff[t] + tu[t];
     }
     const uint64_t nwords = h_woff[T];
-    Buf<uint64_t> d_woff = alloc<uint64_t>(ctx, T + 1);
-    upload(ctx, d_woff.p, h_woff.data(), T + 1);
+    Buf<uint64_t> up_woff;  // word offsets per text, when not on the device yet
+    if (!d_wo) {
+      up_woff = alloc<uint64_t>(ctx, T + 1);
+      upload(ctx, up_woff.p, h_woff.data(), T + 1);
+      d_wo = up_woff.p;
+    }
     Buf<uint64_t> words = alloc<uint64_t>(ctx, nwords), wrank = alloc<uint64_t>(ctx, nwords + 1);
-    Buf<uint64_t> wtmp = alloc<uint64_t>(ctx, nwords + 1);
-    HIPCHK(ctx, launch_pack_marks(marked, T, d_tf, d_tc, d_woff.p, nwords, words.p, s));
-    HIPCHK(ctx, launch_word_pop(words.p, nwords, wtmp.p, s));
-    scan(wtmp.p, nwords);
-    HIPCHK(ctx, launch_word_rank(wtmp.p, T, d_woff.p, nwords, wrank.p, s));
+    HIPCHK(ctx, launch_store_marks(marked, uoff, T, d_tf, d_tc, d_wo, nwords, words.p, wrank.p, s));
     LevelBufs LB;
     LB.words = store->add(std::move(words), nwords);
     LB.wrank = store->add(std::move(wrank), nwords + 1);
@@ -934,12 +973,14 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
         rec[t][step - (H - plan[t].h)] = {b, tcount[t], tu[t], h_woff[t], h_poff[t], tfirst[t]};
   };
   // ---- tree storage of the leaf level: block j's bytes at j*b (only a text's
-  // last block is short, and it ends the text's region).  When runs_at is given,
-  // the device's run count there is checked against R in the same read-back.
+  // last block is short, and it ends the text's region; its length is read at
+  // the end of the build).
+  Buf<uint64_t> d_last = alloc<uint64_t>(ctx, T);
+  std::vector<uint64_t> leaf_count(T, 0);
   auto store_leaf_level = [&](uint32_t step, uint64_t b, uint64_t c, const uint64_t* st,
                               const uint32_t* text, const std::vector<uint64_t>& tcount,
                               const std::vector<uint64_t>& tfirst, const uint64_t* d_tf,
-                              const uint64_t* d_tc, const uint64_t* runs_at, uint64_t R) {
+                              const uint64_t* d_tc) {
     LevelDev lvl{c, b, st, text, nullptr, 0, nullptr, nullptr, nullptr};
     Buf<uint8_t> lb = alloc<uint8_t>(ctx, c * b);
     HIPCHK(ctx, launch_leaves(d_base, lvl, tx, lb.p, s));
@@ -951,14 +992,10 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
       rank_counts(step, b, c, st, text, d_tf, tcount, tfirst, A, LL);
     }
     lbufs[step] = std::move(LL);
-    Buf<uint64_t> d_last = alloc<uint64_t>(ctx, T);
     HIPCHK(ctx, launch_last_block_len(lvl, tx, d_tf, d_tc, d_last.p, s));
-    std::vector<uint64_t> last;
-    read_words(ctx, {{d_last.p, T}, {runs_at, runs_at ? 1u : 0u}}, last);
-    if (runs_at) check_runs(last[T], R);
+    leaf_count = tcount;
     for (uint32_t t = 0; t < T; ++t) {
       leaf_off[t] = tfirst[t] * b;
-      leaf_bytes[t] = tcount[t] ? (tcount[t] - 1) * b + last[t] : 0;
       rec[t][plan[t].h - 1] = {b, tcount[t], 0, 0, 0, tfirst[t]};
     }
   };
@@ -968,29 +1005,29 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
   // on its level, and where each block's children start.
   struct PruneLevel {
     uint64_t b = 0, c = 0;
-    Buf<uint64_t> st, lm, cs, tfirst, tcount;
+    Buf<uint64_t> st, lm, cs, tfirst, tcount;  // (level 0's tfirst and tcount: in d_tx)
+    const uint64_t *tfp = nullptr, *tcp = nullptr;
     Buf<uint32_t> text, run;
     Buf<uint8_t> marked;
     std::vector<uint64_t> h_tcount, h_tfirst;
   };
   std::vector<PruneLevel> pl(prune ? H : 0);
 
+  const auto alloc_next = [&](uint64_t cn, uint64_t En, Buf<uint64_t>& nst, Buf<uint32_t>& ntext) {
+    nst = alloc<uint64_t>(ctx, cn);
+    ntext = alloc<uint32_t>(ctx, cn);
+    cflag = alloc<uint8_t>(ctx, cn);
+    ent_a = alloc<uint64_t>(ctx, En);
+    ent_e = alloc<uint64_t>(ctx, En);
+    ent_child = alloc<uint64_t>(ctx, En);
+    ent_f = alloc<uint8_t>(ctx, En);
+    return NextLevel{nst.p, ntext.p, cflag.p, ent_a.p, ent_e.p, ent_f.p, ent_child.p};
+  };
+  c = h_tfirst[T];
+  E_ent = id_first[1];
   {
-    const uint64_t b0 = b_at(0);
-    std::vector<uint32_t> ids;
-    std::vector<uint64_t> cnt;
-    entering(0, ids, cnt, b0);
-    for (uint32_t t = 0; t < T; ++t) h_tfirst[t + 1] = h_tfirst[t] + cnt[t];
-    c = h_tfirst[T];
-    h_tcount = cnt;
-    upload(ctx, d_tcount.p, h_tcount.data(), T);
-    upload(ctx, d_tfirst.p, h_tfirst.data(), T + 1);
-    st = alloc<uint64_t>(ctx, c);
-    text = alloc<uint32_t>(ctx, c);
-    Buf<uint32_t> d_ids = alloc<uint32_t>(ctx, ids.size());
-    upload(ctx, d_ids.p, ids.data(), ids.size());
-    HIPCHK(ctx, launch_write_entering(d_ids.p, (uint32_t)ids.size(), tx, b0, d_tfirst.p, st.p,
-                                      text.p, s));
+    const NextLevel nl = alloc_next(c, E_ent, st, text);
+    HIPCHK(ctx, launch_enter(d_ids, id_first[1], tx, b_at(0), tfp, 0, nl, s));
   }
 
   // Runs of the first level: one per non-empty text that enters there.  Each
@@ -1004,41 +1041,10 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
     const uint64_t b = b_at(step);
     const bool leaf_step = (step == H - 1);
 
-    // runs of this level (maximal sequences of consecutive blocks of one text)
-    Buf<uint64_t> roff = alloc<uint64_t>(ctx, c + 1);
-    Buf<uint32_t> run = alloc<uint32_t>(ctx, c);
-    HIPCHK(ctx, launch_run_flags(st.p, text.p, c, b, roff.p, s));
-    scan(roff.p, c);
-    const uint64_t R = R_pred;
-    // sized by c, which bounds any run count: the run table is indexed by the
-    // device's own count, which is checked against R only later
-    Buf<uint64_t> rs = alloc<uint64_t>(ctx, c), re = alloc<uint64_t>(ctx, c);
-    Buf<uint32_t> rtext = alloc<uint32_t>(ctx, c);
-    HIPCHK(ctx, launch_run_table(st.p, text.p, c, b, tx, roff.p, run.p, rs.p, re.p, rtext.p, s));
-    LevelDev lv{c, b, st.p, text.p, run.p, R, rs.p, re.p, rtext.p};
-    Buf<uint32_t> ent_run;
-    if (!leaf_step) {
-      if (!have_entries) {
-        E_ent = R;
-        ent_a = alloc<uint64_t>(ctx, R);
-        ent_e = alloc<uint64_t>(ctx, R);
-        ent_f = alloc<uint8_t>(ctx, R);
-        ent_run = alloc<uint32_t>(ctx, R);
-        HIPCHK(ctx, launch_entries_from_runs(lv, ent_a.p, ent_e.p, ent_f.p, ent_run.p, s));
-      } else {
-        ent_run = alloc<uint32_t>(ctx, E_ent);
-        HIPCHK(ctx, launch_entry_runs(ent_child.p, E_ent, run.p, ent_run.p, s));
-      }
-    }
-
     if (leaf_step) {
       if (!prune) {
-        store_leaf_level(step, b, c, st.p, text.p, h_tcount, h_tfirst, d_tfirst.p, d_tcount.p,
-                         roff.p + c, R);
+        store_leaf_level(step, b, c, st.p, text.p, h_tcount, h_tfirst, tfp, tcp);
       } else {
-        std::vector<uint64_t> rr;
-        read_words(ctx, {{roff.p + c, 1}}, rr);
-        check_runs(rr[0], R);
         PruneLevel& K = pl[step];
         K.b = b;
         K.c = c;
@@ -1046,11 +1052,24 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
         K.text = std::move(text);
         K.tfirst = std::move(d_tfirst);
         K.tcount = std::move(d_tcount);
+        K.tfp = tfp;
+        K.tcp = tcp;
         K.h_tcount = h_tcount;
         K.h_tfirst = h_tfirst;
       }
       break;
     }
+
+    // runs of this level (maximal sequences of consecutive blocks of one text).
+    // The run table is sized by c, which bounds any run count: it is indexed by
+    // the device's own count, which is checked against R only later
+    Buf<uint32_t> run = alloc<uint32_t>(ctx, c);
+    const uint64_t R = R_pred;
+    Buf<uint64_t> rs = alloc<uint64_t>(ctx, c), re = alloc<uint64_t>(ctx, c);
+    Buf<uint32_t> rtext = alloc<uint32_t>(ctx, c);
+    HIPCHK(ctx, launch_runs(st.p, text.p, c, b, tx, run.p, rs.p, re.p, rtext.p, lvl_totals.p + 2,
+                            next_scan(c), s));
+    LevelDev lv{c, b, st.p, text.p, run.p, R, rs.p, re.p, rtext.p};
 
     // a text whose final block is present and short has odd-length keys
     bool has_odd = false;
@@ -1063,10 +1082,13 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
                   klm = alloc<uint64_t>(ctx, c);
     Buf<uint32_t> kslot = alloc<uint32_t>(ctx, c);
     Buf<uint64_t> oddb = alloc<uint64_t>(ctx, 8 * (uint64_t)T);
-    Buf<uint64_t> woff = alloc<uint64_t>(ctx, E_ent + 1);
-    Buf<uint64_t> seg_ws = alloc<uint64_t>(ctx, E_ent), seg_re = alloc<uint64_t>(ctx, E_ent);
-    Buf<uint32_t> seg_text = alloc<uint32_t>(ctx, E_ent);
-    SegDev sg{E_ent, ent_a.p, ent_e.p, ent_f.p, ent_run.p, seg_ws.p, seg_re.p, seg_text.p};
+    // the phase's scan segments: at most one per entry (phase 1) or block (phase 2)
+    const uint64_t nseg = std::max(E_ent, c);
+    Buf<uint64_t> seg_ws = alloc<uint64_t>(ctx, nseg), seg_re = alloc<uint64_t>(ctx, nseg),
+                  seg_woff = alloc<uint64_t>(ctx, nseg + 1);
+    Buf<uint32_t> seg_text = alloc<uint32_t>(ctx, nseg);
+    const SegDev sg{E_ent, ent_a.p, ent_e.p, ent_f.p, ent_child.p};
+    const SegOut so{seg_ws.p, seg_re.p, seg_text.p, seg_woff.p, segn.p};
     Buf<uint8_t> facts = alloc<uint8_t>(ctx, c);
     Buf<uint32_t> vlist = alloc<uint32_t>(ctx, c), vmis = alloc<uint32_t>(ctx, c),
                   rlist = alloc<uint32_t>(ctx, c);
@@ -1083,6 +1105,7 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
 
     PhaseArgs a{};
     a.T = d_base;
+    a.segn = segn.p;
     a.P = P;
     a.Ps = (sample_p || quarter_p) ? d_P.p : nullptr;
     a.pshift = quarter_p ? 2 : 4;
@@ -1105,33 +1128,26 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
     a.filt2 = filt2.p;
     // parent facts per block: keys inside a parent region that occurs earlier
     // are known copies and stay out of the table
-    Buf<uint8_t> cflag;
-    if (have_entries && c) {
-      cflag = alloc<uint8_t>(ctx, c);
-      HIPCHK(ctx, launch_fill_u8(cflag.p, 0, c, s));
-      HIPCHK(ctx, launch_child_flags(sg, b, ent_child.p, cflag.p, s));
-      a.cflag = cflag.p;
-    }
+    a.cflag = cflag.p;
     a.exact_all = prune ? 1 : 0;
-
-    // Phase-2 segments come from this level's blocks and pair facts.
-    Buf<uint64_t> bwc = alloc<uint64_t>(ctx, c + 1), bhd = alloc<uint64_t>(ctx, c + 1);
-    Buf<uint64_t> bws = alloc<uint64_t>(ctx, c), bre = alloc<uint64_t>(ctx, c);
-    Buf<uint64_t> bwoff = alloc<uint64_t>(ctx, c + 1);
-    Buf<uint32_t> btext = alloc<uint32_t>(ctx, c);
 
     // Text-local filters (batches): per text, 2^wl 32-bit words with wl the
     // least >= 3 such that each of the text's blocks (a bound on its keys in
     // either phase) has a word.  One layout serves both phases.
     // A text whose filter is larger than LDS also gets a folded copy of LDS
     // size (tf_fold), built after the keys.
-    Buf<uint64_t> tf_off, tf_fold_off, span_ctr;
-    Buf<uint32_t> tf_words, tf_wl, tf_fold, tf_big;
+    Buf<uint64_t> tf_off, span_ctr;
+    Buf<uint32_t> tf_words, tf_fold;
+    const uint64_t* tf_fold_off = nullptr;
+    uint32_t *tf_wl = nullptr, *tf_big = nullptr;
     uint64_t tf_total = 0;
     uint32_t nbig = 0;
     if (has_salt && c && !(prm.debug_flags & (BT_DBG_SHARED_FILTERS | BT_DBG_SORT_PHASES))) {
-      std::vector<uint64_t> h_off(T), h_foff(T, 0);
-      std::vector<uint32_t> h_wl(T), h_big;
+      // one upload: filter offsets and folded ones (u64), log2 sizes (u32), the
+      // texts with a folded filter (u32)
+      std::vector<uint64_t> up(3 * (uint64_t)T + 1, 0);
+      uint64_t *h_off = up.data(), *h_foff = h_off + T;
+      uint32_t *h_wl = reinterpret_cast<uint32_t*>(h_foff + T), *h_big = h_wl + T;
       const uint32_t tf_lds = kTextFilterLdsLog2;
       for (uint32_t t = 0; t < T; ++t) {
         uint32_t wl = 3;
@@ -1143,24 +1159,18 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
         h_off[t] = tf_total;
         tf_total += 1ull << wl;
         if (wl > tf_lds) {
-          h_foff[t] = (uint64_t)h_big.size() << tf_lds;
-          h_big.push_back(t);
+          h_foff[t] = (uint64_t)nbig << tf_lds;
+          h_big[nbig++] = t;
         }
       }
-      nbig = (uint32_t)h_big.size();
       tf_words = alloc<uint32_t>(ctx, tf_total);
-      tf_off = alloc<uint64_t>(ctx, T);
-      tf_wl = alloc<uint32_t>(ctx, T);
+      tf_off = alloc<uint64_t>(ctx, up.size());
+      tf_fold_off = tf_off.p + T;
+      tf_wl = reinterpret_cast<uint32_t*>(tf_off.p + 2 * (uint64_t)T);
+      tf_big = tf_wl + T;
+      upload(ctx, tf_off.p, up.data(), up.size());
+      if (nbig) tf_fold = alloc<uint32_t>(ctx, (uint64_t)nbig << tf_lds);
       span_ctr = alloc<uint64_t>(ctx, 1);
-      upload(ctx, tf_off.p, h_off.data(), T);
-      upload(ctx, tf_wl.p, h_wl.data(), T);
-      if (nbig) {
-        tf_fold = alloc<uint32_t>(ctx, (uint64_t)nbig << tf_lds);
-        tf_fold_off = alloc<uint64_t>(ctx, T);
-        tf_big = alloc<uint32_t>(ctx, nbig);
-        upload(ctx, tf_fold_off.p, h_foff.data(), T);
-        upload(ctx, tf_big.p, h_big.data(), nbig);
-      }
     }
 
     // nkeys: keys of the phase (pairs of consecutive blocks, or unmarked blocks)
@@ -1168,6 +1178,7 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
       a.phase = phase;
       a.pc = ctx->profile ? pstats.p + (2 * (uint64_t)step + (phase - 1)) * kPcWords : nullptr;
       if (ctx->profile) phase_host.push_back({step, b, (uint64_t)phase, c});
+      if (phase == 2 && nkeys == 0) return;  // nothing of the phase is read
       a.Lmain = phase == 1 ? 2 * b : b;
       a.xLmain = host_pow61(x, a.Lmain);
       // LDS filter: 32 bits per key or more, at most 2^19 bits (64 KiB; 2^20 in
@@ -1225,9 +1236,9 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
       }
       a.tf_words = text_local ? tf_words.p : nullptr;
       a.tf_off = text_local ? tf_off.p : nullptr;
-      a.tf_wl = text_local ? tf_wl.p : nullptr;
+      a.tf_wl = text_local ? tf_wl : nullptr;
       a.tf_fold = text_local ? tf_fold.p : nullptr;
-      a.tf_fold_off = text_local ? tf_fold_off.p : nullptr;
+      a.tf_fold_off = text_local ? tf_fold_off : nullptr;
       a.filt_bits = fbits;
       a.filt_two = fbits && 8 * nkeys <= (1ull << fbits);
       a.pre32 = !byte_scan && scan_mode == 1;
@@ -1266,7 +1277,7 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
         }
         return hipSuccess;
       };
-      {
+      if (nkeys) {
         FillList f;
         f.add(tab.p, 4 * cap, ~0u);  // empty slots: fp = best = ~0
         f.add(oddb.p, 16 * (uint64_t)T, 0);
@@ -1282,47 +1293,22 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
       HIPCHK(ctx, launch_keys(a, s));
       // no keys: the slots say so (kNoKey), and there is nothing to scan for
       if (nkeys == 0) return;
-      if (text_local) HIPCHK(ctx, launch_fold_filters(a, tf_big.p, nbig, s));
+      if (text_local) HIPCHK(ctx, launch_fold_filters(a, tf_big, nbig, s));
       PhaseArgs as = a;  // the scan walks segments in place of runs
-      uint64_t* swoff = woff.p;
+      as.lv.rs = seg_ws.p;
+      as.lv.re = seg_re.p;
+      as.lv.rtext = seg_text.p;
+      uint64_t* swoff = seg_woff.p;
       uint64_t* wst = wstats.p + 2 * step + (phase - 1);
-      if (phase == 1) {
-        HIPCHK(ctx, launch_segments(a, sg, woff.p, s));
-        scan(woff.p, E_ent);
-        as.lv.R = E_ent;
-        as.lv.rs = seg_ws.p;
-        as.lv.re = seg_re.p;
-        as.lv.rtext = seg_text.p;
-        if (E_ent && E_ent <= c) {
-          // entries whose starts continue the previous entry's join its
-          // segment (phase 2's segment arrays are free until then)
-          HIPCHK(ctx, launch_seg_heads(sg, woff.p, bhd.p, s));
-          scan(bhd.p, E_ent);
-          HIPCHK(ctx, launch_seg_merge(sg, woff.p, bhd.p, bws.p, bre.p, btext.p, bwoff.p, s));
-          swoff = bwoff.p;
-          as.lv.rs = bws.p;
-          as.lv.re = bre.p;
-          as.lv.rtext = btext.p;
-        }
-      } else {
-        HIPCHK(ctx, launch_block_seg_counts(a, facts.p, bwc.p, bhd.p, s));
-        scan(bwc.p, c);
-        scan(bhd.p, c);
-        HIPCHK(ctx, launch_block_segments(a, bwc.p, bhd.p, bws.p, bre.p, btext.p, bwoff.p, s));
-        swoff = bwoff.p;
-        as.lv.R = c;
-        as.lv.rs = bws.p;
-        as.lv.re = bre.p;
-        as.lv.rtext = btext.p;
-      }
-      if (ctx->profile)  // window count of the launch, for the kernel statistics
-        HIPCHK(ctx, hipMemcpyAsync(wst, swoff + as.lv.R, 8, hipMemcpyDeviceToDevice, s));
+      uint64_t* wcount = ctx->profile ? wst : nullptr;  // windows, for the kernel statistics
+      if (phase == 1) HIPCHK(ctx, launch_entry_segs(a, sg, so, wcount, next_scan(E_ent), s));
+      else HIPCHK(ctx, launch_block_segs(a, facts.p, so, wcount, next_scan(c), s));
       // algorithmic bytes per window: the two prefix values it reads (8-byte
       // 61-bit prefixes, or 4-byte 32-bit hashes when pre-filtering)
       if (prm.debug_flags & BT_DBG_SORT_PHASES) {
         // Section 5.1: sort (fingerprint, position) of every window and key
         std::vector<uint64_t> wv;
-        read_words(ctx, {{swoff + as.lv.R, 1}}, wv);
+        read_words(ctx, {{segn.p + 1, 1}}, wv);
         const uint64_t W = wv[0], n2 = W + c;
         if (n2 >= (1ull << 31)) {
           ctx->err = "sort-based phase: 2^31 windows or more";
@@ -1365,7 +1351,7 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
         Buf<uint64_t> span_info;
         // with many segments, the tiles' segments from a pass of their own
         Buf<uint32_t> tseg;
-        if (!text_local && scan_mode == 1 && !lean && as.lv.R >= kTileSegsMin)
+        if (!text_local && scan_mode == 1 && !lean && (phase == 1 ? E_ent : c) >= kTileSegsMin)
           tseg = alloc<uint32_t>(ctx, c * b / kProbeTile + 2);
         if (text_local) {
           span_info = alloc<uint64_t>(ctx, 3 * probe_text_spans(c * b, span_chunks));
@@ -1389,94 +1375,58 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
     // ---- phase 1: pairs (a3, a4) and marks (a5)
     a.all_blocks = 0;
     run_phase(1, c - R);
-    Buf<uint64_t> uoff = alloc<uint64_t>(ctx, c + 1), nrun = alloc<uint64_t>(ctx, c + 1);
-    HIPCHK(ctx, launch_mark_facts(a, marked.p, facts.p, uoff.p, nrun.p, s));
+    // marks and, from them, the shape of the next level: one read-back
+    const uint64_t bn = b / prm.tau;
+    Buf<uint64_t> uoff = alloc<uint64_t>(ctx, c + 1), cs = alloc<uint64_t>(ctx, c + 1);
+    HIPCHK(ctx, launch_marks(a, bn, marked.p, facts.p, uoff.p, cs.p, lvl_totals.p, next_scan(c), s));
+    Buf<uint64_t> ntcount = alloc<uint64_t>(ctx, T), ntfirst = alloc<uint64_t>(ctx, T + 1),
+                  d_woff = alloc<uint64_t>(ctx, T + 1);
+    const TextStep ts{cs.p,      tfp,          tcp,       uoff.p,
+                      d_estep,   step + 1,     bn,        ntcount.p,
+                      ntfirst.p, d_woff.p,     lvl_totals.p, seen_read ? nullptr : d_seen.p,
+                      d_lvl + kHostTotals, d_lvl + kHostTotals + T, d_lvl};
+    HIPCHK(ctx, launch_texts(tx, ts, next_scan(T), s));
+    HIPCHK(ctx, hipStreamSynchronize(s));
+    ctx->h_stage_used = 0;  // every queued upload has completed
+    collect_events(ctx);
+    const uint64_t u = h_lvl[0];
+    const uint32_t n_enter = id_first[step + 2] - id_first[step + 1];
+    R_pred = h_lvl[1] + n_enter;  // runs of the next level: marked groups, entering texts
+    check_runs(h_lvl[2], R);
+    if (!seen_read) check_seen(h_lvl + 3);
+    const std::vector<uint64_t> h_ntcount(h_lvl + kHostTotals, h_lvl + kHostTotals + T),
+        h_tu(h_lvl + kHostTotals + T, h_lvl + kHostTotals + 2 * (uint64_t)T);
 
     // ---- phase 2: unmarked blocks (a6) and pointers (a7)
-    scan(uoff.p, c);
-    std::vector<uint64_t> uu;
-    read_words(ctx, {{uoff.p + c, 1}, {roff.p + c, 1}}, uu);
-    check_runs(uu[1], R);
     // When most blocks are unmarked the phase-2 scan costs the same with a key
     // for every block; the leftmost occurrences of the marked blocks then tell
     // the next level which windows are copies.  Not worth it before the last
     // scanned level.
     // Pruning needs every block's leftmost occurrence, so it asks for all.
-    a.all_blocks = (prune || (4 * uu[0] >= c && step + 2 < H)) ? 1 : 0;
-    run_phase(2, a.all_blocks ? c : uu[0]);
-    if (a.all_blocks) HIPCHK(ctx, launch_block_facts(a, facts.p, s));
+    a.all_blocks = (prune || (4 * u >= c && step + 2 < H)) ? 1 : 0;
+    run_phase(2, a.all_blocks ? c : u);
     // pointers of the unmarked blocks, compacted by unmarked rank: tree storage
-    // (with pruning, written once the marks are final)
+    // (with pruning, written once the marks are final), and the next level (a8)
     Buf<uint64_t> spb, spo;
     if (!prune) {
-      spb = alloc<uint64_t>(ctx, uu[0]);
-      spo = alloc<uint64_t>(ctx, uu[0]);
-      HIPCHK(ctx, launch_pointers(a, marked.p, uoff.p, d_tfirst.p, spb.p, spo.p,
-                                  reinterpret_cast<uint32_t*>(d_err.p), s));
+      spb = alloc<uint64_t>(ctx, u);
+      spo = alloc<uint64_t>(ctx, u);
     }
-
-    // ---- split (a8): per-text counts of the next level
-    const uint64_t bn = b / prm.tau;
-    Buf<uint64_t> cs = alloc<uint64_t>(ctx, c + 1);
-    HIPCHK(ctx, launch_child_counts(lv, tx, marked.p, bn, cs.p, s));
-    scan(cs.p, c);
-    std::vector<uint32_t> ids;
-    std::vector<uint64_t> ent;
-    entering(step + 1, ids, ent, bn);
-    Buf<uint64_t> d_ent = alloc<uint64_t>(ctx, T);
-    upload(ctx, d_ent.p, ent.data(), T);
-    Buf<uint64_t> ntcount = alloc<uint64_t>(ctx, T + 1), ntfirst = alloc<uint64_t>(ctx, T + 1);
-    Buf<uint64_t> tu = alloc<uint64_t>(ctx, T);
-    if (T <= kTextStepMax) {  // counts, their prefix and the unmarked deltas in one launch
-      HIPCHK(ctx, launch_text_step(T, cs.p, d_tfirst.p, d_tcount.p, d_ent.p, uoff.p, ntcount.p,
-                                   ntfirst.p, tu.p, s));
-    } else {
-      HIPCHK(ctx, launch_text_counts(T, cs.p, d_tfirst.p, d_tcount.p, d_ent.p, ntcount.p, s));
-      HIPCHK(ctx, hipMemcpyAsync(ntfirst.p, ntcount.p, T * 8, hipMemcpyDeviceToDevice, s));
-      scan(ntfirst.p, T);
-      HIPCHK(ctx, launch_text_deltas(uoff.p, d_tfirst.p, d_tcount.p, T, tu.p, s));
-    }
-    scan(nrun.p, c);
-    std::vector<uint64_t> got;
-    read_words(ctx, {{ntcount.p, T}, {tu.p, T}, {uoff.p + c, 1}, {nrun.p + c, 1}}, got);
-    std::vector<uint64_t> h_ntcount(got.begin(), got.begin() + T);
-    std::vector<uint64_t> h_tu(got.begin() + T, got.begin() + 2 * T);
-    const uint64_t u = got[2 * T];
-    R_pred = got[2 * T + 1];  // runs of the next level: groups of marked blocks ...
-    for (uint32_t t : ids) R_pred += ent[t] ? 1 : 0;  // ... and non-empty entering texts
+    uint64_t cn = 0;
+    for (uint32_t t = 0; t < T; ++t) cn += h_ntcount[t];
+    Buf<uint64_t> nst;
+    Buf<uint32_t> ntext;
+    const NextLevel nl = alloc_next(cn, (c - u) + n_enter, nst, ntext);
+    E_ent = (c - u) + n_enter;
+    HIPCHK(ctx, launch_split(a, facts.p, uoff.p, cs.p, tfp, ntfirst.p, bn, a.all_blocks, nl,
+                             prune ? nullptr : spb.p, spo.p, reinterpret_cast<uint32_t*>(d_err.p), s));
+    HIPCHK(ctx, launch_enter(d_ids + id_first[step + 1], n_enter, tx, bn, ntfirst.p, c - u, nl, s));
 
     // ---- outputs of this level: marks (word range per text) and pointers
     if (!prune)
       store_level(step, b, c, st.p, text.p, marked.p, uoff.p, spb, spo, u, h_tcount, h_tfirst,
-                  h_tu, d_tfirst.p, d_tcount.p);
+                  h_tu, tfp, tcp, d_woff.p);
 
-    // ---- next level's blocks
-    uint64_t cn = 0;
-    for (uint32_t t = 0; t < T; ++t) cn += h_ntcount[t];
-    Buf<uint64_t> nst = alloc<uint64_t>(ctx, cn);
-    Buf<uint32_t> ntext = alloc<uint32_t>(ctx, cn);
-    HIPCHK(ctx, launch_write_children(lv, tx, marked.p, bn, prm.tau, cs.p, d_tfirst.p, ntfirst.p,
-                                      nst.p, ntext.p, s));
-    Buf<uint32_t> d_ids = alloc<uint32_t>(ctx, ids.size());
-    upload(ctx, d_ids.p, ids.data(), ids.size());
-    HIPCHK(ctx, launch_write_entering(d_ids.p, (uint32_t)ids.size(), tx, bn, ntfirst.p, nst.p,
-                                      ntext.p, s));
-    {
-      const uint64_t nmarked = c - u;
-      const uint64_t En = nmarked + ids.size();
-      Buf<uint64_t> na = alloc<uint64_t>(ctx, En), ne = alloc<uint64_t>(ctx, En),
-                    nchild = alloc<uint64_t>(ctx, En);
-      Buf<uint8_t> nf = alloc<uint8_t>(ctx, En);
-      HIPCHK(ctx, launch_entries_next(lv, tx, marked.p, facts.p, uoff.p, cs.p, d_tfirst.p,
-                                      ntfirst.p, nmarked, d_ids.p, (uint32_t)ids.size(), na.p,
-                                      ne.p, nf.p, nchild.p, s));
-      E_ent = En;
-      ent_a = std::move(na);
-      ent_e = std::move(ne);
-      ent_f = std::move(nf);
-      ent_child = std::move(nchild);
-      have_entries = true;
-    }
     if (prune) {
       PruneLevel& K = pl[step];
       K.b = b;
@@ -1489,11 +1439,15 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
       K.cs = std::move(cs);
       K.tfirst = std::move(d_tfirst);
       K.tcount = std::move(d_tcount);
+      K.tfp = tfp;
+      K.tcp = tcp;
       K.h_tcount = h_tcount;
       K.h_tfirst = h_tfirst;
     }
-    std::swap(d_tcount, ntcount);
-    std::swap(d_tfirst, ntfirst);
+    d_tcount = std::move(ntcount);
+    d_tfirst = std::move(ntfirst);
+    tcp = d_tcount.p;
+    tfp = d_tfirst.p;
     h_tcount = h_ntcount;
     for (uint32_t t = 0; t < T; ++t) h_tfirst[t + 1] = h_tfirst[t] + h_tcount[t];
     st = std::move(nst);
@@ -1524,9 +1478,9 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
       scan(unmk.p, c0);
       Buf<uint64_t> ntf = alloc<uint64_t>(ctx, T + 1), ntc = alloc<uint64_t>(ctx, T + 1),
                     ntu = alloc<uint64_t>(ctx, T + 1);
-      HIPCHK(ctx, launch_gather_firsts(keep.p, K.tfirst.p, T, ntf.p, s));
-      HIPCHK(ctx, launch_text_deltas(keep.p, K.tfirst.p, K.tcount.p, T, ntc.p, s));
-      HIPCHK(ctx, launch_text_deltas(unmk.p, K.tfirst.p, K.tcount.p, T, ntu.p, s));
+      HIPCHK(ctx, launch_gather_firsts(keep.p, K.tfp, T, ntf.p, s));
+      HIPCHK(ctx, launch_text_deltas(keep.p, K.tfp, K.tcp, T, ntc.p, s));
+      HIPCHK(ctx, launch_text_deltas(unmk.p, K.tfp, K.tcp, T, ntu.p, s));
       Buf<uint64_t> nst = alloc<uint64_t>(ctx, c0), nlm = alloc<uint64_t>(ctx, c0),
                     nuoff = alloc<uint64_t>(ctx, c0 + 1);
       Buf<uint32_t> ntext = alloc<uint32_t>(ctx, c0);
@@ -1542,16 +1496,13 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
       for (uint32_t t = 0; t < T; ++t) tf[t + 1] = tf[t] + tc[t];
       const uint64_t c = got[2 * T], u = got[2 * T + 1];
       if (leaf) {
-        store_leaf_level(step, K.b, c, nst.p, ntext.p, tc, tf, ntf.p, ntc.p, nullptr, 0);
+        store_leaf_level(step, K.b, c, nst.p, ntext.p, tc, tf, ntf.p, ntc.p);
       } else {
         // runs of the stored level: a pointer that spills names two consecutive blocks
-        Buf<uint64_t> roff = alloc<uint64_t>(ctx, c + 1), rs = alloc<uint64_t>(ctx, c),
-                      re = alloc<uint64_t>(ctx, c);
+        Buf<uint64_t> rs = alloc<uint64_t>(ctx, c), re = alloc<uint64_t>(ctx, c);
         Buf<uint32_t> run = alloc<uint32_t>(ctx, c), rtext = alloc<uint32_t>(ctx, c);
-        HIPCHK(ctx, launch_run_flags(nst.p, ntext.p, c, K.b, roff.p, s));
-        scan(roff.p, c);
-        HIPCHK(ctx, launch_run_table(nst.p, ntext.p, c, K.b, tx, roff.p, run.p, rs.p, re.p,
-                                     rtext.p, s));
+        HIPCHK(ctx, launch_runs(nst.p, ntext.p, c, K.b, tx, run.p, rs.p, re.p, rtext.p, nullptr,
+                                next_scan(c), s));
         PhaseArgs pa{};
         pa.tx = tx;
         pa.lv = LevelDev{c, K.b, nst.p, ntext.p, run.p, 0, rs.p, re.p, rtext.p};
@@ -1559,7 +1510,7 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
         Buf<uint64_t> spb = alloc<uint64_t>(ctx, u), spo = alloc<uint64_t>(ctx, u);
         if (c) HIPCHK(ctx, launch_pointers(pa, nmarked.p, nuoff.p, ntf.p, spb.p, spo.p, err, s));
         store_level(step, K.b, c, nst.p, ntext.p, nmarked.p, nuoff.p, spb, spo, u, tc, tf, tu,
-                    ntf.p, ntc.p);
+                    ntf.p, ntc.p, nullptr);
       }
       K = PruneLevel{};
     };
@@ -1587,8 +1538,8 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
       d.cmarked = child_leaf ? nullptr : C.marked.p;
       d.cgone = cgone.p;
       d.cs = L.cs.p;
-      d.tfirst = L.tfirst.p;
-      d.ctfirst = C.tfirst.p;
+      d.tfirst = L.tfp;
+      d.ctfirst = C.tfp;
       d.err = err;
       HIPCHK(ctx, launch_prune_decide_begin(d, s));
       // every round settles at least one candidate
@@ -1608,26 +1559,7 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
     compact_store(0, nullptr);
   }
 
-  std::vector<uint64_t> fin;
-  const uint64_t npw = ctx->profile ? 2 * (uint64_t)H * kPcWords : 0;
-  read_words(ctx, {{d_err.p, 1}, {wstats.p, ctx->profile ? 2 * (uint64_t)H + 2 : 0},
-                   {pstats.p, npw}}, fin);
-  if (ctx->profile) {
-    collect_events(ctx, wstats.p, fin.data() + 1, 2 * (uint64_t)H + 2);
-    const uint64_t* pw = fin.data() + 1 + 2 * (uint64_t)H + 2;
-    for (const auto& ph : phase_host) {
-      if (ctx->phases.size() >= kLaunchLogMax) break;
-      const uint64_t* r = pw + (2 * ph[0] + (ph[2] - 1)) * kPcWords;
-      ctx->phases.push_back({{ph[0], ph[1], ph[2], ph[3], r[kPcKeys], r[kPcWindows], r[kPcCand],
-                              r[kPcVerified], r[kPcCollisions]}});
-    }
-  }
-  if (fin[0]) {
-    ctx->err = "device check failed: a pointer does not target a marked block or pair";
-    return BT_E_INTERNAL;
-  }
-
-  // ---- trees
+  // ---- trees (their query level tables in one upload), then the last read-back
   // a tree's counts on one level: absolute for the whole step, absolute rows of
   // its first level, or relative
   auto rank_level = [&](TreeLevel& tl, const LevelBufs& L, uint32_t t, uint32_t l, uint64_t first) {
@@ -1637,8 +1569,10 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
     tl.qw = L.qw;
     tl.st = L.st + first;
   };
+  std::vector<std::unique_ptr<bt_tree>> trees(T);
   for (uint32_t t = 0; t < T; ++t) {
-    bt_tree* tr = new bt_tree;
+    trees[t].reset(new bt_tree);
+    bt_tree* tr = trees[t].get();
     tr->store = store;
     tr->dev = ctx->dev;
     tr->n = h_n[t];
@@ -1678,32 +1612,48 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
     tr->total = d_Rtot ? d_Rtot + (uint64_t)t * S : nullptr;
     tr->tstart = h_n[t] ? offs[t] : offs[t];
     tr->leaves = leaves + leaf_off[t];
-    tr->leaf_bytes = leaf_bytes[t];
-    outs[t] = tr;
   }
-  // query level tables of every tree, in one upload
   {
     std::vector<QLevel> ql;
     std::vector<uint64_t> at(T);
     for (uint32_t t = 0; t < T; ++t) {
       at[t] = ql.size();
-      for (const TreeLevel& L : outs[t]->lv)
+      for (const TreeLevel& L : trees[t]->lv)
         ql.push_back(QLevel{L.b, L.c, L.words, L.wrank, L.pb, L.po, L.acnt, L.qc, L.pc, L.msel,
                             L.st, L.qw, L.pw});
     }
     Buf<QLevel> d = alloc<QLevel>(ctx, ql.size());
-    const uint64_t words = (ql.size() * sizeof(QLevel) + 7) / 8;
-    uint64_t* stg = small_host(ctx, words);
-    std::memcpy(stg, ql.data(), ql.size() * sizeof(QLevel));
-    HIPCHK(ctx, hipMemcpyAsync(d.p, stg, ql.size() * sizeof(QLevel), hipMemcpyHostToDevice, s));
-    HIPCHK(ctx, hipStreamSynchronize(s));
+    upload(ctx, d.p, ql.data(), ql.size());
     QLevel* base = store->add(std::move(d), ql.size());
     for (uint32_t t = 0; t < T; ++t) {
-      outs[t]->d_levels = base + at[t];
-      outs[t]->dev_bytes = store->bytes / T;
-      outs[t]->rank_bytes = rank_bytes / T;
+      trees[t]->d_levels = base + at[t];
+      trees[t]->dev_bytes = store->bytes / T;
+      trees[t]->rank_bytes = rank_bytes / T;
     }
   }
+  // the pointer check's word, the texts' last leaf lengths, what is still unread
+  std::vector<uint64_t> fin;
+  const uint64_t nws = ctx->profile ? 2 * (uint64_t)H + 2 : 0;
+  const uint64_t npw = ctx->profile ? 2 * (uint64_t)H * kPcWords : 0;
+  read_words(ctx, {{d_small.p, 5}, {d_last.p, T}, {wstats.p, nws}, {pstats.p, npw}}, fin);
+  if (!seen_read) check_seen(fin.data());
+  for (uint32_t t = 0; t < T; ++t)
+    trees[t]->leaf_bytes = leaf_count[t] ? (leaf_count[t] - 1) * prm.leaf_len + fin[5 + t] : 0;
+  if (ctx->profile) {
+    collect_events(ctx, wstats.p, fin.data() + 5 + T, nws);
+    const uint64_t* pw = fin.data() + 5 + T + nws;
+    for (const auto& ph : phase_host) {
+      if (ctx->phases.size() >= kLaunchLogMax) break;
+      const uint64_t* r = pw + (2 * ph[0] + (ph[2] - 1)) * kPcWords;
+      ctx->phases.push_back({{ph[0], ph[1], ph[2], ph[3], r[kPcKeys], r[kPcWindows], r[kPcCand],
+                              r[kPcVerified], r[kPcCollisions]}});
+    }
+  }
+  if (fin[4]) {
+    ctx->err = "device check failed: a pointer does not target a marked block or pair";
+    return BT_E_INTERNAL;
+  }
+  for (uint32_t t = 0; t < T; ++t) outs[t] = trees[t].release();
   return BT_OK;
 }
 

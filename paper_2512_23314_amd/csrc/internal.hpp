@@ -105,6 +105,7 @@ struct TableDev {
 
 struct PhaseArgs {
   const uint8_t* T;
+  const uint64_t* segn;   // the phase's scan segments and their windows (two words)
   const uint64_t* P;      // prefix fingerprints by text position, or null when sampled:
   const uint64_t* Ps;     // Ps[q] = P[pbase + 2^pshift q]
   uint32_t pshift;        // 4 (memory-lean builds), or 2 (dense 32-bit hashes beside them)
@@ -177,18 +178,21 @@ constexpr uint8_t kSkipInterior = 1;  // windows ending inside the entry are cop
 constexpr uint8_t kSkipCross = 2;     // every window starting in the entry is a copy
 constexpr uint8_t kLastChild = 4;     // (per block) the last child of its parent
 struct SegDev {
-  uint64_t E;             // entries
-  const uint64_t* ea;     // [E] entry start
-  const uint64_t* ee;     // [E] entry end
-  const uint8_t* ef;      // [E] kSkip* flags
-  const uint32_t* erun;   // [E] run of the entry
-  uint64_t* ws;           // [E] first window start of the segment
-  uint64_t* sre;          // [E] run end
-  uint32_t* stext;        // [E] text
+  uint64_t E;               // entries
+  const uint64_t* ea;       // [E] entry start
+  const uint64_t* ee;       // [E] entry end
+  const uint8_t* ef;        // [E] kSkip* flags
+  const uint64_t* echild;   // [E] first block of the entry on this level
+};
+struct SegOut {
+  uint64_t* ws;     // first window start of each segment
+  uint64_t* sre;    // run end
+  uint32_t* stext;  // text
+  uint64_t* woff;   // windows before each segment, the total after the last
+  uint64_t* segn;   // {segments, windows}
 };
 
 hipError_t launch_fill_u64(uint64_t* p, uint64_t v, uint64_t n, hipStream_t s);
-hipError_t launch_fill_u32(uint32_t* p, uint32_t v, uint64_t n, hipStream_t s);
 hipError_t launch_fill_u8(uint8_t* p, uint8_t v, uint64_t n, hipStream_t s);
 // Up to kFillJobs fills of 32-bit words in one launch (jobs with no words are
 // skipped by their blocks).
@@ -211,14 +215,17 @@ hipError_t launch_fill_many(const FillList& f, hipStream_t s);
 // scan_tmp_words(n) words.
 uint64_t scan_tmp_words(uint64_t n);
 hipError_t scan_excl_u64(uint64_t* a, uint64_t n, uint64_t* tmp, hipStream_t s);
-// Per-text counts of the next level in one launch, for T <= kTextStepMax texts:
-// ncount[t] = cs[tfirst[t] + tcount[t]] - cs[tfirst[t]] + enter[t];
-// nfirst = exclusive prefix of ncount (T + 1 words);
-// tu[t] = uoff[tfirst[t] + tcount[t]] - uoff[tfirst[t]].
-constexpr uint32_t kTextStepMax = 2048;
-hipError_t launch_text_step(uint32_t T, const uint64_t* cs, const uint64_t* tfirst,
-                            const uint64_t* tcount, const uint64_t* enter, const uint64_t* uoff,
-                            uint64_t* ncount, uint64_t* nfirst, uint64_t* tu, hipStream_t s);
+// One-pass prefix sums of a level (scan_pass.hpp): the status words, the ticket
+// counter and its value before this scan, and the scan's number in its build.
+struct ScanDev {
+  uint64_t* status;  // three arrays of `stride` words (one per value and tile)
+  uint64_t stride;
+  uint64_t* ticket;
+  uint64_t base;
+  uint64_t epoch;    // 1 .. 2^22 - 1
+};
+constexpr uint64_t kPassTile = 2048;
+inline uint64_t scan_pass_tiles(uint64_t n) { return n ? (n + kPassTile - 1) / kPassTile : 1; }
 
 // The probe scan's tile: a wave takes this many consecutive window numbers at
 // a time (lanes step through them 64 apart).
@@ -226,36 +233,6 @@ constexpr uint64_t kProbeTile = 1024;
 
 // Phase kernels (steps a3-a7).
 hipError_t launch_keys(const PhaseArgs& a, hipStream_t s);
-hipError_t launch_entries_from_runs(const LevelDev& lv, uint64_t* ea, uint64_t* ee, uint8_t* ef,
-                                    uint32_t* erun, hipStream_t s);
-hipError_t launch_pair_facts(const PhaseArgs& a, uint8_t* pf, hipStream_t s);
-hipError_t launch_block_facts(const PhaseArgs& a, uint8_t* pf, hipStream_t s);
-hipError_t launch_entries_next(const LevelDev& lv, const TextsDev& tx, const uint8_t* marked,
-                               const uint8_t* pf, const uint64_t* uoff, const uint64_t* cs,
-                               const uint64_t* tfirst, const uint64_t* ntfirst, uint64_t nmarked,
-                               const uint32_t* ids, uint32_t E, uint64_t* ea, uint64_t* ee,
-                               uint8_t* ef, uint64_t* echild, hipStream_t s);
-hipError_t launch_entry_runs(const uint64_t* echild, uint64_t E, const uint32_t* run,
-                             uint32_t* erun, hipStream_t s);
-// Per-block parent facts from the level's entries: cflag (c bytes, zeroed by
-// the caller) gets the entry's kSkip* flags on each child of a flagged entry,
-// plus kLastChild on its last child.  b: this level's block length.
-hipError_t launch_child_flags(const SegDev& sg, uint64_t b, const uint64_t* echild, uint8_t* cflag,
-                              hipStream_t s);
-// Per-segment window counts into woff[0..E) (then scanned by the caller).
-hipError_t launch_segments(const PhaseArgs& a, const SegDev& sg, uint64_t* woff, hipStream_t s);
-// Phase-1 segments merged where one entry's window starts continue the previous
-// entry's (see level.hip): head[0..E) then scanned by the caller (total at E),
-// then the merged arrays, E of them (E + 1 offsets), padded past the last.
-hipError_t launch_seg_heads(const SegDev& sg, const uint64_t* woff, uint64_t* head, hipStream_t s);
-hipError_t launch_seg_merge(const SegDev& sg, const uint64_t* woff, const uint64_t* hs, uint64_t* ws,
-                            uint64_t* sre, uint32_t* stext, uint64_t* woff2, hipStream_t s);
-// Phase-2 segments from this level's pair facts (bit 0 of pf); see level.hip.
-hipError_t launch_block_seg_counts(const PhaseArgs& a, const uint8_t* pf, uint64_t* wc,
-                                   uint64_t* head, hipStream_t s);
-hipError_t launch_block_segments(const PhaseArgs& a, const uint64_t* wcs, const uint64_t* hs,
-                                 uint64_t* ws, uint64_t* sre, uint32_t* stext, uint64_t* woff,
-                                 hipStream_t s);
 // Sort-based phases (sort_phase.hip): windows and keys as (fingerprint,
 // position or key block), sorted by fingerprint; none marks entries that match
 // nothing (above every fingerprint).
@@ -331,50 +308,67 @@ hipError_t launch_verify(const PhaseArgs& a, const VerifyBufs& v, uint64_t max_l
 hipError_t launch_finish(const PhaseArgs& a, const VerifyBufs& v, hipStream_t s);
 hipError_t launch_retry(const PhaseArgs& a, const VerifyBufs& v, hipStream_t s);
 
-// Step a5: marks from the phase-1 results (plus the isolated-block rule).
-hipError_t launch_mark(const PhaseArgs& a, uint8_t* marked, hipStream_t s);
-// marks, pair facts (bit 0), the unmarked indicator and the next level's run
-// starts in one pass
-hipError_t launch_mark_facts(const PhaseArgs& a, uint8_t* marked, uint8_t* pf, uint64_t* ucnt,
-                             uint64_t* nrun, hipStream_t s);
-// Unmarked-prefix counts: cnt[j] = !marked[j].
-hipError_t launch_unmarked_counts(const uint8_t* marked, uint64_t c, uint64_t* cnt,
-                                  hipStream_t s);
-// Step a7: pointers.  uoff = exclusive scan of unmarked counts; tfirst = first
-// block of each text on this level.  err receives 1 on a broken invariant.
+// The passes over a level's blocks (level_pass.hip).
+// Runs of a level: run ids, the run table, and the number of runs (or null).
+hipError_t launch_runs(const uint64_t* st, const uint32_t* text, uint64_t c, uint64_t b,
+                       const TextsDev& tx, uint32_t* run, uint64_t* rs, uint64_t* re,
+                       uint32_t* rtext, uint64_t* total, const ScanDev& sd, hipStream_t s);
+// Scan segments: phase 1 from the level's entries, phase 2 from its blocks and
+// pair facts (bit 0 of pf).  wst (or null) receives the window count too.
+hipError_t launch_entry_segs(const PhaseArgs& a, const SegDev& sg, const SegOut& o, uint64_t* wst,
+                             const ScanDev& sd, hipStream_t s);
+hipError_t launch_block_segs(const PhaseArgs& a, const uint8_t* pf, const SegOut& o, uint64_t* wst,
+                             const ScanDev& sd, hipStream_t s);
+// Step a5 from the phase-1 results: marks, pair facts, unmarked ranks and
+// children's ranks (exclusive, c + 1 words), totals = {unmarked, runs of the next
+// level among the children}.  bn: the next level's block length.
+hipError_t launch_marks(const PhaseArgs& a, uint64_t bn, uint8_t* marked, uint8_t* pf, uint64_t* uoff,
+                        uint64_t* cs, uint64_t* totals, const ScanDev& sd, hipStream_t s);
+// Per text, for the next level (h_*: pinned host memory).
+struct TextStep {
+  const uint64_t *cs, *tfirst, *tcount, *uoff;  // this level
+  const uint32_t* estep;   // [T] step at which a text enters
+  uint32_t enter;          // the next step
+  uint64_t bn;             // its block length
+  uint64_t *ncount, *nfirst;  // [T], [T + 1] blocks of the next level
+  uint64_t* woff;          // [T + 1] words of this level's marks
+  const uint64_t* totals;  // as launch_marks left them, then this level's runs
+  const uint64_t* seen;    // the four words of launch_byte_presence, or null
+  uint64_t *h_ncount, *h_tu;  // [T] next level's blocks, this level's unmarked ones
+  uint64_t* h_totals;      // the three totals, then seen
+};
+hipError_t launch_texts(const TextsDev& tx, const TextStep& ts, const ScanDev& sd, hipStream_t s);
+
+// Step a7: pointers.  uoff = unmarked ranks; tfirst = first block of each text on
+// this level.  err receives 1 on a broken invariant.
 hipError_t launch_pointers(const PhaseArgs& a, const uint8_t* marked, const uint64_t* uoff,
                            const uint64_t* tfirst, uint64_t* ptr_block, uint64_t* ptr_off,
                            uint32_t* err, hipStream_t s);
 
-// Step a8: split.
-hipError_t launch_child_counts(const LevelDev& lv, const TextsDev& tx, const uint8_t* marked,
-                               uint64_t bn, uint64_t* cnt, hipStream_t s);
-// Per-text next-level counts: children (from the scanned child counts) plus
-// entering blocks.  tcount/tfirst describe the current level.
-hipError_t launch_text_counts(uint32_t T, const uint64_t* cs, const uint64_t* tfirst,
-                              const uint64_t* tcount, const uint64_t* enter,
-                              uint64_t* ncount, hipStream_t s);
-hipError_t launch_write_children(const LevelDev& lv, const TextsDev& tx, const uint8_t* marked,
-                                 uint64_t bn, uint32_t tau, const uint64_t* cs,
-                                 const uint64_t* tfirst, const uint64_t* ntfirst,
-                                 uint64_t* nst, uint32_t* ntext, hipStream_t s);
-hipError_t launch_write_entering(const uint32_t* ids, uint32_t E, const TextsDev& tx,
-                                 uint64_t bn, const uint64_t* ntfirst, uint64_t* nst,
-                                 uint32_t* ntext, hipStream_t s);
-// Runs of a level: flags into rflag (c entries, then scanned by the caller).
-hipError_t launch_run_flags(const uint64_t* st, const uint32_t* text, uint64_t c, uint64_t b,
-                            uint64_t* rflag, hipStream_t s);
-// From the scanned flags (exclusive; roff[c] = R): run ids and the run table.
-hipError_t launch_run_table(const uint64_t* st, const uint32_t* text, uint64_t c, uint64_t b,
-                            const TextsDev& tx, const uint64_t* roff, uint32_t* run,
-                            uint64_t* rs, uint64_t* re, uint32_t* rtext, hipStream_t s);
+// Step a8: the next level's blocks, their parents' facts (PhaseArgs.cflag) and
+// its scan entries; and, with pb, this level's pointers as launch_pointers.
+struct NextLevel {
+  uint64_t* st;
+  uint32_t* text;
+  uint8_t* cflag;
+  uint64_t *ea, *ee;
+  uint8_t* ef;
+  uint64_t* echild;
+};
+hipError_t launch_split(const PhaseArgs& a, const uint8_t* pf, const uint64_t* uoff,
+                        const uint64_t* cs, const uint64_t* tfirst, const uint64_t* ntfirst,
+                        uint64_t bn, uint32_t blocks, const NextLevel& o, uint64_t* pb, uint64_t* po,
+                        uint32_t* err, hipStream_t s);
+// E texts that enter there (none empty), their entries from `base` on.
+hipError_t launch_enter(const uint32_t* ids, uint32_t E, const TextsDev& tx, uint64_t bn,
+                        const uint64_t* ntfirst, uint64_t base, const NextLevel& o, hipStream_t s);
 
 // Outputs.
-// Pack marks of each text into its own word range: words of text t start at
-// woff[t]; tfirst/tcount give its blocks.
-hipError_t launch_pack_marks(const uint8_t* marked, uint32_t T, const uint64_t* tfirst,
-                             const uint64_t* tcount, const uint64_t* woff, uint64_t nwords,
-                             uint64_t* words, hipStream_t s);
+// Marks of each text in its own word range (from woff[t]) and the marks before
+// each word; tfirst/tcount give its blocks, uoff their unmarked ranks.
+hipError_t launch_store_marks(const uint8_t* marked, const uint64_t* uoff, uint32_t T,
+                              const uint64_t* tfirst, const uint64_t* tcount, const uint64_t* woff,
+                              uint64_t nwords, uint64_t* words, uint64_t* wrank, hipStream_t s);
 // Leaves: bytes of every block of the last level, block after block.
 hipError_t launch_leaves(const uint8_t* T, const LevelDev& lv, const TextsDev& tx,
                          uint8_t* out, hipStream_t s);

@@ -166,305 +166,6 @@ hipError_t launch_keys(const PhaseArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-// ---------------------------------------------------------------- scan segments
-//
-// The probe scan walks "segments": ranges of window starts, each inside one run.
-// A window whose content also occurs earlier can never be the leftmost
-// occurrence of anything, so the previous level's results prune segments.  For
-// a marked parent block P (all windows of this level start inside some parent):
-//   - if the pair (P, P+1) has an earlier occurrence, every window starting in
-//     P lies inside a copy of it (windows are at most one parent long);
-//   - if the pair (P-1, P) has an earlier occurrence, or P itself does, every
-//     window that ends inside P is a copy.
-// Entries describe parents (or whole runs where there is no parent level) as
-// [a, e) plus these two facts; per phase they become segments.
-
-// Entries from runs: the whole run, nothing skipped.
-__global__ void k_entries_from_runs(LevelDev lv, uint64_t* ea, uint64_t* ee, uint8_t* ef,
-                                    uint32_t* erun) {
-  GRID_STRIDE(r, lv.R) {
-    ea[r] = lv.rs[r];
-    ee[r] = lv.re[r];
-    ef[r] = 0;
-    erun[r] = (uint32_t)r;
-  }
-}
-
-hipError_t launch_entries_from_runs(const LevelDev& lv, uint64_t* ea, uint64_t* ee, uint8_t* ef,
-                                    uint32_t* erun, hipStream_t s) {
-  if (!lv.R) return hipSuccess;
-  k_entries_from_runs<<<grid_for(lv.R, 256), 256, 0, s>>>(lv, ea, ee, ef, erun);
-  return hipGetLastError();
-}
-
-// Pair facts after phase 1: bit 0 of pf[j] = the pair (j, j+1) occurs earlier.
-__global__ void k_pair_facts(PhaseArgs a, uint8_t* pf) {
-  GRID_STRIDE(j, a.lv.c) {
-    pf[j] = (a.k.slot[j] != kNoKey && a.k.lm[j] < a.lv.st[j]) ? 1 : 0;
-  }
-}
-
-hipError_t launch_pair_facts(const PhaseArgs& a, uint8_t* pf, hipStream_t s) {
-  k_pair_facts<<<grid_for(a.lv.c, 256), 256, 0, s>>>(a, pf);
-  return hipGetLastError();
-}
-
-// Block facts after a phase 2 over all blocks: bit 1 = block j occurs earlier.
-__global__ void k_block_facts(PhaseArgs a, uint8_t* pf) {
-  GRID_STRIDE(j, a.lv.c) {
-    if (a.k.slot[j] != kNoKey && a.k.lm[j] < a.lv.st[j]) pf[j] |= 2;
-  }
-}
-
-hipError_t launch_block_facts(const PhaseArgs& a, uint8_t* pf, hipStream_t s) {
-  k_block_facts<<<grid_for(a.lv.c, 256), 256, 0, s>>>(a, pf);
-  return hipGetLastError();
-}
-
-// Entries of the next level: one per marked block P of this level (in order;
-// its children start at next index ntfirst[t] + cs[P] - cs[tfirst[t]]), then
-// one per entering text (whole text, nothing skipped).
-__global__ void k_entries_from_parents(LevelDev lv, TextsDev tx, const uint8_t* marked,
-                                       const uint8_t* pf, const uint64_t* uoff, const uint64_t* cs,
-                                       const uint64_t* tfirst, const uint64_t* ntfirst,
-                                       uint64_t* ea, uint64_t* ee, uint8_t* ef, uint64_t* echild) {
-  GRID_STRIDE(P, lv.c) {
-    if (!marked[P]) continue;
-    const uint64_t k = P - uoff[P];
-    const uint32_t t = lv.text[P];
-    const uint64_t st = lv.st[P], te = tx.tend[t];
-    ea[k] = st;
-    ee[k] = st + (te - st < lv.b ? te - st : lv.b);
-    uint8_t f = 0;
-    if (pf[P] & 1) f |= kSkipCross;
-    if ((pf[P] & 2) || (P > 0 && (pf[P - 1] & 1))) f |= kSkipInterior;
-    ef[k] = f;
-    echild[k] = ntfirst[t] + (cs[P] - cs[tfirst[t]]);
-  }
-}
-
-__global__ void k_entries_entering(const uint32_t* ids, uint32_t E, TextsDev tx, uint64_t base,
-                                   const uint64_t* ntfirst, uint64_t* ea, uint64_t* ee,
-                                   uint8_t* ef, uint64_t* echild) {
-  GRID_STRIDE(k, E) {
-    const uint32_t t = ids[k];
-    ea[base + k] = tx.tstart[t];
-    ee[base + k] = tx.tend[t];
-    ef[base + k] = 0;
-    echild[base + k] = ntfirst[t];
-  }
-}
-
-hipError_t launch_entries_next(const LevelDev& lv, const TextsDev& tx, const uint8_t* marked,
-                               const uint8_t* pf, const uint64_t* uoff, const uint64_t* cs,
-                               const uint64_t* tfirst, const uint64_t* ntfirst, uint64_t nmarked,
-                               const uint32_t* ids, uint32_t E, uint64_t* ea, uint64_t* ee,
-                               uint8_t* ef, uint64_t* echild, hipStream_t s) {
-  if (lv.c)
-    k_entries_from_parents<<<grid_for(lv.c, 256), 256, 0, s>>>(lv, tx, marked, pf, uoff, cs, tfirst,
-                                                               ntfirst, ea, ee, ef, echild);
-  if (E)
-    k_entries_entering<<<grid_for(E, 256), 256, 0, s>>>(ids, E, tx, nmarked, ntfirst, ea, ee, ef,
-                                                          echild);
-  return hipGetLastError();
-}
-
-__global__ void k_child_flags(SegDev sg, uint64_t b, const uint64_t* echild, uint8_t* cflag) {
-  GRID_STRIDE(k, sg.E) {
-    const uint8_t f = sg.ef[k];
-    if (!f) continue;
-    const uint64_t n = (sg.ee[k] - sg.ea[k] + b - 1) / b;
-    const uint64_t c0 = echild[k];
-    for (uint64_t i = 0; i < n; ++i) cflag[c0 + i] = f | (i + 1 == n ? kLastChild : 0);
-  }
-}
-
-hipError_t launch_child_flags(const SegDev& sg, uint64_t b, const uint64_t* echild, uint8_t* cflag,
-                              hipStream_t s) {
-  if (!sg.E) return hipSuccess;
-  k_child_flags<<<grid_for(sg.E, 256), 256, 0, s>>>(sg, b, echild, cflag);
-  return hipGetLastError();
-}
-
-// Run of each entry, from the block its children start with.
-__global__ void k_entry_runs(const uint64_t* echild, uint64_t E, const uint32_t* run,
-                             uint32_t* erun) {
-  GRID_STRIDE(k, E) erun[k] = run[echild[k]];
-}
-
-hipError_t launch_entry_runs(const uint64_t* echild, uint64_t E, const uint32_t* run,
-                             uint32_t* erun, hipStream_t s) {
-  if (!E) return hipSuccess;
-  k_entry_runs<<<grid_for(E, 256), 256, 0, s>>>(echild, E, run, erun);
-  return hipGetLastError();
-}
-
-// Per phase: segment k = window starts [ws[k], ws[k] + cnt - 1] (cnt into woff[k]),
-// bounded by the run end sre[k]; stext[k] = the run's text.
-__global__ void k_segments(PhaseArgs a, SegDev sg, uint64_t* woff) {
-  GRID_STRIDE(k, sg.E) {
-    const uint32_t r = sg.erun[k];
-    const uint32_t t = a.lv.rtext[r];
-    const uint64_t re = a.lv.re[r];
-    const uint64_t L = a.Lmain;
-    uint64_t Lmin = L;
-    const uint64_t oL = a.odd.L[t];
-    if (oL && oL < Lmin) Lmin = oL;
-    const uint8_t f = sg.ef[k];
-    uint64_t lo = sg.ea[k];
-    if (f & kSkipInterior) {
-      const uint64_t x = sg.ee[k] + 1 > L ? sg.ee[k] + 1 - L : 0;  // first start crossing e
-      if (x > lo) lo = x;
-    }
-    uint64_t cnt = 0;
-    if (a.odd.nkeys[t] && !(f & kSkipCross) && re >= Lmin) {
-      uint64_t hi = sg.ee[k] - 1;
-      if (re - Lmin < hi) hi = re - Lmin;
-      if (hi >= lo && sg.ee[k] > lo) cnt = hi - lo + 1;
-    }
-    sg.ws[k] = lo;
-    sg.sre[k] = re;
-    sg.stext[k] = t;
-    woff[k] = cnt;
-  }
-}
-
-hipError_t launch_segments(const PhaseArgs& a, const SegDev& sg, uint64_t* woff, hipStream_t s) {
-  if (!sg.E) return hipSuccess;
-  k_segments<<<grid_for(sg.E, 256), 256, 0, s>>>(a, sg, woff);
-  return hipGetLastError();
-}
-
-// Phase-2 segments from this level's phase-1 results.  A window of length b
-// that starts in block Q lies inside the pair (Q, Q+1), so if that pair occurs
-// earlier, so does the window: Q contributes no window starts.  Consecutive
-// blocks of a run that keep their starts form one segment (their starts are
-// consecutive positions).
-//   k_block_seg_counts: wc[Q] = starts of Q, head[Q] = 1 where a segment begins;
-//   (exclusive scans of both, totals at index c)
-//   k_block_segments: segment k < S (S = head total) from its first block;
-//   entries S..c repeat the window total (and name text 0), so a scan over c
-//   segments works.
-__global__ void k_block_seg_counts(PhaseArgs a, const uint8_t* pf, uint64_t* wc, uint64_t* head) {
-  const LevelDev lv = a.lv;
-  GRID_STRIDE(Q, lv.c) {
-    const uint32_t t = lv.text[Q];
-    const uint64_t re = lv.re[lv.run[Q]];
-    const uint64_t st = lv.st[Q];
-    uint64_t Lmin = a.Lmain;
-    const uint64_t oL = a.odd.L[t];
-    if (oL && oL < Lmin) Lmin = oL;
-    uint64_t cnt = 0;
-    if (a.odd.nkeys[t] && !(pf[Q] & 1) && re >= Lmin) {
-      uint64_t hi = st + block_len(lv, a.tx, Q) - 1;
-      if (re - Lmin < hi) hi = re - Lmin;
-      if (hi >= st) cnt = hi - st + 1;
-    }
-    wc[Q] = cnt;
-    bool h = cnt != 0;
-    if (h && Q > 0 && lv.run[Q - 1] == lv.run[Q] && !(pf[Q - 1] & 1)) {
-      // the previous block keeps its starts: they run up to st - 1 (a block
-      // whose starts stop short of its end is the run's last with any)
-      h = false;
-    }
-    head[Q] = h ? 1 : 0;
-  }
-}
-
-__global__ void k_block_segments(PhaseArgs a, const uint64_t* wcs, const uint64_t* hs,
-                                 uint64_t* ws, uint64_t* sre, uint32_t* stext, uint64_t* woff) {
-  const LevelDev lv = a.lv;
-  const uint64_t S = hs[lv.c], W = wcs[lv.c];
-  GRID_STRIDE(k, lv.c + 1) {
-    if (k < lv.c && hs[k + 1] != hs[k]) {
-      const uint64_t g = hs[k];
-      woff[g] = wcs[k];
-      ws[g] = lv.st[k];
-      sre[g] = lv.re[lv.run[k]];
-      stext[g] = lv.text[k];
-    }
-    if (k >= S) {
-      // padding: no windows, and a valid text for lanes that land here
-      woff[k] = W;
-      if (k < lv.c) {
-        ws[k] = 0;
-        sre[k] = 0;
-        stext[k] = 0;
-      }
-    }
-  }
-}
-
-hipError_t launch_block_seg_counts(const PhaseArgs& a, const uint8_t* pf, uint64_t* wc,
-                                   uint64_t* head, hipStream_t s) {
-  if (!a.lv.c) return hipSuccess;
-  k_block_seg_counts<<<grid_for(a.lv.c, 256), 256, 0, s>>>(a, pf, wc, head);
-  return hipGetLastError();
-}
-
-hipError_t launch_block_segments(const PhaseArgs& a, const uint64_t* wcs, const uint64_t* hs,
-                                 uint64_t* ws, uint64_t* sre, uint32_t* stext, uint64_t* woff,
-                                 hipStream_t s) {
-  k_block_segments<<<grid_for(a.lv.c + 1, 256), 256, 0, s>>>(a, wcs, hs, ws, sre, stext, woff);
-  return hipGetLastError();
-}
-
-// Phase-1 segments are one per entry (a parent, at most tau b window starts),
-// so at the lower levels a tile of the scan would cross several of them.  An
-// entry whose starts continue those of the previous entry (same run, first
-// start one past the previous entry's last: adjacent parents that no fact cut
-// apart) joins its segment.  Window numbers and positions stay the same; only
-// the boundaries the scan has to walk go.
-//   k_seg_heads: head[k] = 1 where entry k opens a merged segment (woff: the
-//   scanned window counts, total at E);
-//   k_seg_merge: merged segment g from the entry that opens it; entries S..E
-//   repeat the window total (and name text 0), as the scan expects E of them.
-__global__ void k_seg_heads(SegDev sg, const uint64_t* woff, uint64_t* head) {
-  GRID_STRIDE(k, sg.E) {
-    const uint64_t cnt = woff[k + 1] - woff[k];
-    bool h = cnt != 0;
-    if (h && k > 0) {
-      const uint64_t pc = woff[k] - woff[k - 1];
-      if (pc && sg.erun[k - 1] == sg.erun[k] && sg.ws[k - 1] + pc == sg.ws[k]) h = false;
-    }
-    head[k] = h ? 1 : 0;
-  }
-}
-
-__global__ void k_seg_merge(SegDev sg, const uint64_t* woff, const uint64_t* hs, uint64_t* ws,
-                            uint64_t* sre, uint32_t* stext, uint64_t* woff2) {
-  const uint64_t S = hs[sg.E], W = woff[sg.E];
-  GRID_STRIDE(k, sg.E + 1) {
-    if (k < sg.E && hs[k + 1] != hs[k]) {
-      const uint64_t g = hs[k];
-      woff2[g] = woff[k];
-      ws[g] = sg.ws[k];
-      sre[g] = sg.sre[k];
-      stext[g] = sg.stext[k];
-    }
-    if (k >= S) {
-      woff2[k] = W;
-      if (k < sg.E) {
-        ws[k] = 0;
-        sre[k] = 0;
-        stext[k] = 0;
-      }
-    }
-  }
-}
-
-hipError_t launch_seg_heads(const SegDev& sg, const uint64_t* woff, uint64_t* head, hipStream_t s) {
-  if (!sg.E) return hipSuccess;
-  k_seg_heads<<<grid_for(sg.E, 256), 256, 0, s>>>(sg, woff, head);
-  return hipGetLastError();
-}
-
-hipError_t launch_seg_merge(const SegDev& sg, const uint64_t* woff, const uint64_t* hs, uint64_t* ws,
-                            uint64_t* sre, uint32_t* stext, uint64_t* woff2, hipStream_t s) {
-  k_seg_merge<<<grid_for(sg.E + 1, 256), 256, 0, s>>>(sg, woff, hs, ws, sre, stext, woff2);
-  return hipGetLastError();
-}
-
 // ---------------------------------------------------------------- probe scan (a4, a6)
 
 constexpr int kScanK = 16;                      // windows per lane per chunk
@@ -569,7 +270,7 @@ __device__ __forceinline__ uint64_t round_tile(uint64_t W, uint32_t f) {
 // nothing, now fail the filter; and of the keys that occur nowhere earlier, those
 // that start before the round drop out.
 __global__ void k_refilter(PhaseArgs a, const uint64_t* __restrict__ woff, uint32_t f0) {
-  const uint64_t R = a.lv.R, W = woff[R];
+  const uint64_t R = a.segn[0], W = a.segn[1];
   const uint64_t w = round_tile(W, f0) * kScanChunk;
   if (w >= W) return;
   const uint64_t r = segment_of(woff, R, w);
@@ -595,8 +296,9 @@ hipError_t launch_refilter(const PhaseArgs& a, const uint64_t* woff, uint32_t f0
 // The segment of each tile's first window (tile ch: window number ch kScanChunk),
 // one thread per tile, so that a wave of the scan reads it with one load instead
 // of searching for it in log2(R) dependent ones.
-__global__ void k_tile_segs(const uint64_t* __restrict__ woff, uint64_t R, uint32_t* __restrict__ tseg) {
-  const uint64_t W = woff[R];
+__global__ void k_tile_segs(const uint64_t* __restrict__ woff, const uint64_t* __restrict__ segn,
+                            uint32_t* __restrict__ tseg) {
+  const uint64_t R = segn[0], W = segn[1];
   GRID_STRIDE(ch, (W + kScanChunk - 1) / kScanChunk) tseg[ch] = (uint32_t)segment_of(woff, R, ch * kScanChunk);
 }
 
@@ -634,8 +336,7 @@ void k_probe_dense(PhaseArgs a, const uint64_t* __restrict__ woff, uint32_t f0, 
   const int lane = lane_id();
   ProbeQueue<SALT> queue(a, s_lds + (1ull << (fbits - 6)) + (uint64_t)(threadIdx.x >> 6) * kQueue);
 
-  const uint64_t R = a.lv.R;
-  const uint64_t W = woff[R];
+  const uint64_t R = a.segn[0], W = a.segn[1];
   const uint64_t t0 = round_tile(W, f0), t1 = round_tile(W, f1);
   // wave-uniform (all of a wave's lanes share threadIdx.x / 64)
   const uint64_t gw = (uint64_t)blockIdx.x * (kProbeThreads / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -889,8 +590,7 @@ void k_probe_scan(PhaseArgs a, const uint64_t* __restrict__ woff, uint32_t f0, u
   const uint32_t fbits = a.filt_bits;
   const bool two = a.filt_two != 0;
   const int lane = lane_id();
-  const uint64_t R = a.lv.R;
-  const uint64_t W = woff[R];
+  const uint64_t R = a.segn[0], W = a.segn[1];
   const uint64_t gw = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
   const uint64_t nw = ((uint64_t)gridDim.x * blockDim.x) >> 6;
 
@@ -994,7 +694,6 @@ static uint64_t column_rows(uint64_t tiles, uint64_t stride) {
 hipError_t launch_probe_scan(const PhaseArgs& a, const uint64_t* woff, bool has_odd,
                              bool has_salt, uint64_t max_windows, int mode, uint32_t* tseg,
                              uint32_t f0, uint32_t f1, hipStream_t s) {
-  if (a.lv.R == 0) return hipSuccess;
   if (f0 >= f1 || f1 > 64 || (mode != 1 && (f0 != 0 || f1 != 64))) return hipErrorInvalidValue;
   const uint64_t all = (max_windows + kScanChunk - 1) / kScanChunk;
   const uint64_t tiles = (all * (f1 - f0) + 63) / 64;
@@ -1015,7 +714,7 @@ hipError_t launch_probe_scan(const PhaseArgs& a, const uint64_t* woff, bool has_
     return hipGetLastError();
   };
   if (mode == 1 && !lean) {
-    if (tseg && f0 == 0) k_tile_segs<<<grid_for(all, 256), 256, 0, s>>>(woff, a.lv.R, tseg);
+    if (tseg && f0 == 0) k_tile_segs<<<grid_for(all, 256), 256, 0, s>>>(woff, a.segn, tseg);
     const uint64_t stride = a.Lmain % kScanChunk == 0 && a.Lmain / kScanChunk < tiles ? a.Lmain / kScanChunk : 1;
     const uint64_t rows = stride * kScanChunk == a.Lmain ? column_rows(tiles, stride) : 1;
     const unsigned grid = grid_for(tiles * 64, kProbeThreads, 256);
@@ -1073,8 +772,7 @@ void k_byte_scan(PhaseArgs a, const uint64_t* __restrict__ woff) {
   const int lane = lane_id();
   uint64_t* q = s_lds + (1ull << (bits - 6)) + (uint64_t)(threadIdx.x >> 6) * kQueue;
   uint32_t qn = 0;  // wave-uniform queue length
-  const uint64_t R = a.lv.R;
-  const uint64_t W = woff[R];
+  const uint64_t R = a.segn[0], W = a.segn[1];
   const uint64_t gw = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
   const uint64_t nw = ((uint64_t)gridDim.x * blockDim.x) >> 6;
   const uint8_t* __restrict__ T = a.T;
@@ -1231,7 +929,6 @@ void k_byte_scan(PhaseArgs a, const uint64_t* __restrict__ woff) {
 
 hipError_t launch_byte_scan(const PhaseArgs& a, const uint64_t* woff, bool has_odd, bool has_salt,
                             uint64_t max_windows, hipStream_t s) {
-  if (a.lv.R == 0) return hipSuccess;
   if (a.bfilt_bits < 12 || a.bfilt_bits > 19) return hipErrorInvalidValue;
   const uint64_t waves = (max_windows + 64 * kByteK - 1) / (64 * kByteK);
   const unsigned grid = grid_for(waves * 64, kByteThreads, 512);
@@ -1492,257 +1189,7 @@ hipError_t launch_retry(const PhaseArgs& a, const VerifyBufs& v, hipStream_t s) 
   return hipGetLastError();
 }
 
-// ---------------------------------------------------------------- marks (a5)
-
-__global__ void k_mark(PhaseArgs a, uint8_t* marked) {
-  const LevelDev lv = a.lv;
-  GRID_STRIDE(j, lv.c) {
-    bool m = a.k.slot[j] != kNoKey && a.k.lm[j] == lv.st[j];
-    if (j > 0 && a.k.slot[j - 1] != kNoKey && a.k.lm[j - 1] == lv.st[j - 1]) m = true;
-    const uint32_t r = lv.run[j];
-    const bool left = j > 0 && lv.run[j - 1] == r;
-    const bool right = j + 1 < lv.c && lv.run[j + 1] == r;
-    if (!left && !right) m = true;  // a block with no consecutive neighbour
-    marked[j] = m ? 1 : 0;
-  }
-}
-
-hipError_t launch_mark(const PhaseArgs& a, uint8_t* marked, hipStream_t s) {
-  k_mark<<<grid_for(a.lv.c, 256), 256, 0, s>>>(a, marked);
-  return hipGetLastError();
-}
-
-// The mark of block j (as k_mark): its pair or its left neighbour's pair is
-// leftmost, or it has no consecutive neighbour.
-__device__ __forceinline__ bool mark_of(const PhaseArgs& a, uint64_t j) {
-  const LevelDev& lv = a.lv;
-  const auto leftmost = [&](uint64_t q) { return a.k.slot[q] != kNoKey && a.k.lm[q] == lv.st[q]; };
-  if (leftmost(j) || (j > 0 && leftmost(j - 1))) return true;
-  const uint32_t r = lv.run[j];
-  const bool left = j > 0 && lv.run[j - 1] == r;
-  const bool right = j + 1 < lv.c && lv.run[j + 1] == r;
-  return !left && !right;
-}
-
-// After phase 1, in one pass: the marks, the pair facts (as k_pair_facts), the
-// unmarked indicator that the pointer ranks scan from, and where the next
-// level's runs start.  The children of a maximal group of consecutive marked
-// blocks of one run are consecutive blocks of one run, so nrun[j] = 1 exactly
-// where such a group starts.
-__global__ void k_mark_facts(PhaseArgs a, uint8_t* marked, uint8_t* pf, uint64_t* ucnt,
-                             uint64_t* nrun) {
-  const LevelDev lv = a.lv;
-  GRID_STRIDE(j, lv.c) {
-    const bool own = a.k.slot[j] != kNoKey;
-    const bool m = mark_of(a, j);
-    marked[j] = m ? 1 : 0;
-    pf[j] = (own && a.k.lm[j] < lv.st[j]) ? 1 : 0;
-    ucnt[j] = m ? 0 : 1;
-    nrun[j] = (m && (j == 0 || lv.run[j - 1] != lv.run[j] || !mark_of(a, j - 1))) ? 1 : 0;
-  }
-}
-
-hipError_t launch_mark_facts(const PhaseArgs& a, uint8_t* marked, uint8_t* pf, uint64_t* ucnt,
-                             uint64_t* nrun, hipStream_t s) {
-  if (!a.lv.c) return hipSuccess;
-  k_mark_facts<<<grid_for(a.lv.c, 256), 256, 0, s>>>(a, marked, pf, ucnt, nrun);
-  return hipGetLastError();
-}
-
-__global__ void k_unmarked_counts(const uint8_t* marked, uint64_t c, uint64_t* cnt) {
-  GRID_STRIDE(j, c) cnt[j] = marked[j] ? 0 : 1;
-}
-
-hipError_t launch_unmarked_counts(const uint8_t* marked, uint64_t c, uint64_t* cnt,
-                                  hipStream_t s) {
-  k_unmarked_counts<<<grid_for(c, 256), 256, 0, s>>>(marked, c, cnt);
-  return hipGetLastError();
-}
-
-// ---------------------------------------------------------------- pointers (a7)
-
-__global__ void k_pointers(PhaseArgs a, const uint8_t* marked, const uint64_t* uoff,
-                           const uint64_t* tfirst, uint64_t* pb, uint64_t* po, uint32_t* err) {
-  const LevelDev lv = a.lv;
-  GRID_STRIDE(j, lv.c) {
-    if (marked[j]) continue;
-    const uint64_t p = a.k.lm[j];
-    const uint32_t tx = lv.text[j];
-    // the target block: the last one starting at or before p, searched among
-    // the blocks of j's own text before j (an occurrence lies in its text and
-    // ends by j's start; the checks below catch anything else)
-    uint64_t lo = tfirst[tx], hi = j;
-    while (hi - lo > 1) {
-      const uint64_t mid = (lo + hi) >> 1;
-      if (lv.st[mid] <= p) lo = mid; else hi = mid;
-    }
-    const uint64_t t = lo;
-    const uint64_t lj = block_len(lv, a.tx, j), lt = block_len(lv, a.tx, t);
-    bool ok = lv.st[t] <= p && p < lv.st[t] + lt && marked[t] && lv.text[t] == tx &&
-              p + lj <= lv.st[j];
-    if (ok && p + lj > lv.st[t] + lt)
-      ok = t + 1 < lv.c && lv.run[t + 1] == lv.run[t] && marked[t + 1];
-    if (!ok) *err = 1;
-    const uint64_t u = uoff[j];
-    pb[u] = t - tfirst[tx];
-    po[u] = p - lv.st[t];
-  }
-}
-
-hipError_t launch_pointers(const PhaseArgs& a, const uint8_t* marked, const uint64_t* uoff,
-                           const uint64_t* tfirst, uint64_t* ptr_block, uint64_t* ptr_off,
-                           uint32_t* err, hipStream_t s) {
-  k_pointers<<<grid_for(a.lv.c, 256), 256, 0, s>>>(a, marked, uoff, tfirst, ptr_block, ptr_off,
-                                                    err);
-  return hipGetLastError();
-}
-
-// ---------------------------------------------------------------- split (a8)
-
-__global__ void k_child_counts(LevelDev lv, TextsDev tx, const uint8_t* marked, uint64_t bn,
-                               uint64_t* cnt) {
-  GRID_STRIDE(j, lv.c) {
-    cnt[j] = marked[j] ? (block_len(lv, tx, j) + bn - 1) / bn : 0;
-  }
-}
-
-hipError_t launch_child_counts(const LevelDev& lv, const TextsDev& tx, const uint8_t* marked,
-                               uint64_t bn, uint64_t* cnt, hipStream_t s) {
-  k_child_counts<<<grid_for(lv.c, 256), 256, 0, s>>>(lv, tx, marked, bn, cnt);
-  return hipGetLastError();
-}
-
-__global__ void k_text_counts(uint32_t T, const uint64_t* cs, const uint64_t* tfirst,
-                              const uint64_t* tcount, const uint64_t* enter, uint64_t* ncount) {
-  GRID_STRIDE(t, T) {
-    const uint64_t f = tfirst[t];
-    ncount[t] = cs[f + tcount[t]] - cs[f] + (enter ? enter[t] : 0);
-  }
-}
-
-hipError_t launch_text_counts(uint32_t T, const uint64_t* cs, const uint64_t* tfirst,
-                              const uint64_t* tcount, const uint64_t* enter, uint64_t* ncount,
-                              hipStream_t s) {
-  k_text_counts<<<grid_for(T, 256), 256, 0, s>>>(T, cs, tfirst, tcount, enter, ncount);
-  return hipGetLastError();
-}
-
-__global__ void k_write_children(LevelDev lv, TextsDev tx, const uint8_t* marked, uint64_t bn,
-                                 const uint64_t* cs, const uint64_t* tfirst,
-                                 const uint64_t* ntfirst, uint64_t* nst, uint32_t* ntext) {
-  GRID_STRIDE(j, lv.c) {
-    if (!marked[j]) continue;
-    const uint32_t t = lv.text[j];
-    const uint64_t base = ntfirst[t] + (cs[j] - cs[tfirst[t]]);
-    const uint64_t nk = cs[j + 1] - cs[j];
-    const uint64_t st = lv.st[j];
-    for (uint64_t k = 0; k < nk; ++k) {
-      nst[base + k] = st + k * bn;
-      ntext[base + k] = t;
-    }
-  }
-}
-
-hipError_t launch_write_children(const LevelDev& lv, const TextsDev& tx, const uint8_t* marked,
-                                 uint64_t bn, uint32_t tau, const uint64_t* cs,
-                                 const uint64_t* tfirst, const uint64_t* ntfirst, uint64_t* nst,
-                                 uint32_t* ntext, hipStream_t s) {
-  (void)tau;
-  k_write_children<<<grid_for(lv.c, 256), 256, 0, s>>>(lv, tx, marked, bn, cs, tfirst, ntfirst,
-                                                        nst, ntext);
-  return hipGetLastError();
-}
-
-__global__ void k_write_entering(const uint32_t* ids, TextsDev tx, uint64_t bn,
-                                 const uint64_t* ntfirst, uint64_t* nst, uint32_t* ntext) {
-  const uint32_t t = ids[blockIdx.x];
-  const uint64_t ts = tx.tstart[t], te = tx.tend[t];
-  const uint64_t nb = (te - ts + bn - 1) / bn;
-  const uint64_t base = ntfirst[t];
-  for (uint64_t k = threadIdx.x; k < nb; k += blockDim.x) {
-    nst[base + k] = ts + k * bn;
-    ntext[base + k] = t;
-  }
-}
-
-hipError_t launch_write_entering(const uint32_t* ids, uint32_t E, const TextsDev& tx,
-                                 uint64_t bn, const uint64_t* ntfirst, uint64_t* nst,
-                                 uint32_t* ntext, hipStream_t s) {
-  if (!E) return hipSuccess;
-  k_write_entering<<<E, 256, 0, s>>>(ids, tx, bn, ntfirst, nst, ntext);
-  return hipGetLastError();
-}
-
-__global__ void k_run_flags(const uint64_t* st, const uint32_t* text, uint64_t c, uint64_t b,
-                            uint64_t* rflag) {
-  GRID_STRIDE(j, c) {
-    rflag[j] = (j == 0 || text[j] != text[j - 1] || st[j] != st[j - 1] + b) ? 1 : 0;
-  }
-}
-
-hipError_t launch_run_flags(const uint64_t* st, const uint32_t* text, uint64_t c, uint64_t b,
-                            uint64_t* rflag, hipStream_t s) {
-  k_run_flags<<<grid_for(c, 256), 256, 0, s>>>(st, text, c, b, rflag);
-  return hipGetLastError();
-}
-
-__global__ void k_run_table(const uint64_t* st, const uint32_t* text, uint64_t c, uint64_t b,
-                            TextsDev tx, const uint64_t* roff, uint32_t* run, uint64_t* rs,
-                            uint64_t* re, uint32_t* rtext) {
-  GRID_STRIDE(j, c) {
-    const uint64_t r = roff[j + 1] - 1;
-    run[j] = (uint32_t)r;
-    if (roff[j + 1] != roff[j]) {
-      rs[r] = st[j];
-      rtext[r] = text[j];
-    }
-    const bool last = (j + 1 == c) || (roff[j + 2] != roff[j + 1]);
-    if (last) {
-      const uint64_t te = tx.tend[text[j]];
-      re[r] = st[j] + (te - st[j] < b ? te - st[j] : b);
-    }
-  }
-}
-
-hipError_t launch_run_table(const uint64_t* st, const uint32_t* text, uint64_t c, uint64_t b,
-                            const TextsDev& tx, const uint64_t* roff, uint32_t* run,
-                            uint64_t* rs, uint64_t* re, uint32_t* rtext, hipStream_t s) {
-  k_run_table<<<grid_for(c, 256), 256, 0, s>>>(st, text, c, b, tx, roff, run, rs, re, rtext);
-  return hipGetLastError();
-}
-
-// ---------------------------------------------------------------- outputs
-
-__global__ void k_pack_marks(const uint8_t* marked, uint32_t T, const uint64_t* tfirst,
-                             const uint64_t* tcount, const uint64_t* woff, uint64_t nwords,
-                             uint64_t* words) {
-  GRID_STRIDE(wi, nwords) {
-    uint64_t lo = 0, hi = T;
-    while (hi - lo > 1) {
-      const uint64_t mid = (lo + hi) >> 1;
-      if (woff[mid] <= wi) lo = mid; else hi = mid;
-    }
-    // skip texts with no words (equal offsets): take the last one not past wi
-    const uint64_t t = lo;
-    const uint64_t lw = wi - woff[t];
-    const uint64_t f = tfirst[t], cnt = tcount[t];
-    uint64_t word = 0;
-    for (uint64_t k = 0; k < 64; ++k) {
-      const uint64_t j = lw * 64 + k;
-      if (j < cnt && marked[f + j]) word |= 1ull << k;
-    }
-    words[wi] = word;
-  }
-}
-
-hipError_t launch_pack_marks(const uint8_t* marked, uint32_t T, const uint64_t* tfirst,
-                             const uint64_t* tcount, const uint64_t* woff, uint64_t nwords,
-                             uint64_t* words, hipStream_t s) {
-  if (!nwords) return hipSuccess;
-  k_pack_marks<<<grid_for(nwords, 256), 256, 0, s>>>(marked, T, tfirst, tcount, woff, nwords,
-                                                      words);
-  return hipGetLastError();
-}
+// ---------------------------------------------------------------- leaves (a8)
 
 // Leaf bytes: block j of the last level lands at j*b (texts' regions are
 // contiguous; only a text-final block is short, and it ends its region; the

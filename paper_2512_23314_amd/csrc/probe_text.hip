@@ -66,8 +66,7 @@ void k_probe_text(PhaseArgs a, const uint64_t* __restrict__ woff, uint64_t span_
   const uint32_t wave = threadIdx.x >> 6;
   uint32_t qn = 0;  // wave-uniform queue length
 
-  const uint64_t R = a.lv.R;
-  const uint64_t W = woff[R];
+  const uint64_t R = a.segn[0], W = a.segn[1];
   const uint64_t* __restrict__ P = a.P;
   const uint32_t* __restrict__ H = a.P32;
   const uint64_t* __restrict__ rs_ = a.lv.rs;
@@ -479,10 +478,10 @@ void k_probe_text(PhaseArgs a, const uint64_t* __restrict__ woff, uint64_t span_
 // segment and, when both belong to one text, that text (else kNoText), as
 // three words.  One thread per span, so that the resident workgroups of the
 // scan read a span's facts with one load instead of searching for them.
-__global__ void k_span_info(const uint64_t* __restrict__ woff, uint64_t R,
+__global__ void k_span_info(const uint64_t* __restrict__ woff, const uint64_t* __restrict__ segn,
                             const uint32_t* __restrict__ rtext, uint64_t span, uint64_t nspan,
                             uint64_t* __restrict__ info) {
-  const uint64_t W = woff[R];
+  const uint64_t R = segn[0], W = segn[1];
   for (uint64_t sp = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; sp < nspan;
        sp += (uint64_t)gridDim.x * blockDim.x) {
     const uint64_t w0 = sp * span;
@@ -503,19 +502,17 @@ uint64_t probe_text_spans(uint64_t max_windows, uint64_t span_chunks) {
 
 hipError_t launch_span_info(const PhaseArgs& a, const uint64_t* woff, uint64_t max_windows,
                             uint64_t span_chunks, uint64_t* span_info, hipStream_t s) {
-  if (a.lv.R == 0) return hipSuccess;
   if (span_chunks == 0 || !span_info) return hipErrorInvalidValue;
   const uint64_t spans = probe_text_spans(max_windows, span_chunks);
   const uint64_t g = (spans + 255) / 256;
   k_span_info<<<(unsigned)(g < 4096 ? (g ? g : 1) : 4096), 256, 0, s>>>(
-      woff, a.lv.R, a.lv.rtext, span_chunks * kProbeTile, spans, span_info);
+      woff, a.segn, a.lv.rtext, span_chunks * kProbeTile, spans, span_info);
   return hipGetLastError();
 }
 
 hipError_t launch_probe_text(const PhaseArgs& a, const uint64_t* woff, bool has_odd,
                              uint64_t max_windows, uint64_t span_chunks, uint64_t* span_ctr,
                              const uint64_t* span_info, bool short_segments, hipStream_t s) {
-  if (a.lv.R == 0) return hipSuccess;
   if (!a.tf_words || !a.pre32 || span_chunks == 0 || !span_info) return hipErrorInvalidValue;
   const uint64_t spans = probe_text_spans(max_windows, span_chunks);
   // one resident 1024-thread workgroup per CU (256 CUs): registers (up to 128

@@ -363,34 +363,4 @@ hipError_t launch_text_deltas(const uint64_t* scanned, const uint64_t* tfirst,
   return hipGetLastError();
 }
 
-__global__ void k_word_pop(const uint64_t* words, uint64_t nwords, uint64_t* out) {
-  GRID_STRIDE(w, nwords) out[w] = __popcll(words[w]);
-}
-
-hipError_t launch_word_pop(const uint64_t* words, uint64_t nwords, uint64_t* out, hipStream_t s) {
-  if (!nwords) return hipSuccess;
-  k_word_pop<<<grid_for(nwords, 256), 256, 0, s>>>(words, nwords, out);
-  return hipGetLastError();
-}
-
-// wrank[w] = marks in words [first word of w's text, w)
-__global__ void k_word_rank(const uint64_t* scanned, uint32_t T, const uint64_t* woff,
-                            uint64_t nwords, uint64_t* wrank) {
-  GRID_STRIDE(w, nwords) {
-    uint64_t lo = 0, hi = T;
-    while (hi - lo > 1) {
-      const uint64_t mid = (lo + hi) >> 1;
-      if (woff[mid] <= w) lo = mid; else hi = mid;
-    }
-    wrank[w] = scanned[w] - scanned[woff[lo]];
-  }
-}
-
-hipError_t launch_word_rank(const uint64_t* scanned, uint32_t T, const uint64_t* woff,
-                            uint64_t nwords, uint64_t* wrank, hipStream_t s) {
-  if (!nwords) return hipSuccess;
-  k_word_rank<<<grid_for(nwords, 256), 256, 0, s>>>(scanned, T, woff, nwords, wrank);
-  return hipGetLastError();
-}
-
 }  // namespace bt

@@ -95,8 +95,5 @@ hipError_t launch_last_block_len(const LevelDev& lv, const TextsDev& tx, const u
                                  const uint64_t* tcount, uint64_t* out, hipStream_t s);
 hipError_t launch_text_deltas(const uint64_t* scanned, const uint64_t* tfirst,
                               const uint64_t* tcount, uint32_t T, uint64_t* out, hipStream_t s);
-hipError_t launch_word_pop(const uint64_t* words, uint64_t nwords, uint64_t* out, hipStream_t s);
-hipError_t launch_word_rank(const uint64_t* scanned, uint32_t T, const uint64_t* woff,
-                            uint64_t nwords, uint64_t* wrank, hipStream_t s);
 
 }  // namespace bt

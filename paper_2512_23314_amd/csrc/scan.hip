@@ -28,11 +28,6 @@ hipError_t launch_fill_u64(uint64_t* p, uint64_t v, uint64_t n, hipStream_t s) {
   k_fill<uint64_t><<<grid_for(n, 256), 256, 0, s>>>(p, v, n);
   return hipGetLastError();
 }
-hipError_t launch_fill_u32(uint32_t* p, uint32_t v, uint64_t n, hipStream_t s) {
-  if (!n) return hipSuccess;
-  k_fill<uint32_t><<<grid_for(n, 256), 256, 0, s>>>(p, v, n);
-  return hipGetLastError();
-}
 hipError_t launch_fill_u8(uint8_t* p, uint8_t v, uint64_t n, hipStream_t s) {
   if (!n) return hipSuccess;
   k_fill<uint8_t><<<grid_for(n, 256), 256, 0, s>>>(p, v, n);
@@ -63,27 +58,6 @@ hipError_t launch_fill_many(const FillList& f, hipStream_t s) {
   const dim3 grid(grid_for((most + 3) / 4, 256, 4096), (unsigned)f.n);
   k_fill_many<<<grid, 256, 0, s>>>(f);
   return hipGetLastError();
-}
-
-// Exclusive scan of one block's values (256 threads); returns the block total.
-__device__ uint64_t block_excl_scan(uint64_t v, uint64_t* s_w) {
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  uint64_t inc = v;
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const uint64_t o = __shfl_up(inc, d);
-    if (lane >= d) inc += o;
-  }
-  if (lane == 63) s_w[wv] = inc;
-  __syncthreads();
-  uint64_t before = 0, total = 0;
-#pragma unroll
-  for (int k = 0; k < kScanThreads / 64; ++k) {
-    if (k < wv) before += s_w[k];
-    total += s_w[k];
-  }
-  __syncthreads();
-  return before + inc - v + 0 * total;
 }
 
 __device__ uint64_t block_total(uint64_t v, uint64_t* s_w) {
@@ -164,49 +138,6 @@ __global__ __launch_bounds__(kScanThreads) void k_tile_scan(uint64_t* __restrict
              lane == (int)((n - 1 - wbase) & 63)) {
     a[n] = off + incl_last;
   }
-}
-
-__global__ __launch_bounds__(kScanThreads) void k_text_step(uint32_t T, const uint64_t* __restrict__ cs,
-                                                            const uint64_t* __restrict__ tfirst,
-                                                            const uint64_t* __restrict__ tcount,
-                                                            const uint64_t* __restrict__ enter,
-                                                            const uint64_t* __restrict__ uoff,
-                                                            uint64_t* __restrict__ ncount,
-                                                            uint64_t* __restrict__ nfirst,
-                                                            uint64_t* __restrict__ tu) {
-  __shared__ uint64_t s_w[kScanThreads / 64];
-  const uint64_t first = (uint64_t)threadIdx.x * kScanItems;
-  uint64_t v[kScanItems];
-  uint64_t sum = 0;
-#pragma unroll
-  for (int k = 0; k < kScanItems; ++k) {
-    const uint64_t t = first + k;
-    v[k] = 0;
-    if (t < T) {
-      const uint64_t f = tfirst[t], e = f + tcount[t];
-      v[k] = cs[e] - cs[f] + enter[t];
-      ncount[t] = v[k];
-      tu[t] = uoff[e] - uoff[f];
-    }
-    sum += v[k];
-  }
-  uint64_t run = block_excl_scan(sum, s_w);
-#pragma unroll
-  for (int k = 0; k < kScanItems; ++k) {
-    const uint64_t t = first + k;
-    if (t < T) nfirst[t] = run;
-    run += v[k];
-    if (t + 1 == T || (T == 0 && t == 0)) nfirst[T] = run;
-  }
-}
-
-hipError_t launch_text_step(uint32_t T, const uint64_t* cs, const uint64_t* tfirst,
-                            const uint64_t* tcount, const uint64_t* enter, const uint64_t* uoff,
-                            uint64_t* ncount, uint64_t* nfirst, uint64_t* tu, hipStream_t s) {
-  if (T > kTextStepMax) return hipErrorInvalidValue;
-  static_assert(kTextStepMax == kScanTile, "one workgroup scans the texts");
-  k_text_step<<<1, kScanThreads, 0, s>>>(T, cs, tfirst, tcount, enter, uoff, ncount, nfirst, tu);
-  return hipGetLastError();
 }
 
 uint64_t scan_tmp_words(uint64_t n) {

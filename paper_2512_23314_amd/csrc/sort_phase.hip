@@ -42,7 +42,7 @@ constexpr uint64_t kSortChunk = 64 * 16;  // windows per wave and chunk
 // The text's short final key, if any, is compared directly, as in the scan.
 __global__ void k_sort_emit(PhaseArgs a, const uint64_t* __restrict__ woff, uint64_t none,
                             uint64_t* __restrict__ fpv, uint64_t* __restrict__ posv) {
-  const uint64_t R = a.lv.R, W = woff[R];
+  const uint64_t R = a.segn[0], W = a.segn[1];
   const uint64_t gw = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
   const uint64_t nw = ((uint64_t)gridDim.x * blockDim.x) >> 6;
   const uint64_t lane = threadIdx.x & 63;
