@@ -1090,10 +1090,9 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
     const SegDev sg{E_ent, ent_a.p, ent_e.p, ent_f.p, ent_child.p};
     const SegOut so{seg_ws.p, seg_re.p, seg_text.p, seg_woff.p, segn.p};
     Buf<uint8_t> facts = alloc<uint8_t>(ctx, c);
-    Buf<uint32_t> vlist = alloc<uint32_t>(ctx, c), vmis = alloc<uint32_t>(ctx, c),
-                  rlist = alloc<uint32_t>(ctx, c);
-    Buf<uint64_t> vbest = alloc<uint64_t>(ctx, c), rlb = alloc<uint64_t>(ctx, c),
-                  vcnt = alloc<uint64_t>(ctx, 2);
+    Buf<uint32_t> vlist = alloc<uint32_t>(ctx, c),
+                  vmis = alloc<uint32_t>(ctx, 2 * b > kSettleMax ? c : 0);
+    Buf<uint64_t> vbest = alloc<uint64_t>(ctx, c), vcnt = alloc<uint64_t>(ctx, 2);
     Buf<uint8_t> marked = alloc<uint8_t>(ctx, c);
     // LDS key filter of up to 2^20 bits, sized per phase from the key count
     Buf<uint32_t> filt = alloc<uint32_t>(ctx, (1ull << 20) / 32);
@@ -1101,7 +1100,7 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
     Buf<uint32_t> filt2 = alloc<uint32_t>(ctx, (1ull << ctx->tune.filter2_max_log2) / 32);
     int scan_mode = 1;
     uint32_t fbits = 12;
-    VerifyBufs vb{vlist.p, vbest.p, vmis.p, rlist.p, rlb.p, vcnt.p};
+    VerifyBufs vb{vlist.p, vbest.p, vmis.p, vcnt.p};
 
     PhaseArgs a{};
     a.T = d_base;
@@ -1365,10 +1364,13 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
                             : scan_rounds(as, swoff, rounds, tseg.p);
         }, a.Lmain);
       }
-      HIPCHK(ctx, launch_resolve(a, vb, s));
-      timed(ctx, "verify", 0, 0, nullptr, 0, [&] { return launch_verify(a, vb, a.Lmain, s); });
-      HIPCHK(ctx, launch_finish(a, vb, s));
-      HIPCHK(ctx, launch_retry(a, vb, s));
+      if (a.Lmain <= kSettleMax) {
+        timed(ctx, "verify", 0, 0, nullptr, 0, [&] { return launch_settle(a, vb, a.Lmain, s); });
+      } else {
+        HIPCHK(ctx, launch_resolve(a, vb, s));
+        timed(ctx, "verify", 0, 0, nullptr, 0, [&] { return launch_verify(a, vb, a.Lmain, s); });
+        HIPCHK(ctx, launch_finish(a, vb, s));
+      }
       if (a.pc) HIPCHK(ctx, launch_phase_record(a.pc, wst, vb, s));
     };
 

@@ -291,14 +291,17 @@ hipError_t launch_fold_filters(const PhaseArgs& a, const uint32_t* big, uint32_t
 // room for the filter and the queues in the CU's 160 KiB).
 constexpr uint32_t kTextFilterLdsLog2 = 15;
 
+// Phases of keys of at most this many bytes: resolved, verified and settled in
+// one launch (launch_settle); longer ones through a list (launch_resolve, _verify,
+// _finish).
+constexpr uint64_t kSettleMax = 4096;
 struct VerifyBufs {
   uint32_t* vlist;  // [c]
   uint64_t* vbest;  // [c]
-  uint32_t* vmis;   // [c]
-  uint32_t* rlist;  // [c]
-  uint64_t* rlb;    // [c]
-  uint64_t* counts; // [2]: verify count, retry count
+  uint32_t* vmis;   // [c] (longer keys only)
+  uint64_t* counts; // [2]: keys verified (profiling only in launch_settle), collisions
 };
+hipError_t launch_settle(const PhaseArgs& a, const VerifyBufs& v, uint64_t max_len, hipStream_t s);
 hipError_t launch_resolve(const PhaseArgs& a, const VerifyBufs& v, hipStream_t s);
 // Profiling: copy the phase's window count and verification counts into pc.
 hipError_t launch_phase_record(uint64_t* pc, const uint64_t* windows, const VerifyBufs& v,
@@ -306,7 +309,6 @@ hipError_t launch_phase_record(uint64_t* pc, const uint64_t* windows, const Veri
 hipError_t launch_verify(const PhaseArgs& a, const VerifyBufs& v, uint64_t max_len,
                          hipStream_t s);
 hipError_t launch_finish(const PhaseArgs& a, const VerifyBufs& v, hipStream_t s);
-hipError_t launch_retry(const PhaseArgs& a, const VerifyBufs& v, hipStream_t s);
 
 // The passes over a level's blocks (level_pass.hip).
 // Runs of a level: run ids, the run table, and the number of runs (or null).

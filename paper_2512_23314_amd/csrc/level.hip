@@ -961,11 +961,207 @@ hipError_t launch_byte_scan(const PhaseArgs& a, const uint64_t* woff, bool has_o
 }
 
 // ---------------------------------------------------------------- resolve / verify / retry
+//
+// A key whose slot minimum is its own position is its own leftmost occurrence;
+// any other compares its bytes with the slot's position (verification), and a
+// mismatch, a collision, sends it on an exact walk.
 
-// Keys whose slot minimum is their own position are their own leftmost
-// occurrence; the rest are appended to the verification list.  Returning
-// atomics on one address serialize (about 10 ns apart), so a 1024-thread
-// workgroup claims its whole share of the list with a single update.
+constexpr uint64_t kVChunk = kSettleMax;  // bytes compared per work item
+
+__global__ void k_phase_record(uint64_t* pc, const uint64_t* windows, const uint64_t* counts) {
+  if (threadIdx.x == 0) {
+    pc[kPcWindows] = windows ? *windows : 0;
+    pc[kPcVerified] = counts[0];
+    pc[kPcCollisions] = counts[1];
+  }
+}
+
+hipError_t launch_phase_record(uint64_t* pc, const uint64_t* windows, const VerifyBufs& v,
+                               hipStream_t s) {
+  k_phase_record<<<1, 64, 0, s>>>(pc, windows, v.counts);
+  return hipGetLastError();
+}
+
+// One wave compares up to 4 KiB of a key with the candidate occurrence.
+__device__ __forceinline__ bool wave_bytes_differ(const uint8_t* __restrict__ T, uint64_t a0,
+                                                  uint64_t b0, uint64_t off, uint64_t end) {
+  bool diff = false;
+  for (uint64_t o = off + (uint64_t)lane_id() * 16; o < end; o += 64 * 16) {
+    if (o + 16 <= end) {
+      const uint4 x = load16(T + a0 + o);
+      const uint4 y = load16(T + b0 + o);
+      diff |= (x.x != y.x) | (x.y != y.y) | (x.z != y.z) | (x.w != y.w);
+    } else {
+      for (uint64_t q = o; q < end; ++q) diff |= T[a0 + q] != T[b0 + q];
+    }
+  }
+  return __any(diff);
+}
+
+// Exact fallback after a collision: the wave walks positions lb, lb+1, ... up to
+// the start of key j, fingerprints each window, and verifies hits in increasing
+// order; the first verified hit is the leftmost occurrence (no true occurrence
+// lies before lb, see the file header of bt_host.cpp).  The key's own start
+// always verifies, so the walk ends.  Every lane returns it.
+__device__ uint64_t wave_walk(const PhaseArgs& a, uint64_t j, uint64_t lb) {
+  const int lane = lane_id();
+  const uint64_t pos = a.lv.st[j];
+  const uint64_t L = a.k.len[j];
+  const uint64_t fpk = a.k.fp[j];
+  const uint64_t salt = a.tx.tsalt[a.lv.text[j]];
+  const uint64_t xp = pow61(a.x, L);
+  for (uint64_t p0 = lb; p0 <= pos; p0 += 64) {
+    const uint64_t p = p0 + lane;
+    const bool m = p <= pos && finish_fp(win61_any(a, p, L, xp), salt, a.fpmask) == fpk;
+    uint64_t bal = __ballot(m);
+    while (bal) {
+      const uint64_t q = p0 + (uint64_t)(__ffsll((unsigned long long)bal) - 1);
+      bool diff = false;
+      for (uint64_t off = 0; off < L && !diff; off += kVChunk) {
+        const uint64_t end = L - off < kVChunk ? L : off + kVChunk;
+        diff = wave_bytes_differ(a.T, q, pos, off, end);
+      }
+      if (!diff) return q;
+      bal &= bal - 1;
+    }
+  }
+  return pos;
+}
+
+__device__ __forceinline__ uint64_t slot_best(const PhaseArgs& a, uint64_t j, uint32_t s) {
+  return s == kOddKey ? a.odd.best[a.lv.text[j]] : a.tab.slots[s].best;
+}
+
+// Keys of at most kVChunk bytes: resolved, verified and settled in one launch
+// (before, a list of the keys to verify, its verification and its results, each
+// writing and reading the list).  A wave takes 64 keys, one per lane; those
+// to verify are compared by groups of G lanes, 16 bytes per lane and step, 64 / G
+// keys at a time (G: about a key's 16-byte words, 64 for 1 KiB or more), four such
+// batches' first words loaded together.  Bound by the random lines it reads (slot,
+// occurrence, key).  Builds with one launch in place of three: 256 MiB 8.99 ->
+// 8.72 ms, 2 GiB 94.4 -> 91.9 ms, 1 MiB 2.22 -> 2.09 ms.  Walking in this kernel took
+// its registers from 79 to 104; held to 64 it spilled, and ran 1.5x slower.
+template <int G>
+__global__ __launch_bounds__(256) void k_settle(PhaseArgs a, VerifyBufs v) {
+  const int lane = lane_id();
+  const int sub = lane % G, grp = lane / G;
+  constexpr uint32_t per = 64 / G;
+  constexpr int kBatch = 4;
+  const uint64_t c = a.lv.c;
+  uint64_t verified = 0;
+  for (uint64_t j0 = ((uint64_t)blockIdx.x * 256 + (threadIdx.x & ~63u)); j0 < c;
+       j0 += (uint64_t)gridDim.x * 256) {
+    const uint64_t j = j0 + lane;
+    bool need = false, bad = false;
+    uint64_t best = 0, pos = 0;
+    uint32_t len = 0;
+    if (j < c) {
+      const uint32_t s = a.k.slot[j];
+      if (s != kNoKey && s != kCopyKey) {
+        pos = a.lv.st[j];
+        best = slot_best(a, j, s);
+        need = best != pos;
+        if (need) {
+          len = (uint32_t)a.k.len[j];
+          bad = best < a.tx.tstart[a.lv.text[j]];  // hit in another text: a collision
+        } else {
+          a.k.lm[j] = pos;
+        }
+      }
+    }
+    const uint64_t bal = __ballot(need && !bad);
+    const uint32_t n = (uint32_t)__popcll(bal);
+    const uint32_t rank = (uint32_t)__popcll(bal & ((1ull << lane) - 1));
+    verified += (uint64_t)__popcll(__ballot(need));
+    // lane k of `order` holds the lane of the k-th key to compare
+    const int order = __builtin_amdgcn_ds_permute((need && !bad ? (int)rank : 63) << 2, lane);
+    for (uint32_t k0 = 0; k0 < n; k0 += kBatch * per) {
+      // kBatch keys per group, their first 16 bytes per lane loaded together
+      uint64_t b0[kBatch], p0[kBatch];
+      uint32_t L[kBatch];
+      uint4 x[kBatch], y[kBatch];
+#pragma unroll
+      for (int e = 0; e < kBatch; ++e) {
+        const uint32_t k = k0 + e * per + grp;
+        const uint32_t src = (uint32_t)__shfl(order, (int)(k < n ? k : 0));
+        b0[e] = shfl64(best, src);
+        p0[e] = shfl64(pos, src);
+        L[e] = __shfl(len, (int)src);
+        if (k >= n) L[e] = 0;
+        if ((uint32_t)sub * 16 + 16 <= L[e]) {
+          x[e] = load16(a.T + b0[e] + sub * 16);
+          y[e] = load16(a.T + p0[e] + sub * 16);
+        } else {
+          x[e] = y[e] = make_uint4(0, 0, 0, 0);
+        }
+      }
+#pragma unroll
+      for (int e = 0; e < kBatch; ++e) {
+        bool diff = (x[e].x != y[e].x) | (x[e].y != y[e].y) | (x[e].z != y[e].z) | (x[e].w != y[e].w);
+        for (uint32_t o = (uint32_t)sub * 16 + ((uint32_t)sub * 16 + 16 <= L[e] ? G * 16 : 0); o < L[e];
+             o += G * 16) {
+          if (o + 16 <= L[e]) {
+            const uint4 u = load16(a.T + b0[e] + o);
+            const uint4 w = load16(a.T + p0[e] + o);
+            diff |= (u.x != w.x) | (u.y != w.y) | (u.z != w.z) | (u.w != w.w);
+          } else {
+            for (uint32_t q = o; q < L[e]; ++q) diff |= a.T[b0[e] + q] != a.T[p0[e] + q];
+          }
+        }
+        const uint64_t dm = __ballot(diff);
+        const uint32_t r0 = k0 + e * per;  // the ranks compared here: r0 .. r0 + per - 1
+        if (need && !bad && rank >= r0 && rank < r0 + per) {
+          const uint64_t mine = G == 64 ? ~0ull : ((1ull << (G & 63)) - 1) << ((rank - r0) * (G & 63));
+          if (dm & mine) bad = true;
+          else a.k.lm[j] = best;
+        }
+      }
+    }
+    if (bad) {  // rare: listed for k_walk, whose registers would halve this kernel's waves
+      const uint64_t at = atomicAdd((unsigned long long*)&v.counts[1], 1ull);
+      v.vlist[at] = (uint32_t)j;
+      v.vbest[at] = best;
+    }
+  }
+  if (a.pc) {  // profiling: one update per workgroup (they serialize)
+    __shared__ unsigned long long s_n;
+    if (threadIdx.x == 0) s_n = 0;
+    __syncthreads();
+    if (lane == 0 && verified) atomicAdd(&s_n, (unsigned long long)verified);
+    __syncthreads();
+    if (threadIdx.x == 0 && s_n) atomicAdd((unsigned long long*)&v.counts[0], s_n);
+  }
+}
+
+// The walks of the keys that failed (counts[1] of them listed), one wave each.
+__global__ __launch_bounds__(256) void k_walk(PhaseArgs a, VerifyBufs v) {
+  const uint64_t cnt = v.counts[1];
+  const uint64_t gw = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+  const uint64_t nw = ((uint64_t)gridDim.x * blockDim.x) >> 6;
+  for (uint64_t i = gw; i < cnt; i += nw) {
+    const uint64_t j = v.vlist[i], ts = a.tx.tstart[a.lv.text[j]], lb = v.vbest[i] + 1;
+    const uint64_t found = wave_walk(a, j, lb > ts ? lb : ts);
+    if (lane_id() == 0) a.k.lm[j] = found;
+  }
+}
+
+hipError_t launch_settle(const PhaseArgs& a, const VerifyBufs& v, uint64_t max_len, hipStream_t s) {
+  if (max_len > kVChunk) return hipErrorInvalidValue;
+  const unsigned g = grid_for(a.lv.c, 256, 8192);
+  // lanes per key: about one 16-byte word per lane, at least 4 lanes
+  if (max_len <= 64) k_settle<4><<<g, 256, 0, s>>>(a, v);
+  else if (max_len <= 128) k_settle<8><<<g, 256, 0, s>>>(a, v);
+  else if (max_len <= 256) k_settle<16><<<g, 256, 0, s>>>(a, v);
+  else if (max_len <= 512) k_settle<32><<<g, 256, 0, s>>>(a, v);
+  else k_settle<64><<<g, 256, 0, s>>>(a, v);
+  k_walk<<<grid_for(a.lv.c * 64, 256, 1024), 256, 0, s>>>(a, v);
+  return hipGetLastError();
+}
+
+// Longer keys: the ones to verify go to a list first, so that their bytes can be
+// shared out in chunks.  Returning atomics on one address serialize (about 10 ns
+// apart), so a 1024-thread workgroup claims its whole share of the list with a
+// single update.
 constexpr int kResolveThreads = 1024;
 
 __global__ __launch_bounds__(kResolveThreads) void k_resolve(PhaseArgs a, VerifyBufs v) {
@@ -983,7 +1179,7 @@ __global__ __launch_bounds__(kResolveThreads) void k_resolve(PhaseArgs a, Verify
       const uint32_t s = a.k.slot[j];
       if (s != kNoKey && s != kCopyKey) {
         const uint64_t pos = a.lv.st[j];
-        best = (s == kOddKey) ? a.odd.best[a.lv.text[j]] : a.tab.slots[s].best;
+        best = slot_best(a, j, s);
         if (best == pos) a.k.lm[j] = pos;
         else need = true;
       }
@@ -1016,176 +1212,58 @@ hipError_t launch_resolve(const PhaseArgs& a, const VerifyBufs& v, hipStream_t s
   return hipGetLastError();
 }
 
-__global__ void k_phase_record(uint64_t* pc, const uint64_t* windows, const uint64_t* counts) {
-  if (threadIdx.x == 0) {
-    pc[kPcWindows] = windows ? *windows : 0;
-    pc[kPcVerified] = counts[0];
-    pc[kPcCollisions] = counts[1];
-  }
-}
-
-hipError_t launch_phase_record(uint64_t* pc, const uint64_t* windows, const VerifyBufs& v,
-                               hipStream_t s) {
-  k_phase_record<<<1, 64, 0, s>>>(pc, windows, v.counts);
-  return hipGetLastError();
-}
-
-constexpr uint64_t kVChunk = 4096;  // bytes compared per work item
-
-// One wave compares up to 4 KiB of a key with the candidate occurrence.
-__device__ __forceinline__ bool wave_bytes_differ(const uint8_t* __restrict__ T, uint64_t a0,
-                                                  uint64_t b0, uint64_t off, uint64_t end) {
-  bool diff = false;
-  for (uint64_t o = off + (uint64_t)lane_id() * 16; o < end; o += 64 * 16) {
-    if (o + 16 <= end) {
-      const uint4 x = load16(T + a0 + o);
-      const uint4 y = load16(T + b0 + o);
-      diff |= (x.x != y.x) | (x.y != y.y) | (x.z != y.z) | (x.w != y.w);
-    } else {
-      for (uint64_t q = o; q < end; ++q) diff |= T[a0 + q] != T[b0 + q];
-    }
-  }
-  return __any(diff);
-}
-
-// Items are (key, 4 KiB chunk) pairs.  A group of G lanes (G = 64 for keys of
-// 1 KiB or more, fewer for short keys so that several keys share a wave)
-// compares one item, 16 bytes per lane per step.
-template <int G>
+// Items are (key, 4 KiB chunk) pairs; one wave compares one, 16 bytes per lane
+// per step.
 __global__ __launch_bounds__(256) void k_verify(PhaseArgs a, VerifyBufs v, uint64_t cpk) {
-  const uint64_t cnt = v.counts[0];
-  const uint64_t items = cnt * cpk;
-  const int lane = lane_id();
-  const int sub = lane % G;
-  const uint64_t ggrp = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) / G;
-  const uint64_t ngrp = ((uint64_t)gridDim.x * blockDim.x) / G;
-  // every lane of a wave runs the same number of iterations (the group
-  // reduction below is a wave-wide ballot)
-  const uint64_t iters = (items + ngrp - 1) / ngrp;
-  for (uint64_t k = 0; k < iters; ++k) {
-    const uint64_t it = ggrp + k * ngrp;
-    bool diff = false;
-    bool mine = false;
-    uint64_t idx = 0;
-    if (it < items) {
-      idx = it / cpk;
-      const uint64_t chunk = it - idx * cpk;
-      const uint32_t j = v.vlist[idx];
-      const uint64_t best = v.vbest[idx];
-      const uint64_t pos = a.lv.st[j];
-      const uint64_t L = a.k.len[j];
-      if (best < a.tx.tstart[a.lv.text[j]]) {  // hit in another text: a collision
-        diff = true;
-        mine = true;
-      } else {
-        const uint64_t off = chunk * kVChunk;
-        if (off < L) {
-          mine = true;
-          const uint64_t end = L - off < kVChunk ? L : off + kVChunk;
-          for (uint64_t o = off + (uint64_t)sub * 16; o < end; o += (uint64_t)G * 16) {
-            if (o + 16 <= end) {
-              const uint4 x = load16(a.T + best + o);
-              const uint4 y = load16(a.T + pos + o);
-              diff |= (x.x != y.x) | (x.y != y.y) | (x.z != y.z) | (x.w != y.w);
-            } else {
-              for (uint64_t q = o; q < end; ++q) diff |= a.T[best + q] != a.T[pos + q];
-            }
-          }
-        }
-      }
-    }
-    const uint64_t bal = __ballot(diff);
-    const uint64_t gmask = (G == 64) ? ~0ull : (((1ull << G) - 1) << (lane - sub));
-    if (mine && sub == 0 && (bal & gmask)) v.vmis[idx] = 1;
+  const uint64_t items = v.counts[0] * cpk;
+  const uint64_t gw = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+  const uint64_t nw = ((uint64_t)gridDim.x * blockDim.x) >> 6;
+  for (uint64_t it = gw; it < items; it += nw) {
+    const uint64_t idx = it / cpk;
+    const uint64_t off = (it - idx * cpk) * kVChunk;
+    const uint32_t j = v.vlist[idx];
+    const uint64_t best = v.vbest[idx];
+    const uint64_t L = a.k.len[j];
+    bool diff;
+    if (best < a.tx.tstart[a.lv.text[j]]) diff = true;  // hit in another text: a collision
+    else if (off >= L) continue;
+    else diff = wave_bytes_differ(a.T, best, a.lv.st[j], off, L - off < kVChunk ? L : off + kVChunk);
+    if (diff && lane_id() == 0) v.vmis[idx] = 1;
   }
 }
 
 hipError_t launch_verify(const PhaseArgs& a, const VerifyBufs& v, uint64_t max_len,
                          hipStream_t s) {
-  const uint64_t cpk = max_len ? (max_len + kVChunk - 1) / kVChunk : 1;
-  const uint64_t items = a.lv.c * cpk;
-  // lanes per item: about one 16-byte word per lane, at least 4 lanes
-  if (max_len <= 64) {
-    k_verify<4><<<grid_for(items * 4, 256, 2048), 256, 0, s>>>(a, v, cpk);
-  } else if (max_len <= 128) {
-    k_verify<8><<<grid_for(items * 8, 256, 2048), 256, 0, s>>>(a, v, cpk);
-  } else if (max_len <= 256) {
-    k_verify<16><<<grid_for(items * 16, 256, 2048), 256, 0, s>>>(a, v, cpk);
-  } else if (max_len <= 512) {
-    k_verify<32><<<grid_for(items * 32, 256, 2048), 256, 0, s>>>(a, v, cpk);
-  } else {
-    k_verify<64><<<grid_for(items * 64, 256, 2048), 256, 0, s>>>(a, v, cpk);
-  }
+  const uint64_t cpk = (max_len + kVChunk - 1) / kVChunk;
+  k_verify<<<grid_for(a.lv.c * cpk * 64, 256, 2048), 256, 0, s>>>(a, v, cpk);
   return hipGetLastError();
 }
 
-__global__ void k_finish(PhaseArgs a, VerifyBufs v) {
+// The list's results: a wave takes 64 keys, one per lane, and walks for each of
+// those that failed in turn.
+__global__ __launch_bounds__(256) void k_finish(PhaseArgs a, VerifyBufs v) {
   const uint64_t cnt = v.counts[0];
-  GRID_STRIDE(idx, cnt) {
-    const uint32_t j = v.vlist[idx];
-    if (v.vmis[idx]) {
-      const uint64_t r = atomicAdd((unsigned long long*)&v.counts[1], 1ull);
-      const uint64_t ts = a.tx.tstart[a.lv.text[j]];
-      const uint64_t lb = v.vbest[idx] + 1;
-      v.rlist[r] = j;
-      v.rlb[r] = lb > ts ? lb : ts;
-    } else {
-      a.k.lm[j] = v.vbest[idx];
+  for (uint64_t i0 = ((uint64_t)blockIdx.x * 256 + (threadIdx.x & ~63u)); i0 < cnt;
+       i0 += (uint64_t)gridDim.x * 256) {
+    const uint64_t idx = i0 + lane_id();
+    bool bad = false;
+    if (idx < cnt) {
+      bad = v.vmis[idx] != 0;
+      if (!bad) a.k.lm[v.vlist[idx]] = v.vbest[idx];
+    }
+    uint64_t m = __ballot(bad);
+    if (m && lane_id() == 0) atomicAdd((unsigned long long*)&v.counts[1], (unsigned long long)__popcll(m));
+    for (; m; m &= m - 1) {
+      const uint64_t i = i0 + (uint64_t)__ffsll((unsigned long long)m) - 1;
+      const uint64_t j = v.vlist[i], ts = a.tx.tstart[a.lv.text[j]], lb = v.vbest[i] + 1;
+      const uint64_t found = wave_walk(a, j, lb > ts ? lb : ts);
+      if (lane_id() == 0) a.k.lm[j] = found;
     }
   }
 }
 
 hipError_t launch_finish(const PhaseArgs& a, const VerifyBufs& v, hipStream_t s) {
   k_finish<<<grid_for(a.lv.c, 256), 256, 0, s>>>(a, v);
-  return hipGetLastError();
-}
-
-// Exact fallback after a collision: one wave per key walks positions
-// lb, lb+1, ... up to the key's own start, fingerprints each window, and
-// verifies hits in increasing order; the first verified hit is the leftmost
-// occurrence (no true occurrence lies before lb, see the file header of
-// bt_host.cpp).  The key's own start always verifies, so the walk ends.
-__global__ __launch_bounds__(256) void k_retry(PhaseArgs a, VerifyBufs v) {
-  const uint64_t cnt = v.counts[1];
-  const uint64_t gw = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-  const uint64_t nw = ((uint64_t)gridDim.x * blockDim.x) >> 6;
-  const int lane = lane_id();
-  for (uint64_t idx = gw; idx < cnt; idx += nw) {
-    const uint32_t j = v.rlist[idx];
-    const uint64_t lb = v.rlb[idx];
-    const uint64_t pos = a.lv.st[j];
-    const uint64_t L = a.k.len[j];
-    const uint64_t fpk = a.k.fp[j];
-    const uint64_t salt = a.tx.tsalt[a.lv.text[j]];
-    const uint64_t xp = pow61(a.x, L);
-    uint64_t found = pos;
-    bool done = false;
-    for (uint64_t p0 = lb; p0 <= pos && !done; p0 += 64) {
-      const uint64_t p = p0 + lane;
-      const bool m = p <= pos && finish_fp(win61_any(a, p, L, xp), salt, a.fpmask) == fpk;
-      uint64_t bal = __ballot(m);
-      while (bal) {
-        const uint64_t q = p0 + (uint64_t)(__ffsll((unsigned long long)bal) - 1);
-        bool diff = false;
-        for (uint64_t off = 0; off < L && !diff; off += kVChunk) {
-          const uint64_t end = L - off < kVChunk ? L : off + kVChunk;
-          diff = wave_bytes_differ(a.T, q, pos, off, end);
-        }
-        if (!diff) {
-          found = q;
-          done = true;
-          break;
-        }
-        bal &= bal - 1;
-      }
-    }
-    if (lane == 0) a.k.lm[j] = found;
-  }
-}
-
-hipError_t launch_retry(const PhaseArgs& a, const VerifyBufs& v, hipStream_t s) {
-  const unsigned grid = grid_for(a.lv.c * 64, 256, 1024);
-  k_retry<<<grid, 256, 0, s>>>(a, v);
   return hipGetLastError();
 }
 
