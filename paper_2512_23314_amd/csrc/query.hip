@@ -23,71 +23,97 @@ static unsigned grid_for(uint64_t n, unsigned threads, unsigned cap = 8192) {
   for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < (n); \
        i += (uint64_t)gridDim.x * blockDim.x)
 
-__device__ __forceinline__ uint64_t marks_before(const QLevel& L, uint64_t j) {
-  const uint64_t w = L.words[j >> 6];
-  const uint64_t below = (j & 63) ? (w << (64 - (j & 63))) : 0;
-  return L.wrank[j >> 6] + __popcll(below);
-}
-__device__ __forceinline__ bool is_marked(const QLevel& L, uint64_t j) {
-  return (L.words[j >> 6] >> (j & 63)) & 1;
+// Queries are chains of dependent loads, one or two per level, so what they cost
+// is latency times the length of the chain.  The level table is read at every
+// step, by lanes on different levels: it lies in LDS.  Block lengths are mostly
+// powers of two, where a shift replaces a 64-bit division.  Measured on a 64 MiB
+// text of 96 symbols, 2^20 queries: access 82 -> 61 us, rank 337 -> 185 us, select
+// 535 -> 469 us (which is bound by the lines it reads, about 100 per query).
+constexpr uint32_t kMaxLevels = 64;  // block lengths are leaf tau^k < 2^64
+
+__device__ __forceinline__ void load_levels(const QTree& q, QLevel* s_lv) {
+  static_assert(sizeof(QLevel) % 8 == 0, "copied as words");
+  const uint64_t* src = reinterpret_cast<const uint64_t*>(q.lv);
+  uint64_t* dst = reinterpret_cast<uint64_t*>(s_lv);
+  for (uint32_t k = threadIdx.x; k < q.h * (sizeof(QLevel) / 8); k += blockDim.x) dst[k] = src[k];
+  __syncthreads();
 }
 
-// Descend from level 0 to the leaf holding text position i.  Returns the leaf
-// index and the offset inside it.  Calls on_ptr(level, j, u, t, off, o) at every
-// pointer that is followed (for rank's counter adjustments).
-template <typename F>
-__device__ __forceinline__ void descend(const QTree& q, uint64_t i, uint64_t& leaf, uint64_t& off,
-                                        F&& on_ptr) {
-  const QLevel* lv = q.lv;
-  uint64_t j = i / lv[0].b;
-  uint64_t o = i - j * lv[0].b;
-  uint32_t l = 0;
-  while (l + 1 < q.h) {
-    const QLevel L = lv[l];
-    const uint64_t r1 = marks_before(L, j);
-    if (is_marked(L, j)) {
-      const uint64_t bn = lv[l + 1].b;
-      const uint64_t k = o / bn;
-      j = r1 * q.tau + k;
-      o -= k * bn;
-      ++l;
-    } else {
-      const uint64_t u = j - r1;
-      uint64_t t = L.pb[u];
-      uint64_t o2 = L.po[u] + o;
-      on_ptr(l, j, u, t, L.po[u], o);
-      if (o2 >= L.b) {
-        o2 -= L.b;
-        ++t;
-      }
-      j = t;
-      o = o2;
-    }
+// x / b, and the remainder in x
+__device__ __forceinline__ uint64_t take_div(uint64_t& x, uint64_t b) {
+  if ((b & (b - 1)) == 0) {
+    const uint64_t k = x >> (63 - __builtin_clzll(b));
+    x &= b - 1;
+    return k;
   }
-  leaf = j;
-  off = o;
+  const uint64_t k = x / b;
+  x -= k * b;
+  return k;
+}
+
+// Marks before block j of a level, and whether j is marked.
+struct Mark {
+  uint64_t before;
+  bool marked;
+};
+__device__ __forceinline__ Mark mark_at(const QLevel& L, uint64_t j) {
+  const uint64_t w = L.words[j >> 6], r = L.wrank[j >> 6];
+  const uint32_t k = (uint32_t)j & 63;
+  return {r + __popcll(w & ((1ull << k) - 1)), ((w >> k) & 1) != 0};
 }
 
 __global__ void k_access(QTree q, const uint64_t* __restrict__ pos, uint64_t m,
                          uint8_t* __restrict__ out, uint32_t* bad) {
+  __shared__ QLevel lv[kMaxLevels];
+  load_levels(q, lv);
   GRID_STRIDE(k, m) {
-    const uint64_t i = pos[k];
-    if (i >= q.n) {
+    uint64_t o = pos[k];
+    if (o >= q.n) {
       out[k] = 0;
       *bad = 1;
       continue;
     }
-    uint64_t leaf, o;
-    descend(q, i, leaf, o, [](uint32_t, uint64_t, uint64_t, uint64_t, uint64_t, uint64_t) {});
-    out[k] = q.leaves[leaf * q.leaf_len + o];
+    uint64_t j = take_div(o, lv[0].b);
+    uint32_t l = 0;
+    while (l + 1 < q.h) {
+      const QLevel& L = lv[l];
+      const Mark mk = mark_at(L, j);
+      if (mk.marked) {
+        ++l;
+        j = mk.before * q.tau + take_div(o, lv[l].b);
+      } else {
+        const uint64_t u = j - mk.before;
+        j = L.pb[u];
+        o += L.po[u];
+        if (o >= L.b) {
+          o -= L.b;
+          ++j;
+        }
+      }
+    }
+    out[k] = q.leaves[j * q.leaf_len + o];
   }
 }
 
 hipError_t launch_access(QTree t, const uint64_t* pos, uint64_t m, uint8_t* out, uint32_t* bad,
                          hipStream_t s) {
   if (!m) return hipSuccess;
+  if (t.h > kMaxLevels) return hipErrorInvalidValue;
   k_access<<<grid_for(m, 256), 256, 0, s>>>(t, pos, m, out, bad);
   return hipGetLastError();
+}
+
+// The top bit of each byte of w that equals ch (exact: no carry crosses bytes).
+__device__ __forceinline__ uint64_t equal_bytes(uint64_t w, uint8_t ch) {
+  const uint64_t x = w ^ (0x0101010101010101ull * ch), low = 0x7F7F7F7F7F7F7F7Full;
+  return ~(((x & low) + low) | x | low);
+}
+
+// Eight bytes of a leaf (unaligned).
+__device__ __forceinline__ uint64_t leaf_word(const uint8_t* p) {
+  uint64_t w;
+  __builtin_memcpy(&w, p, 8);
+  return w;
 }
 
 // Counter of width w at index idx.
@@ -97,32 +123,46 @@ __device__ __forceinline__ uint64_t narrow_at(const uint8_t* p, uint32_t w, uint
                          : reinterpret_cast<const uint32_t*>(p)[idx];
 }
 
-// R (occurrences of symbol s before block x of level l, from the text's
-// start): relative counts up the parents to the nearest absolute level.
-__device__ uint64_t block_count(const QTree& q, uint32_t l, uint64_t x, uint32_t s) {
-  uint64_t r = 0;
-  while (!q.lv[l].acnt) {
-    const QLevel& L = q.lv[l];
-    r += narrow_at(L.qc, L.qw, x * q.S + s);
-    x = q.lv[l - 1].msel[x / q.tau];
+// Occurrences of symbol s between the starts of a marked block and of its child
+// x, where j0 is its first child (which starts where it does), on level N.
+__device__ __forceinline__ uint64_t child_count(const QLevel& N, uint64_t j0, uint64_t x, uint32_t S,
+                                                uint32_t s) {
+  if (N.acnt) return N.acnt[(j0 + x) * S + s] - N.acnt[j0 * S + s];
+  return narrow_at(N.qc, N.qw, (j0 + x) * S + s);
+}
+
+// Occurrences of symbol s in block t of level l, whose right neighbour t + 1
+// starts where it ends.  Counts relative to the parent give it where both have
+// one parent; else t is the last child of its parent and t + 1 the first of the
+// next one, and the parent's count less what lies before t is left (one more
+// level in one of tau cases).  A tree's first levels hold absolute counts.
+__device__ uint64_t block_occ(const QTree& q, const QLevel* lv, uint32_t l, uint64_t t, uint32_t s) {
+  int64_t sub = 0;
+  while (true) {
+    const QLevel& L = lv[l];
+    if (L.acnt) return (uint64_t)(L.acnt[(t + 1) * q.S + s] - L.acnt[t * q.S + s] - sub);
+    const uint64_t mine = narrow_at(L.qc, L.qw, t * q.S + s);
+    const uint64_t p = t / q.tau;
+    if ((t + 1) / q.tau == p) return narrow_at(L.qc, L.qw, (t + 1) * q.S + s) - mine - sub;
+    sub += mine;
+    t = lv[l - 1].msel[p];
     --l;
   }
-  return r + q.lv[l].acnt[x * q.S + s];
 }
 
-// R of block jc of level l1 whose parent has R = rp.
-__device__ __forceinline__ uint64_t child_count(const QTree& q, uint32_t l1, uint64_t jc, uint32_t s,
-                                                uint64_t rp) {
-  const QLevel& N = q.lv[l1];
-  return N.acnt ? N.acnt[jc * q.S + s] : rp + narrow_at(N.qc, N.qw, jc * q.S + s);
-}
-
-// rank(c, i): the walk of access, carrying R of the current block.  Every
-// pointer followed from block j (unmarked number u, target t) adds
-// R[j] - (R[t] + P[u]), the count before block j minus the count before the
-// source position; at the leaf, R of the leaf and the bytes before the offset.
+// rank(c, i): the walk of access.  Let D be the count before the current block
+// plus what the pointers followed have shifted it by, so that the answer is D
+// plus the occurrences in the current block before the offset.  Moving to child
+// x adds the occurrences between the two starts; following a pointer of block j
+// to offset off of block t replaces "before block j" by "before the source", which
+// lies P[u] occurrences into t: D - P[u] is the new D, whatever the counts of j
+// and t are.  Spilling into t + 1 adds the occurrences in t.  (Carrying the
+// absolute counts of j and t instead took a climb to the nearest absolute level
+// at every pointer.)
 __global__ void k_rank(QTree q, const uint8_t* __restrict__ cs, const uint64_t* __restrict__ pos,
                        uint64_t m, uint64_t* __restrict__ out) {
+  __shared__ QLevel lv[kMaxLevels];
+  load_levels(q, lv);
   const uint32_t S = q.S;
   GRID_STRIDE(k, m) {
     const uint64_t i = pos[k];
@@ -140,62 +180,56 @@ __global__ void k_rank(QTree q, const uint8_t* __restrict__ cs, const uint64_t* 
       out[k] = q.total[s];
       continue;
     }
-    const QLevel* lv = q.lv;
-    uint64_t j = i / lv[0].b;
-    uint64_t o = i - j * lv[0].b;
-    uint64_t R = lv[0].acnt[j * S + s];
-    int64_t acc = 0;
+    uint64_t o = i;
+    uint64_t j = take_div(o, lv[0].b);
+    int64_t D = lv[0].acnt[j * S + s];
     uint32_t l = 0;
     while (l + 1 < q.h) {
       const QLevel& L = lv[l];
-      const uint64_t r1 = marks_before(L, j);
-      if (is_marked(L, j)) {
-        const uint64_t bn = lv[l + 1].b;
-        const uint64_t x = o / bn;
-        j = r1 * q.tau + x;
-        o -= x * bn;
-        ++l;
-        R = child_count(q, l, j, s, R);
+      const Mark mk = mark_at(L, j);
+      if (mk.marked) {
+        const QLevel& N = lv[++l];
+        const uint64_t j0 = mk.before * q.tau, x = take_div(o, N.b);
+        if (x) D += (int64_t)child_count(N, j0, x, S, s);
+        j = j0 + x;
       } else {
-        const uint64_t u = j - r1;
-        uint64_t t = L.pb[u];
-        uint64_t o2 = L.po[u] + o;
-        const uint64_t Rt = block_count(q, l, t, s);
-        acc += (int64_t)R - (int64_t)(Rt + narrow_at(L.pc, L.pw, u * S + s));
-        if (o2 >= L.b) {
-          o2 -= L.b;
-          ++t;
-          R = block_count(q, l, t, s);
-        } else {
-          R = Rt;
+        const uint64_t u = j - mk.before;
+        D -= (int64_t)narrow_at(L.pc, L.pw, u * S + s);
+        j = L.pb[u];
+        o += L.po[u];
+        if (o >= L.b) {
+          o -= L.b;
+          D += (int64_t)block_occ(q, lv, l, j, s);
+          ++j;
         }
-        j = t;
-        o = o2;
       }
     }
-    acc += (int64_t)R;
     const uint8_t* lb = q.leaves + j * q.leaf_len;
-    for (uint64_t r = 0; r < o; ++r) acc += lb[r] == ch;
-    out[k] = (uint64_t)acc;
+    uint64_t r = 0;
+    for (; r + 8 <= o; r += 8) D += __popcll(equal_bytes(leaf_word(lb + r), ch));
+    for (; r < o; ++r) D += lb[r] == ch;
+    out[k] = (uint64_t)D;
   }
 }
 
 hipError_t launch_rank(QTree t, const uint8_t* cs, const uint64_t* pos, uint64_t m, uint64_t* out,
                        hipStream_t s) {
   if (!m) return hipSuccess;
+  if (t.h > kMaxLevels) return hipErrorInvalidValue;
   k_rank<<<grid_for(m, 256), 256, 0, s>>>(t, cs, pos, m, out);
   return hipGetLastError();
 }
 
-// select(c, k): keep the invariant R[j] < k <= R[j] + (occurrences in block
-// j), carrying R of the current block.  Level 1: binary search over the blocks.
-// Marked block: the last child whose count is below k.  Unmarked block j with
-// pointer (t, off): the wanted occurrence is the (k - R[j])-th inside the block,
-// i.e. occurrence k' = R[t] + P[u] + (k - R[j]) of the source, which lies in
-// block t or t+1; the answer moves by (start of j) - (source position).  At the
-// leaf, scan its bytes.
+// select(c, k): the wanted occurrence is the k-th inside the current block.
+// Level 1: binary search over the blocks.  Marked block: the last child with
+// fewer than k occurrences before it.  Unmarked block with pointer (t, off): the
+// (P[u] + k)-th of block t, or, past t's occurrences, one of block t + 1; the
+// answer moves by (start of the block) - (source position).  At the leaf, scan
+// its bytes.
 __global__ void k_select(QTree q, const uint8_t* __restrict__ cs, const uint64_t* __restrict__ ks,
                          uint64_t m, uint64_t* __restrict__ out) {
+  __shared__ QLevel lv[kMaxLevels];
+  load_levels(q, lv);
   const uint32_t S = q.S;
   GRID_STRIDE(qi, m) {
     const uint8_t ch = cs[qi];
@@ -205,62 +239,73 @@ __global__ void k_select(QTree q, const uint8_t* __restrict__ cs, const uint64_t
       out[qi] = ~0ull;
       continue;
     }
-    const QLevel* lv = q.lv;
     uint64_t lo = 0, hi = lv[0].c;
     while (hi - lo > 1) {
       const uint64_t mid = (lo + hi) >> 1;
       if (lv[0].acnt[mid * S + s] < k) lo = mid; else hi = mid;
     }
     uint64_t j = lo;
-    uint64_t R = lv[0].acnt[j * S + s];
+    k -= lv[0].acnt[j * S + s];
     uint32_t l = 0;
     uint64_t shift = 0;
     while (l + 1 < q.h) {
       const QLevel& L = lv[l];
-      const uint64_t r1 = marks_before(L, j);
-      if (is_marked(L, j)) {
-        const QLevel& N = lv[l + 1];
-        const uint64_t j0 = r1 * q.tau;
+      const Mark mk = mark_at(L, j);
+      if (mk.marked) {
+        const QLevel& N = lv[++l];
+        const uint64_t j0 = mk.before * q.tau;
         uint64_t nch = N.c - j0;
         if (nch > q.tau) nch = q.tau;
-        // the first child starts where its parent does: its R is the parent's
-        uint64_t x = 1, Rx = R;
+        uint64_t x = 1, before = 0;
+        // four children at a time: their counts leave together
         while (x < nch) {
-          const uint64_t Rn = child_count(q, l + 1, j0 + x, s, R);
-          if (Rn >= k) break;
-          Rx = Rn;
-          ++x;
+          uint64_t v[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) v[e] = x + e < nch ? child_count(N, j0, x + e, S, s) : ~0ull;
+          int e = 0;
+#pragma unroll
+          for (int g = 0; g < 4; ++g)
+            if (e == g && v[g] < k) {
+              before = v[g];
+              e = g + 1;
+            }
+          x += e;
+          if (e < 4) break;
         }
         j = j0 + x - 1;
-        R = Rx;
-        ++l;
+        k -= before;
       } else {
-        const uint64_t u = j - r1;
+        const uint64_t u = j - mk.before;
         const uint64_t t = L.pb[u];
-        const uint64_t src = L.st[t] + L.po[u];
-        const uint64_t Rt = block_count(q, l, t, s);
-        const uint64_t k2 = Rt + narrow_at(L.pc, L.pw, u * S + s) + (k - R);
-        shift += L.st[j] - src;
-        uint64_t nt = t, Rn = Rt;
-        if (t + 1 < L.c && L.st[t + 1] == L.st[t] + L.b) {
-          const uint64_t R1 = block_count(q, l, t + 1, s);
-          if (R1 < k2) {
-            nt = t + 1;
-            Rn = R1;
+        const uint64_t off = L.po[u], sj = L.st[j];
+        k += narrow_at(L.pc, L.pw, u * S + s);
+        const uint64_t st = L.st[t];
+        // (a source that starts with t ends with it)
+        const bool next = off && t + 1 < L.c && L.st[t + 1] == st + L.b;
+        shift += sj - (st + off);
+        j = t;
+        if (next) {
+          const uint64_t occ = block_occ(q, lv, l, t, s);
+          if (occ < k) {
+            k -= occ;
+            j = t + 1;
           }
         }
-        j = nt;
-        k = k2;
-        R = Rn;
       }
     }
     const QLevel& LH = lv[q.h - 1];
-    uint64_t need = k - R;
+    uint64_t need = k;
     const uint8_t* lb = q.leaves + j * q.leaf_len;
     uint64_t res = ~0ull;
     const uint64_t rest = q.tstart + q.n - LH.st[j];
     const uint64_t llen = rest < q.leaf_len ? rest : q.leaf_len;
-    for (uint64_t o = 0; o < llen; ++o) {
+    uint64_t o = 0;
+    for (; o + 8 <= llen; o += 8) {  // the word that holds it
+      const uint32_t n = (uint32_t)__popcll(equal_bytes(leaf_word(lb + o), ch));
+      if (n >= need) break;
+      need -= n;
+    }
+    for (; o < llen; ++o) {
       if (lb[o] == ch && --need == 0) {
         res = LH.st[j] + o + shift - q.tstart;
         break;
@@ -273,6 +318,7 @@ __global__ void k_select(QTree q, const uint8_t* __restrict__ cs, const uint64_t
 hipError_t launch_select(QTree t, const uint8_t* cs, const uint64_t* ks, uint64_t m, uint64_t* out,
                          hipStream_t s) {
   if (!m) return hipSuccess;
+  if (t.h > kMaxLevels) return hipErrorInvalidValue;
   k_select<<<grid_for(m, 256), 256, 0, s>>>(t, cs, ks, m, out);
   return hipGetLastError();
 }
