@@ -1088,7 +1088,8 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
                   seg_woff = alloc<uint64_t>(ctx, nseg + 1);
     Buf<uint32_t> seg_text = alloc<uint32_t>(ctx, nseg);
     const SegDev sg{E_ent, ent_a.p, ent_e.p, ent_f.p, ent_child.p};
-    const SegOut so{seg_ws.p, seg_re.p, seg_text.p, seg_woff.p, segn.p};
+    SegOut so{seg_ws.p, seg_re.p, seg_text.p, seg_woff.p, segn.p, nullptr};
+    Buf<uint32_t> tseg;
     Buf<uint8_t> facts = alloc<uint8_t>(ctx, c);
     Buf<uint32_t> vlist = alloc<uint32_t>(ctx, c),
                   vmis = alloc<uint32_t>(ctx, 2 * b > kSettleMax ? c : 0);
@@ -1258,7 +1259,8 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
       if (rounds.size() > 1) kh32 = alloc<uint32_t>(ctx, c);
       a.k.h32 = kh32.p;
       const auto scan_rounds = [&](const PhaseArgs& as, const uint64_t* swoff,
-                                   const std::vector<uint32_t>& ends, uint32_t* tseg) {
+                                   const std::vector<uint32_t>& ends, uint32_t* tseg,
+                                   bool find_segs) {
         uint32_t from = 0;
         for (uint32_t to : ends) {
           if (from) {
@@ -1270,7 +1272,7 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
             if (e != hipSuccess) return e;
           }
           const hipError_t e = launch_probe_scan(as, swoff, has_odd, has_salt, c * b, scan_mode,
-                                                 tseg, from, to, s);
+                                                 tseg, from, to, find_segs, s);
           if (e != hipSuccess) return e;
           from = to;
         }
@@ -1300,6 +1302,12 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
       uint64_t* swoff = seg_woff.p;
       uint64_t* wst = wstats.p + 2 * step + (phase - 1);
       uint64_t* wcount = ctx->profile ? wst : nullptr;  // windows, for the kernel statistics
+      // with many segments, the tiles' segments beforehand
+      const bool tile_segs = !text_local && !byte_scan && scan_mode == 1 && !lean &&
+                             (phase == 1 ? E_ent : c) >= kTileSegsMin;
+      const bool piece_segs = tile_segs && (phase == 1 ? b * prm.tau : b) <= kTileSegsPiece * kProbeTile;
+      if (tile_segs && !tseg.p) tseg = alloc<uint32_t>(ctx, c * b / kProbeTile + 2);
+      so.tseg = piece_segs ? tseg.p : nullptr;
       if (phase == 1) HIPCHK(ctx, launch_entry_segs(a, sg, so, wcount, next_scan(E_ent), s));
       else HIPCHK(ctx, launch_block_segs(a, facts.p, so, wcount, next_scan(c), s));
       // algorithmic bytes per window: the two prefix values it reads (8-byte
@@ -1348,10 +1356,6 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
         span_chunks = std::min<uint64_t>(256, std::max<uint64_t>(16, span_chunks & ~15ull));
         if (ctx->tune.span_chunks) span_chunks = ctx->tune.span_chunks;
         Buf<uint64_t> span_info;
-        // with many segments, the tiles' segments from a pass of their own
-        Buf<uint32_t> tseg;
-        if (!text_local && scan_mode == 1 && !lean && (phase == 1 ? E_ent : c) >= kTileSegsMin)
-          tseg = alloc<uint32_t>(ctx, c * b / kProbeTile + 2);
         if (text_local) {
           span_info = alloc<uint64_t>(ctx, 3 * probe_text_spans(c * b, span_chunks));
           HIPCHK(ctx, launch_span_info(as, swoff, c * b, span_chunks, span_info.p, s));
@@ -1361,7 +1365,7 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
           // earlier) are short against a tile at the lowest levels
           return text_local ? launch_probe_text(as, swoff, has_odd, c * b, span_chunks, span_ctr.p,
                                                 span_info.p, phase == 2 && b <= 64, s)
-                            : scan_rounds(as, swoff, rounds, tseg.p);
+                            : scan_rounds(as, swoff, rounds, tile_segs ? tseg.p : nullptr, !piece_segs);
         }, a.Lmain);
       }
       if (a.Lmain <= kSettleMax) {

@@ -190,6 +190,7 @@ struct SegOut {
   uint32_t* stext;  // text
   uint64_t* woff;   // windows before each segment, the total after the last
   uint64_t* segn;   // {segments, windows}
+  uint32_t* tseg;   // the segment of each scan tile's first window, or null
 };
 
 hipError_t launch_fill_u64(uint64_t* p, uint64_t v, uint64_t n, hipStream_t s);
@@ -252,8 +253,11 @@ hipError_t launch_sort_groups(const PhaseArgs& a, const uint64_t* fp, const uint
 hipError_t launch_byte_scan(const PhaseArgs& a, const uint64_t* woff, bool has_odd, bool has_salt,
                             uint64_t max_windows, hipStream_t s);
 // From this many segments on (a search of eight dependent loads) a dense scan
-// gets its tiles' segments from a launch before it.
+// gets its tiles' segments beforehand: from the segment pass where a piece (an
+// entry, a block) spans at most kTileSegsPiece tiles, which one thread writes,
+// else from a launch of its own (find_segs), one thread per tile.
 constexpr uint64_t kTileSegsMin = 256;
+constexpr uint64_t kTileSegsPiece = 32;
 // The sliding-window probe.  max_windows bounds the grid; mode 1: LDS key filter
 // on 32-bit hashes and per-wave candidate queues (dense or sampled hashes),
 // 2: LDS key filter on 61-bit fingerprints, inline probe.  tseg: null, or one
@@ -262,7 +266,7 @@ constexpr uint64_t kTileSegsMin = 256;
 // Queued scans may go in rounds: [f0, f1) are 64ths of the tiles (0, 64: all).
 hipError_t launch_probe_scan(const PhaseArgs& a, const uint64_t* woff, bool has_odd,
                              bool has_salt, uint64_t max_windows, int mode, uint32_t* tseg,
-                             uint32_t f0, uint32_t f1, hipStream_t s);
+                             uint32_t f0, uint32_t f1, bool find_segs, hipStream_t s);
 // Between rounds (filters cleared by the caller): sets the filter bits of the
 // keys that windows from tile 64ths f0 on can still improve.
 hipError_t launch_refilter(const PhaseArgs& a, const uint64_t* woff, uint32_t f0, hipStream_t s);

@@ -158,37 +158,42 @@ struct BlockPieces {
 template <class Pieces>
 struct SegPass {
   Pieces src;
-  uint64_t *ws, *sre, *woff, *segn, *wst;
-  uint32_t* stext;
+  SegOut o;
+  uint64_t* wst;
   __device__ void value(uint64_t k, uint64_t* v) const {
     const SegPiece p = src.piece(k);
     v[0] = p.cnt;
     v[1] = p.cnt && !(k > 0 && src.joins(src.piece(k - 1), p)) ? 1 : 0;
   }
   __device__ void apply(uint64_t k, const uint64_t* ex, const uint64_t* v) const {
+    if (o.tseg && v[0]) {
+      // tiles whose first window is one of this piece's
+      const uint32_t g = (uint32_t)(ex[1] + v[1] - 1);
+      for (uint64_t t = (ex[0] + kProbeTile - 1) / kProbeTile; t * kProbeTile < ex[0] + v[0]; ++t) o.tseg[t] = g;
+    }
     if (!v[1]) return;
     const SegPiece p = src.piece(k);
     const uint64_t g = ex[1];
-    woff[g] = ex[0];
-    ws[g] = p.lo;
-    sre[g] = p.re;
-    stext[g] = p.t;
+    o.woff[g] = ex[0];
+    o.ws[g] = p.lo;
+    o.sre[g] = p.re;
+    o.stext[g] = p.t;
   }
   __device__ void total(const uint64_t* sum) const {
-    segn[0] = sum[1];
-    segn[1] = sum[0];
-    woff[sum[1]] = sum[0];
+    o.segn[0] = sum[1];
+    o.segn[1] = sum[0];
+    o.woff[sum[1]] = sum[0];
     if (wst) *wst = sum[0];
   }
 };
 
 __global__ __launch_bounds__(kPassThreads) void k_entry_segs(PhaseArgs a, SegDev sg, SegOut o,
                                                              uint64_t* wst, ScanDev sd) {
-  scan_pass<2, 2u>(sg.E, sd, SegPass<EntryPieces>{{a, sg}, o.ws, o.sre, o.woff, o.segn, wst, o.stext});
+  scan_pass<2, 2u>(sg.E, sd, SegPass<EntryPieces>{{a, sg}, o, wst});
 }
 __global__ __launch_bounds__(kPassThreads) void k_block_segs(PhaseArgs a, const uint8_t* pf, SegOut o,
                                                              uint64_t* wst, ScanDev sd) {
-  scan_pass<2, 2u>(a.lv.c, sd, SegPass<BlockPieces>{{a, pf}, o.ws, o.sre, o.woff, o.segn, wst, o.stext});
+  scan_pass<2, 2u>(a.lv.c, sd, SegPass<BlockPieces>{{a, pf}, o, wst});
 }
 
 hipError_t launch_entry_segs(const PhaseArgs& a, const SegDev& sg, const SegOut& o, uint64_t* wst,
