@@ -1183,7 +1183,8 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
       a.xLmain = host_pow61(x, a.Lmain);
       // LDS filter: 32 bits per key or more, at most 2^19 bits (64 KiB; 2^20 in
       // scans of dense hashes, which run one workgroup per CU), two bits per key
-      // while there are at least 8 bits per key.  The scan tests the
+      // while there are at least 3 bits per key (at 4, 17% of windows pass in
+      // place of 22%).  The scan tests the
       // 32-bit pre-filter hash and queues its candidates (mode 1); from 2^14
       // keys on, where the LDS filter starts to pass a sizeable share of the
       // windows, those also test a blocked second filter in global memory of
@@ -1240,7 +1241,7 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
       a.tf_fold = text_local ? tf_fold.p : nullptr;
       a.tf_fold_off = text_local ? tf_fold_off : nullptr;
       a.filt_bits = fbits;
-      a.filt_two = fbits && 8 * nkeys <= (1ull << fbits);
+      a.filt_two = fbits && 3 * nkeys <= (1ull << fbits);
       a.pre32 = !byte_scan && scan_mode == 1;
       a.filt2_words = f2words;
       a.bfilt = byte_scan ? filt.p : nullptr;

@@ -78,40 +78,51 @@ __device__ __forceinline__ uint64_t filter_bit2(uint64_t fp, uint32_t bits) {
   return ((fp >> 17) ^ (fp >> 41) ^ (fp * 0x9E3779B1ull >> 20)) & ((1ull << bits) - 1);
 }
 
-// A 32-bit window hash (mod 2^32 polynomial hash, whose high bits depend on
-// every byte) in a filter of 2^bits bits (12..20): its word from the top bits
-// and one or two bits of that word from the ten below, so that a test is one
-// LDS read and no multiplication.
+// Filters of 32-bit window hashes (mod 2^32 polynomial hashes, whose high bits
+// depend on every byte).  All are blocked: a key's bits lie in one word, so a test
+// is one load.  The scans test every window and are bound by the instructions that
+// takes (four cycles per wave and SIMD each, four times that for a 32-bit
+// multiplication), so a test takes the word by a shift and reads its bits by
+// shifting it: no mask, no compare, one multiplication at most.  Scans of 2^31
+// windows with 2^15 to 2^19 keys: L = 2^17 2.71 -> 2.26 ms, L = 2^15 2.83 -> 2.47.
+// (32-bit words in the second filter ran those at 2.15 and 2.28 but passed more
+// windows where it is full: L = 512 with 7 M keys 13.7 -> 15.1 ms.)
+
+// The LDS filter of 2^bits bits (12..20): the word from the top bits of the hash,
+// one or two bits of it from the ten below.
 __device__ __forceinline__ uint32_t filter32_word(uint32_t h, uint32_t bits) {
   return h >> (37 - bits);
 }
 __device__ __forceinline__ uint32_t filter32_mask(uint32_t h, uint32_t bits, bool two) {
-  const uint32_t u = h << (bits - 5);
-  return (1u << (u >> 27)) | (two ? 1u << ((u >> 22) & 31) : 0u);
+  return (1u << ((h >> (32 - bits)) & 31)) | (two ? 1u << ((h >> (27 - bits)) & 31) : 0u);
+}
+// bit 0: the word has the hash's bits (s1 = 32 - bits; s2 = 27 - bits, or s1)
+__device__ __forceinline__ uint32_t filter32_has(uint32_t w, uint32_t h, uint32_t s1, uint32_t s2) {
+  return (w >> ((h >> s1) & 31)) & (w >> ((h >> s2) & 31)) & 1u;
 }
 
-// Second (global, L2-resident) filter of a 32-bit window hash: blocked, three
-// bits in one 64-bit word, so that a test is one load.  The word and the bit
-// positions come from multiplicative hashes with their own odd constants,
-// unrelated to the bits the LDS filter takes.  words_log2 = log2(64-bit words).
-__device__ __forceinline__ uint32_t filter2_word(uint32_t h, uint32_t words_log2) {
-  return (h * 0x6F4F2A35u) >> (32 - words_log2);
+// The second (global, L2-resident) filter, 64-bit words, and the text-local ones
+// (batches), 32-bit words: three bits per key.  p = the hash times an odd constant
+// of the filter's own; the word from the top bits of p, two of its bits from the
+// lowest ones and the third from the top of the hash itself (further bits of p
+// would overlap the word's, and leave keys of one word a few places for that bit).
+// words_log2 >= 3.
+__device__ __forceinline__ uint32_t filter2_hash(uint32_t h) { return h * 0x6F4F2A35u; }
+__device__ __forceinline__ uint32_t tfilter_hash(uint32_t h) { return h * 0x7FEB352Du; }
+__device__ __forceinline__ uint32_t block_word(uint32_t p, uint32_t words_log2) {
+  return p >> (32 - words_log2);
 }
-__device__ __forceinline__ uint64_t filter2_mask(uint32_t h) {
-  const uint32_t m = h * 0xD35A2D97u;
-  return (1ull << (m >> 26)) | (1ull << ((m >> 20) & 63)) | (1ull << ((m >> 14) & 63));
+__device__ __forceinline__ uint64_t filter2_mask(uint32_t p, uint32_t h) {
+  return (1ull << (p & 63)) | (1ull << ((p >> 6) & 63)) | (1ull << (h >> 26));
 }
-
-// Text-local filter of a 32-bit window hash (batches): blocked, three bits in
-// one 32-bit word, so that a test is one 4-byte load.  words_log2 (>= 3) =
-// log2(32-bit words); word and bits come from multiplicative hashes with their
-// own odd constants.
-__device__ __forceinline__ uint32_t tfilter_word(uint32_t h, uint32_t words_log2) {
-  return (h * 0x7FEB352Du) >> (32 - words_log2);
+__device__ __forceinline__ uint32_t filter2_has(uint64_t w, uint32_t p, uint32_t h) {  // bit 0
+  return (uint32_t)(w >> (p & 63)) & (uint32_t)(w >> ((p >> 6) & 63)) & (uint32_t)(w >> (h >> 26)) & 1u;
 }
-__device__ __forceinline__ uint32_t tfilter_mask(uint32_t h) {
-  const uint32_t m = h * 0x846CA68Bu;
-  return (1u << (m >> 27)) | (1u << ((m >> 22) & 31)) | (1u << ((m >> 17) & 31));
+__device__ __forceinline__ uint32_t tfilter_mask(uint32_t p, uint32_t h) {
+  return (1u << (p & 31)) | (1u << ((p >> 5) & 31)) | (1u << (h >> 27));
+}
+__device__ __forceinline__ uint32_t tfilter_has(uint32_t w, uint32_t p, uint32_t h) {  // bit 0
+  return (w >> (p & 31)) & (w >> ((p >> 5) & 31)) & (w >> (h >> 27)) & 1u;
 }
 
 // Filter bit of a string's first eight bytes (lo = bytes 0..3, hi = bytes

@@ -153,7 +153,7 @@ struct PhaseArgs {
   uint32_t bfilt_bits;
   // Text-local filters (batches, with pre32): per text t, a blocked filter of
   // its keys' 32-bit hashes, 2^tf_wl[t] 32-bit words at tf_words + tf_off[t],
-  // three bits of one word per key (tfilter_word, tfilter_mask).  Null when off.
+  // three bits of one word per key (tfilter_hash, block_word, tfilter_mask).  Null when off.
   uint32_t* tf_words;
   const uint64_t* tf_off;  // [T]
   const uint32_t* tf_wl;   // [T], at least 3

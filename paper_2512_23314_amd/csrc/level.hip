@@ -119,16 +119,19 @@ __global__ void k_keys(PhaseArgs a) {
       if (a.tf_words) {
         // text-local filter: this text's keys only
         const uint32_t h = win32_any(a, st, L, a.x32L) + (uint32_t)a.tx.tsalt[t];
-        atomicOr(a.tf_words + a.tf_off[t] + tfilter_word(h, a.tf_wl[t]), tfilter_mask(h));
+        const uint32_t p = tfilter_hash(h);
+        atomicOr(a.tf_words + a.tf_off[t] + block_word(p, a.tf_wl[t]), tfilter_mask(p, h));
       }
       if (a.filt_bits) {
         if (a.pre32) {
           const uint32_t h = win32_any(a, st, L, a.x32L) + (uint32_t)a.tx.tsalt[t];
           if (a.k.h32) a.k.h32[j] = h;
           atomicOr(&a.filt[filter32_word(h, a.filt_bits)], filter32_mask(h, a.filt_bits, a.filt_two));
-          if (a.filt2_words)
-            atomicOr(reinterpret_cast<unsigned long long*>(a.filt2) + filter2_word(h, a.filt2_words),
-                     (unsigned long long)filter2_mask(h));
+          if (a.filt2_words) {
+            const uint32_t p = filter2_hash(h);
+            atomicOr(reinterpret_cast<unsigned long long*>(a.filt2) + block_word(p, a.filt2_words),
+                     (unsigned long long)filter2_mask(p, h));
+          }
         } else {
           const uint64_t f1 = filter_bit(fp, a.filt_bits), f2 = filter_bit2(fp, a.filt_bits);
           atomicOr(&a.filt[f1 >> 5], 1u << (f1 & 31));
@@ -281,9 +284,11 @@ __global__ void k_refilter(PhaseArgs a, const uint64_t* __restrict__ woff, uint3
     if (a.tab.slots[s].best < from) continue;
     const uint32_t h = a.k.h32[j];
     atomicOr(&a.filt[filter32_word(h, a.filt_bits)], filter32_mask(h, a.filt_bits, a.filt_two));
-    if (a.filt2_words)
-      atomicOr(reinterpret_cast<unsigned long long*>(a.filt2) + filter2_word(h, a.filt2_words),
-               (unsigned long long)filter2_mask(h));
+    if (a.filt2_words) {
+      const uint32_t p = filter2_hash(h);
+      atomicOr(reinterpret_cast<unsigned long long*>(a.filt2) + block_word(p, a.filt2_words),
+               (unsigned long long)filter2_mask(p, h));
+    }
   }
 }
 
@@ -351,13 +356,23 @@ void k_probe_dense(PhaseArgs a, const uint64_t* __restrict__ woff, uint32_t f0, 
   const uint32_t x32L = a.x32L;
   const uint64_t* __restrict__ filt2 = reinterpret_cast<const uint64_t*>(a.filt2);
   const uint32_t f2words = a.filt2_words;
-  const auto pass32 = [&](uint32_t h) {
-    const uint32_t m = filter32_mask(h, fbits, two);
-    return (s_filt[filter32_word(h, fbits)] & m) == m;
-  };
+  const uint32_t s1 = 32 - fbits, s2 = two ? 27 - fbits : s1;
+  const auto pass32 = [&](uint32_t h) { return filter32_has(s_filt[filter32_word(h, fbits)], h, s1, s2); };
   const auto pass2 = [&](uint32_t h) {
-    const uint64_t m = filter2_mask(h);
-    return (filt2[filter2_word(h, f2words)] & m) == m;
+    const uint32_t p = filter2_hash(h);
+    return filter2_has(filt2[block_word(p, f2words)], p, h);
+  };
+  // the second filter for the steps in okm, their loads issued together
+  const auto second = [&](auto& hv, uint32_t okm) {
+    constexpr int K = sizeof(hv) / sizeof(hv[0]);
+    uint64_t wv[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+      wv[k] = (okm >> k) & 1 ? filt2[block_word(filter2_hash(hv[k]), f2words)] : 0ull;
+    uint32_t m = 0;
+#pragma unroll
+    for (int k = 0; k < K; ++k) m |= filter2_has(wv[k], filter2_hash(hv[k]), hv[k]) << k;
+    return m;
   };
 
   // the text t's short final key, if any: its length, its position, and the
@@ -442,22 +457,11 @@ void k_probe_dense(PhaseArgs a, const uint64_t* __restrict__ woff, uint32_t f0, 
         for (int k = 0; k < kScanK; ++k) {
           hv[k] = hb[k] - ha[k] * x32L + s32;
           hp[k] = hb[k];
-          okm |= pass32(hv[k]) ? 1u << k : 0u;
+          okm |= pass32(hv[k]) << k;
         }
         next = ib + L;
         if (!__ballot(okm != 0)) continue;
-        if (f2words) {
-          // second filter: the steps' loads are issued together
-          uint64_t wv[kScanK];
-#pragma unroll
-          for (int k = 0; k < kScanK; ++k)
-            wv[k] = (okm >> k) & 1 ? filt2[filter2_word(hv[k], f2words)] : 0ull;
-#pragma unroll
-          for (int k = 0; k < kScanK; ++k) {
-            const uint64_t m = filter2_mask(hv[k]);
-            if ((wv[k] & m) != m) okm &= ~(1u << k);
-          }
-        }
+        if (f2words) okm = second(hv, okm);
         // as many rounds as the lane with the most candidates has
         while (__ballot(okm != 0)) {
           queue.push(okm != 0, i0 + 64ull * (okm ? __builtin_ctz(okm) : 0), t);
@@ -534,20 +538,10 @@ void k_probe_dense(PhaseArgs a, const uint64_t* __restrict__ woff, uint32_t f0, 
 #pragma unroll
           for (int k = 0; k < kScanSlowGroup; ++k) {
             hv[k] = hb[k] - ha[k] * x32L;
-            okm |= ((vm >> k) & 1) && pass32(hv[k]) ? 1u << k : 0u;
+            okm |= (pass32(hv[k]) & (vm >> k)) << k;
           }
           if (!__ballot(okm != 0)) continue;
-          if (f2words) {
-            uint64_t wv[kScanSlowGroup];
-#pragma unroll
-            for (int k = 0; k < kScanSlowGroup; ++k)
-              wv[k] = (okm >> k) & 1 ? filt2[filter2_word(hv[k], f2words)] : 0ull;
-#pragma unroll
-            for (int k = 0; k < kScanSlowGroup; ++k) {
-              const uint64_t m = filter2_mask(hv[k]);
-              if ((wv[k] & m) != m) okm &= ~(1u << k);
-            }
-          }
+          if (f2words) okm = second(hv, okm);
 #pragma unroll
           for (int k = 0; k < kScanSlowGroup; ++k) queue.push((okm >> k) & 1, ik[k], 0);
         }
@@ -616,28 +610,23 @@ void k_probe_scan(PhaseArgs a, const uint64_t* __restrict__ woff, uint32_t f0, u
   if constexpr (LEAN) {
     ProbeQueue<SALT> queue(a, s_lds + (1ull << (fbits - 6)) + (uint64_t)(threadIdx.x >> 6) * kQueue);
     const uint64_t* __restrict__ filt2 = reinterpret_cast<const uint64_t*>(a.filt2);
+    const uint32_t s1 = 32 - fbits, s2 = two ? 27 - fbits : s1;
     const uint32_t f2words = a.filt2_words;
-    const auto pass32 = [&](uint32_t h) {
-      const uint32_t m = filter32_mask(h, fbits, two);
-      return (s_filt[filter32_word(h, fbits)] & m) == m;
-    };
+    const auto pass32 = [&](uint32_t h) { return filter32_has(s_filt[filter32_word(h, fbits)], h, s1, s2) != 0; };
     const auto test8 = [&](const uint32_t* hv, bool* ok) {
 #pragma unroll
       for (int k = 0; k < 8; ++k) ok[k] = pass32(hv[k]);
       if (f2words) {
         uint64_t wv[8];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) wv[k] = ok[k] ? filt2[filter2_word(hv[k], f2words)] : ~0ull;
+        for (int k = 0; k < 8; ++k) wv[k] = ok[k] ? filt2[block_word(filter2_hash(hv[k]), f2words)] : 0ull;
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-          const uint64_t m = filter2_mask(hv[k]);
-          ok[k] = ok[k] && (wv[k] & m) == m;
-        }
+        for (int k = 0; k < 8; ++k) ok[k] = filter2_has(wv[k], filter2_hash(hv[k]), hv[k]) != 0;
       }
     };
     const auto test1 = [&](uint32_t h) {
-      const uint64_t m = filter2_mask(h);
-      return pass32(h) && (!f2words || (filt2[filter2_word(h, f2words)] & m) == m);
+      const uint32_t p = filter2_hash(h);
+      return pass32(h) && (!f2words || filter2_has(filt2[block_word(p, f2words)], p, h));
     };
     const auto push = [&](bool cand, uint64_t i, uint32_t t) { queue.push(cand, i, t); };
     const uint64_t t1 = round_tile(W, f1);

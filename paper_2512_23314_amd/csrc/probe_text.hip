@@ -125,7 +125,8 @@ void k_probe_text(PhaseArgs a, const uint64_t* __restrict__ woff, uint64_t span_
       }
     };
     const auto pass_word = [&](uint32_t h) -> uint32_t {
-      return LDS ? s_filt[tfilter_word(h, lwl)] : tfw[toff + tfilter_word(h, twl)];
+      const uint32_t p = tfilter_hash(h);
+      return LDS ? s_filt[block_word(p, lwl)] : tfw[toff + block_word(p, twl)];
     };
     const auto test8 = [&](const uint32_t* hv, bool* ok) {
       uint32_t wv[8];
@@ -133,23 +134,21 @@ void k_probe_text(PhaseArgs a, const uint64_t* __restrict__ woff, uint64_t span_
       for (int k = 0; k < 8; ++k) wv[k] = pass_word(hv[k]);
 #pragma unroll
       for (int k = 0; k < 8; ++k) {
-        const uint32_t m = tfilter_mask(hv[k]);
-        ok[k] = (wv[k] & m) == m;
+        ok[k] = tfilter_has(wv[k], tfilter_hash(hv[k]), hv[k]) != 0;
       }
       if (LDS && big) {
 #pragma unroll
-        for (int k = 0; k < 8; ++k) wv[k] = ok[k] ? tfw[toff + tfilter_word(hv[k], twl)] : 0u;
+        for (int k = 0; k < 8; ++k) wv[k] = ok[k] ? tfw[toff + block_word(tfilter_hash(hv[k]), twl)] : 0u;
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
-          const uint32_t m = tfilter_mask(hv[k]);
-          ok[k] = ok[k] && (wv[k] & m) == m;
+          ok[k] = ok[k] && tfilter_has(wv[k], tfilter_hash(hv[k]), hv[k]) != 0;
         }
       }
     };
     const auto test1 = [&](uint32_t h) {
-      const uint32_t m = tfilter_mask(h);
-      bool c = (pass_word(h) & m) == m;
-      if (LDS && big && c) c = (tfw[toff + tfilter_word(h, twl)] & m) == m;
+      const uint32_t p = tfilter_hash(h);
+      bool c = tfilter_has(pass_word(h), p, h) != 0;
+      if (LDS && big && c) c = tfilter_has(tfw[toff + block_word(p, twl)], p, h) != 0;
       return c;
     };
     lean_chunk<ODD, true, true>(a, woff, span_r0, span_r1 + 1, W,
@@ -177,7 +176,8 @@ void k_probe_text(PhaseArgs a, const uint64_t* __restrict__ woff, uint64_t span_
     uint64_t toff = tfo[LDS ? st : t];
     uint32_t twl = tfl[LDS ? st : t];
     const auto pass_word = [&](uint32_t h) -> uint32_t {
-      return LDS ? s_filt[tfilter_word(h, lwl)] : tfw[toff + tfilter_word(h, twl)];
+      const uint32_t p = tfilter_hash(h);
+      return LDS ? s_filt[block_word(p, lwl)] : tfw[toff + block_word(p, twl)];
     };
     // the text's short final key, if any (kept in registers while t holds):
     // its length, the length, hash and power of its anchor
@@ -252,17 +252,15 @@ void k_probe_text(PhaseArgs a, const uint64_t* __restrict__ woff, uint64_t span_
           bool ok[kTlGroup];
 #pragma unroll
           for (int k = 0; k < kTlGroup; ++k) {
-            const uint32_t m = tfilter_mask(hv[k]);
-            ok[k] = (wv[k] & m) == m;
+            ok[k] = tfilter_has(wv[k], tfilter_hash(hv[k]), hv[k]) != 0;
           }
           if (LDS && big) {
             // passed the folded filter: the full one, the loads issued together
 #pragma unroll
-            for (int k = 0; k < kTlGroup; ++k) wv[k] = ok[k] ? tfw[toff + tfilter_word(hv[k], twl)] : 0u;
+            for (int k = 0; k < kTlGroup; ++k) wv[k] = ok[k] ? tfw[toff + block_word(tfilter_hash(hv[k]), twl)] : 0u;
 #pragma unroll
             for (int k = 0; k < kTlGroup; ++k) {
-              const uint32_t m = tfilter_mask(hv[k]);
-              ok[k] = ok[k] && (wv[k] & m) == m;
+              ok[k] = ok[k] && tfilter_has(wv[k], tfilter_hash(hv[k]), hv[k]) != 0;
             }
           }
 #pragma unroll
@@ -366,16 +364,14 @@ void k_probe_text(PhaseArgs a, const uint64_t* __restrict__ woff, uint64_t span_
         }
 #pragma unroll
         for (int k = 0; k < kTlSlowGroup; ++k) {
-          const uint32_t m = tfilter_mask(hv[k]);
-          ok[k] = ((vm >> k) & 1) && (wv[k] & m) == m;
+          ok[k] = ((vm >> k) & 1) && tfilter_has(wv[k], tfilter_hash(hv[k]), hv[k]) != 0;
         }
         if (big) {
 #pragma unroll
-          for (int k = 0; k < kTlSlowGroup; ++k) wv[k] = ok[k] ? tfw[toff + tfilter_word(hv[k], twl)] : 0u;
+          for (int k = 0; k < kTlSlowGroup; ++k) wv[k] = ok[k] ? tfw[toff + block_word(tfilter_hash(hv[k]), twl)] : 0u;
 #pragma unroll
           for (int k = 0; k < kTlSlowGroup; ++k) {
-            const uint32_t m = tfilter_mask(hv[k]);
-            ok[k] = ok[k] && (wv[k] & m) == m;
+            ok[k] = ok[k] && tfilter_has(wv[k], tfilter_hash(hv[k]), hv[k]) != 0;
           }
         }
 #pragma unroll
@@ -408,9 +404,9 @@ void k_probe_text(PhaseArgs a, const uint64_t* __restrict__ woff, uint64_t span_
       bool cand = false;
       if (live && i + L <= re) {
         const uint32_t h = H[i + L] - H[i] * x32L + (uint32_t)salt;
-        const uint32_t m = tfilter_mask(h);
-        cand = (pass_word(h) & m) == m;
-        if (LDS && big && cand) cand = (tfw[toff + tfilter_word(h, twl)] & m) == m;
+        const uint32_t p = tfilter_hash(h);
+        cand = tfilter_has(pass_word(h), p, h) != 0;
+        if (LDS && big && cand) cand = tfilter_has(tfw[toff + block_word(p, twl)], p, h) != 0;
       }
       push(cand, i, t);
       // the short key: its anchor's hash first (equal strings always agree),
