@@ -869,7 +869,7 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
       pass_tickets = pass_epoch = 0;
     }
     ScanDev sd{pass_words.p, pass_tiles, pass_words.p + 3 * pass_tiles, pass_tickets, ++pass_epoch};
-    pass_tickets += tiles;
+    if (tiles > 1) pass_tickets += tiles;
     return sd;
   };
   // pinned words the level's counts are written to (k_texts)
@@ -932,21 +932,20 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
                          Buf<uint64_t>& spb, Buf<uint64_t>& spo, uint64_t u,
                          const std::vector<uint64_t>& tcount, const std::vector<uint64_t>& tfirst,
                          const std::vector<uint64_t>& tu, const uint64_t* d_tf,
-                         const uint64_t* d_tc, const uint64_t* d_wo) {
+                         const uint64_t* d_tc, Buf<uint64_t> words, Buf<uint64_t> wrank) {
     std::vector<uint64_t> h_woff(T + 1, 0), h_poff(T + 1, 0);
     for (uint32_t t = 0; t < T; ++t) {
       h_woff[t + 1] = h_woff[t] + (tcount[t] + 63) / 64;
       h_poff[t + 1] = h_poff[t] + tu[t];
     }
     const uint64_t nwords = h_woff[T];
-    Buf<uint64_t> up_woff;  // word offsets per text, when not on the device yet
-    if (!d_wo) {
-      up_woff = alloc<uint64_t>(ctx, T + 1);
-      upload(ctx, up_woff.p, h_woff.data(), T + 1);
-      d_wo = up_woff.p;
+    if (!words.p) {  // (pruned builds: the others' marks are stored by the split)
+      Buf<uint64_t> d_wo = alloc<uint64_t>(ctx, T + 1);
+      upload(ctx, d_wo.p, h_woff.data(), T + 1);
+      words = alloc<uint64_t>(ctx, nwords);
+      wrank = alloc<uint64_t>(ctx, nwords + 1);
+      HIPCHK(ctx, launch_store_marks(marked, StoreMarks{T, uoff, d_tf, d_tc, d_wo.p, nwords, words.p, wrank.p}, s));
     }
-    Buf<uint64_t> words = alloc<uint64_t>(ctx, nwords), wrank = alloc<uint64_t>(ctx, nwords + 1);
-    HIPCHK(ctx, launch_store_marks(marked, uoff, T, d_tf, d_tc, d_wo, nwords, words.p, wrank.p, s));
     LevelBufs LB;
     LB.words = store->add(std::move(words), nwords);
     LB.wrank = store->add(std::move(wrank), nwords + 1);
@@ -1013,7 +1012,11 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
   };
   std::vector<PruneLevel> pl(prune ? H : 0);
 
-  const auto alloc_next = [&](uint64_t cn, uint64_t En, Buf<uint64_t>& nst, Buf<uint32_t>& ntext) {
+  // (one text's runs are written with its blocks, except for the leaf level)
+  Buf<uint32_t> run, rtext;
+  Buf<uint64_t> rs, re;
+  const auto alloc_next = [&](uint64_t cn, uint64_t En, Buf<uint64_t>& nst, Buf<uint32_t>& ntext,
+                              bool leaf) {
     nst = alloc<uint64_t>(ctx, cn);
     ntext = alloc<uint32_t>(ctx, cn);
     cflag = alloc<uint8_t>(ctx, cn);
@@ -1021,13 +1024,139 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
     ent_e = alloc<uint64_t>(ctx, En);
     ent_child = alloc<uint64_t>(ctx, En);
     ent_f = alloc<uint8_t>(ctx, En);
-    return NextLevel{nst.p, ntext.p, cflag.p, ent_a.p, ent_e.p, ent_f.p, ent_child.p};
+    NextLevel nl{nst.p, ntext.p, cflag.p, ent_a.p, ent_e.p, ent_f.p, ent_child.p,
+                 nullptr, nullptr, nullptr, nullptr};
+    // the run table is sized by c, which bounds any run count
+    if (!leaf) {
+      run = alloc<uint32_t>(ctx, cn);
+      rs = alloc<uint64_t>(ctx, cn);
+      re = alloc<uint64_t>(ctx, cn);
+      rtext = alloc<uint32_t>(ctx, cn);
+      if (T == 1) {
+        nl.run = run.p;
+        nl.rs = rs.p;
+        nl.re = re.p;
+        nl.rtext = rtext.p;
+      }
+    }
+    return nl;
   };
+
+  // Scratch of a level that its phases find cleared: the key table, the short
+  // keys, the verification counts, the key filters.  The kernel before each phase
+  // clears it (the split of the level above, or a launch for the first level; the
+  // marks before phase 2), to sizes that bound either phase's by the blocks.
+  const bool can_queue = T <= (1u << 24) && offs[T] < (1ull << 40) &&
+                         !(prm.debug_flags & BT_DBG_NO_QUEUE);
+  // bits of the LDS filter, log2: 32 per key or more (128 where the scan is long
+  // against the filter's copying), at most 2^19 (64 KiB), or 2^20 in scans of
+  // dense hashes, which run one workgroup per CU
+  const auto filter_bits = [&](uint64_t c, uint64_t b, uint64_t nkeys) {
+    if (!can_queue) return 19u;
+    const uint64_t per_key = !lean && c * b >= (1ull << 26) ? 128 : 32;
+    uint32_t bits = 12;
+    while (bits < (lean ? 19u : 20u) && (1ull << bits) < per_key * nkeys) ++bits;
+    return bits;
+  };
+  // 64-bit words of the second filter, log2: about 32 bits per key, from 2^14 keys
+  const auto filter2_words = [&](uint64_t nkeys) {
+    uint32_t w = 0;
+    if (can_queue && nkeys >= (1ull << 14)) {
+      w = 10;
+      while (w < ctx->tune.filter2_max_log2 - 6 && (64ull << w) < 32 * nkeys) ++w;
+    }
+    return w;
+  };
+  // bits of the byte scan's filter, log2: at least 2048 per key (chance passes
+  // below 1/2048 of windows); every workgroup copies the filter into LDS
+  const auto byte_bits = [](uint64_t nkeys) {
+    uint32_t bits = 12;
+    while (bits < 19 && (1ull << bits) < 2048 * nkeys) ++bits;
+    return bits;
+  };
+  constexpr uint64_t kByteKeys = 128;
+  struct LevelScratch {
+    uint64_t cap = 0;
+    Buf<Slot> tab;
+    Buf<uint64_t> oddb, vcnt;
+    Buf<uint32_t> filt, filt2;
+    // Text-local filters (batches): per text, 2^wl 32-bit words with wl the
+    // least >= 3 such that each of the text's blocks (a bound on its keys in
+    // either phase) has a word.  One layout serves both phases.
+    // A text whose filter is larger than LDS also gets a folded copy of LDS
+    // size (tf_fold), built after the keys.
+    Buf<uint64_t> tf_off, span_ctr;
+    Buf<uint32_t> tf_words, tf_fold;
+    const uint64_t* tf_fold_off = nullptr;
+    uint32_t *tf_wl = nullptr, *tf_big = nullptr;
+    uint64_t tf_total = 0;
+    uint32_t nbig = 0;
+    FillList fill;
+  };
+  const auto make_scratch = [&](uint64_t c, uint64_t b, const std::vector<uint64_t>& tcount) {
+    LevelScratch q;
+    q.cap = std::max<uint64_t>(1024, pow2_at_least(c << ctx->tune.table_load_log2));
+    q.tab = alloc<Slot>(ctx, q.cap);
+    q.oddb = alloc<uint64_t>(ctx, 8 * (uint64_t)T);
+    q.vcnt = alloc<uint64_t>(ctx, 2);
+    const uint32_t bits = std::max(filter_bits(c, b, c), byte_bits(std::min(c, kByteKeys)));
+    q.filt = alloc<uint32_t>(ctx, (1ull << bits) / 32);
+    if (has_salt && c && !(prm.debug_flags & (BT_DBG_SHARED_FILTERS | BT_DBG_SORT_PHASES))) {
+      // one upload: filter offsets and folded ones (u64), log2 sizes (u32), the
+      // texts with a folded filter (u32)
+      std::vector<uint64_t> up(3 * (uint64_t)T + 1, 0);
+      uint64_t *h_off = up.data(), *h_foff = h_off + T;
+      uint32_t *h_wl = reinterpret_cast<uint32_t*>(h_foff + T), *h_big = h_wl + T;
+      const uint32_t tf_lds = kTextFilterLdsLog2;
+      for (uint32_t t = 0; t < T; ++t) {
+        uint32_t wl = 3;
+        // 2^(bits_log2 - 5) words of 32 bits per block
+        const uint32_t bl = ctx->tune.text_filter_bits_log2;
+        const uint64_t need = bl >= 5 ? tcount[t] << (bl - 5) : (tcount[t] + 1) >> (5 - bl);
+        while ((1ull << wl) < need) ++wl;
+        h_wl[t] = wl;
+        h_off[t] = q.tf_total;
+        q.tf_total += 1ull << wl;
+        if (wl > tf_lds) {
+          h_foff[t] = (uint64_t)q.nbig << tf_lds;
+          h_big[q.nbig++] = t;
+        }
+      }
+      q.tf_words = alloc<uint32_t>(ctx, q.tf_total);
+      q.tf_off = alloc<uint64_t>(ctx, up.size());
+      q.tf_fold_off = q.tf_off.p + T;
+      q.tf_wl = reinterpret_cast<uint32_t*>(q.tf_off.p + 2 * (uint64_t)T);
+      q.tf_big = q.tf_wl + T;
+      upload(ctx, q.tf_off.p, up.data(), up.size());
+      if (q.nbig) q.tf_fold = alloc<uint32_t>(ctx, (uint64_t)q.nbig << tf_lds);
+      q.span_ctr = alloc<uint64_t>(ctx, 1);
+    }
+    q.fill.add(q.tab.p, 4 * q.cap, ~0u);  // empty slots: fp = best = ~0
+    q.fill.add(q.oddb.p, 16 * (uint64_t)T, 0);
+    q.fill.add(q.vcnt.p, 4, 0);
+    q.fill.add(q.filt.p, (1ull << bits) / 32, 0);
+    const uint32_t w2 = q.tf_total ? 0 : filter2_words(c);
+    if (w2) {
+      q.filt2 = alloc<uint32_t>(ctx, 2ull << w2);
+      q.fill.add(q.filt2.p, 2ull << w2, 0);
+    }
+    if (q.tf_total) {
+      q.fill.add(q.tf_words.p, q.tf_total, 0);
+      q.fill.add(q.span_ctr.p, 2, 0);
+    }
+    return q;
+  };
+
   c = h_tfirst[T];
   E_ent = id_first[1];
+  LevelScratch scr;
   {
-    const NextLevel nl = alloc_next(c, E_ent, st, text);
+    const NextLevel nl = alloc_next(c, E_ent, st, text, H == 1);
     HIPCHK(ctx, launch_enter(d_ids, id_first[1], tx, b_at(0), tfp, 0, nl, s));
+    if (H > 1) {
+      scr = make_scratch(c, b_at(0), h_tcount);
+      HIPCHK(ctx, launch_fill_many(scr.fill, s));
+    }
   }
 
   // Runs of the first level: one per non-empty text that enters there.  Each
@@ -1060,15 +1189,12 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
       break;
     }
 
-    // runs of this level (maximal sequences of consecutive blocks of one text).
-    // The run table is sized by c, which bounds any run count: it is indexed by
-    // the device's own count, which is checked against R only later
-    Buf<uint32_t> run = alloc<uint32_t>(ctx, c);
+    // runs of this level (maximal sequences of consecutive blocks of one text);
+    // the table is indexed by the device's own count, checked against R only later
     const uint64_t R = R_pred;
-    Buf<uint64_t> rs = alloc<uint64_t>(ctx, c), re = alloc<uint64_t>(ctx, c);
-    Buf<uint32_t> rtext = alloc<uint32_t>(ctx, c);
-    HIPCHK(ctx, launch_runs(st.p, text.p, c, b, tx, run.p, rs.p, re.p, rtext.p, lvl_totals.p + 2,
-                            next_scan(c), s));
+    if (T > 1)
+      HIPCHK(ctx, launch_runs(st.p, text.p, c, b, tx, run.p, rs.p, re.p, rtext.p, lvl_totals.p + 2,
+                              next_scan(c), s));
     LevelDev lv{c, b, st.p, text.p, run.p, R, rs.p, re.p, rtext.p};
 
     // a text whose final block is present and short has odd-length keys
@@ -1076,12 +1202,9 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
     for (uint32_t t = 0; t < T; ++t)
       if (h_tcount[t] && (h_n[t] % b) != 0) has_odd = true;
 
-    const uint64_t cap = std::max<uint64_t>(1024, pow2_at_least(c << ctx->tune.table_load_log2));
-    Buf<Slot> tab = alloc<Slot>(ctx, cap);
     Buf<uint64_t> kfp = alloc<uint64_t>(ctx, c), klen = alloc<uint64_t>(ctx, c),
                   klm = alloc<uint64_t>(ctx, c);
     Buf<uint32_t> kslot = alloc<uint32_t>(ctx, c);
-    Buf<uint64_t> oddb = alloc<uint64_t>(ctx, 8 * (uint64_t)T);
     // the phase's scan segments: at most one per entry (phase 1) or block (phase 2)
     const uint64_t nseg = std::max(E_ent, c);
     Buf<uint64_t> seg_ws = alloc<uint64_t>(ctx, nseg), seg_re = alloc<uint64_t>(ctx, nseg),
@@ -1093,15 +1216,12 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
     Buf<uint8_t> facts = alloc<uint8_t>(ctx, c);
     Buf<uint32_t> vlist = alloc<uint32_t>(ctx, c),
                   vmis = alloc<uint32_t>(ctx, 2 * b > kSettleMax ? c : 0);
-    Buf<uint64_t> vbest = alloc<uint64_t>(ctx, c), vcnt = alloc<uint64_t>(ctx, 2);
+    Buf<uint64_t> vbest = alloc<uint64_t>(ctx, c);
     Buf<uint8_t> marked = alloc<uint8_t>(ctx, c);
-    // LDS key filter of up to 2^20 bits, sized per phase from the key count
-    Buf<uint32_t> filt = alloc<uint32_t>(ctx, (1ull << 20) / 32);
-    // second key filter (global memory, at most 2^24 bits = 2 MiB: stays in L2)
-    Buf<uint32_t> filt2 = alloc<uint32_t>(ctx, (1ull << ctx->tune.filter2_max_log2) / 32);
     int scan_mode = 1;
     uint32_t fbits = 12;
-    VerifyBufs vb{vlist.p, vbest.p, vmis.p, vcnt.p};
+    VerifyBufs vb{vlist.p, vbest.p, vmis.p, scr.vcnt.p};
+    uint64_t* const oddb = scr.oddb.p;
 
     PhaseArgs a{};
     a.T = d_base;
@@ -1117,61 +1237,19 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
     a.tx = tx;
     a.lv = lv;
     a.k = KeysDev{kfp.p, klen.p, kslot.p, klm.p, nullptr};
-    a.odd = OddDev{oddb.p,         oddb.p + T,     oddb.p + 2 * T, oddb.p + 3 * T,
-                   oddb.p + 4 * T, oddb.p + 5 * T, oddb.p + 6 * T, oddb.p + 7 * T};
+    a.odd = OddDev{oddb,         oddb + T,     oddb + 2 * T, oddb + 3 * T,
+                   oddb + 4 * T, oddb + 5 * T, oddb + 6 * T, oddb + 7 * T};
     a.x32 = x32;
-    a.tab = TableDev{tab.p, cap - 1};
+    a.tab = TableDev{scr.tab.p, scr.cap - 1};
     a.x = x;
     a.fpmask = fpmask;
     a.marked = marked.p;
-    a.filt = filt.p;
-    a.filt2 = filt2.p;
+    a.filt = scr.filt.p;
+    a.filt2 = scr.filt2.p;
     // parent facts per block: keys inside a parent region that occurs earlier
     // are known copies and stay out of the table
     a.cflag = cflag.p;
     a.exact_all = prune ? 1 : 0;
-
-    // Text-local filters (batches): per text, 2^wl 32-bit words with wl the
-    // least >= 3 such that each of the text's blocks (a bound on its keys in
-    // either phase) has a word.  One layout serves both phases.
-    // A text whose filter is larger than LDS also gets a folded copy of LDS
-    // size (tf_fold), built after the keys.
-    Buf<uint64_t> tf_off, span_ctr;
-    Buf<uint32_t> tf_words, tf_fold;
-    const uint64_t* tf_fold_off = nullptr;
-    uint32_t *tf_wl = nullptr, *tf_big = nullptr;
-    uint64_t tf_total = 0;
-    uint32_t nbig = 0;
-    if (has_salt && c && !(prm.debug_flags & (BT_DBG_SHARED_FILTERS | BT_DBG_SORT_PHASES))) {
-      // one upload: filter offsets and folded ones (u64), log2 sizes (u32), the
-      // texts with a folded filter (u32)
-      std::vector<uint64_t> up(3 * (uint64_t)T + 1, 0);
-      uint64_t *h_off = up.data(), *h_foff = h_off + T;
-      uint32_t *h_wl = reinterpret_cast<uint32_t*>(h_foff + T), *h_big = h_wl + T;
-      const uint32_t tf_lds = kTextFilterLdsLog2;
-      for (uint32_t t = 0; t < T; ++t) {
-        uint32_t wl = 3;
-        // 2^(bits_log2 - 5) words of 32 bits per block
-        const uint32_t bl = ctx->tune.text_filter_bits_log2;
-        const uint64_t need = bl >= 5 ? h_tcount[t] << (bl - 5) : (h_tcount[t] + 1) >> (5 - bl);
-        while ((1ull << wl) < need) ++wl;
-        h_wl[t] = wl;
-        h_off[t] = tf_total;
-        tf_total += 1ull << wl;
-        if (wl > tf_lds) {
-          h_foff[t] = (uint64_t)nbig << tf_lds;
-          h_big[nbig++] = t;
-        }
-      }
-      tf_words = alloc<uint32_t>(ctx, tf_total);
-      tf_off = alloc<uint64_t>(ctx, up.size());
-      tf_fold_off = tf_off.p + T;
-      tf_wl = reinterpret_cast<uint32_t*>(tf_off.p + 2 * (uint64_t)T);
-      tf_big = tf_wl + T;
-      upload(ctx, tf_off.p, up.data(), up.size());
-      if (nbig) tf_fold = alloc<uint32_t>(ctx, (uint64_t)nbig << tf_lds);
-      span_ctr = alloc<uint64_t>(ctx, 1);
-    }
 
     // nkeys: keys of the phase (pairs of consecutive blocks, or unmarked blocks)
     auto run_phase = [&](int phase, uint64_t nkeys) {
@@ -1181,35 +1259,17 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
       if (phase == 2 && nkeys == 0) return;  // nothing of the phase is read
       a.Lmain = phase == 1 ? 2 * b : b;
       a.xLmain = host_pow61(x, a.Lmain);
-      // LDS filter: 32 bits per key or more, at most 2^19 bits (64 KiB; 2^20 in
-      // scans of dense hashes, which run one workgroup per CU), two bits per key
-      // while there are at least 3 bits per key (at 4, 17% of windows pass in
-      // place of 22%).  The scan tests the
-      // 32-bit pre-filter hash and queues its candidates (mode 1); from 2^14
-      // keys on, where the LDS filter starts to pass a sizeable share of the
-      // windows, those also test a blocked second filter in global memory of
-      // about 32 bits per key (at most 2^24 bits, L2-resident; beyond 2^19
-      // keys it is what rejects most windows).  Queue entries pack a position
+      // The scan tests the 32-bit pre-filter hash against the LDS filter and
+      // queues its candidates (mode 1); from 2^14 keys on, where the LDS filter
+      // starts to pass a sizeable share of the windows, those also test a blocked
+      // second filter in global memory (at most 2^24 bits, L2-resident; beyond
+      // 2^19 keys it is what rejects most windows).  Queue entries pack a position
       // below 2^40 and a text below 2^24; past that, a 2^19-bit filter on
       // 61-bit fingerprints without queues (mode 2), whose passes probe the
       // table at once.
-      fbits = 12;
-      // (128 bits per key where the scan is long against the filter's copying)
-      const uint64_t per_key = !lean && c * b >= (1ull << 26) ? 128 : 32;
-      while (fbits < (lean ? 19u : 20u) && (1ull << fbits) < per_key * nkeys) ++fbits;
-      uint32_t f2words = 0;
-      const bool can_queue = T <= (1u << 24) && offs[T] < (1ull << 40) &&
-                             !(prm.debug_flags & BT_DBG_NO_QUEUE);
-      if (can_queue) {
-        scan_mode = 1;
-        if (nkeys >= (1ull << 14)) {  // 64-bit words, about 32 bits per key
-          f2words = 10;
-          while (f2words < ctx->tune.filter2_max_log2 - 6 && (64ull << f2words) < 32 * nkeys) ++f2words;
-        }
-      } else {
-        scan_mode = 2;
-        fbits = 19;
-      }
+      fbits = filter_bits(c, b, nkeys);
+      uint32_t f2words = filter2_words(nkeys);
+      scan_mode = can_queue ? 1 : 2;
       // The byte scan: phase 1 of the upper levels, whose few keys (pairs of
       // 2b >= 32 bytes, short final pairs of more than b) are all at least 8
       // bytes long.  A filter of the keys' first eight bytes replaces the hash
@@ -1217,34 +1277,33 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
       // 2^23 and a fit bit.  (Measured: with more keys, or in phase 2, the
       // windows that share a key's first eight bytes cost more than the hash
       // filters save.)
-      const bool byte_scan = phase == 1 && b >= 16 && nkeys <= 128 && T < (1u << 23) &&
+      const bool byte_scan = phase == 1 && b >= 16 && nkeys <= kByteKeys && T < (1u << 23) &&
                              offs[T] < (1ull << 40) && !(prm.debug_flags & BT_DBG_NO_BYTE_SCAN);
       uint32_t bbits = 0;
       if (byte_scan) {
-        // at least 2048 bits per key (chance passes below 1/2048 of windows);
-        // every workgroup copies the filter into LDS
-        bbits = 12;
-        while (bbits < 19 && (1ull << bbits) < 2048 * nkeys) ++bbits;
+        bbits = byte_bits(nkeys);
         fbits = 0;
         f2words = 0;
         scan_mode = 1;
       }
       // batches: each window against its own text's filter (probe_text.hip)
-      const bool text_local = tf_total && !byte_scan && scan_mode == 1;
+      const bool text_local = scr.tf_total && !byte_scan && scan_mode == 1;
       if (text_local) {
         fbits = 0;
         f2words = 0;
       }
-      a.tf_words = text_local ? tf_words.p : nullptr;
-      a.tf_off = text_local ? tf_off.p : nullptr;
-      a.tf_wl = text_local ? tf_wl : nullptr;
-      a.tf_fold = text_local ? tf_fold.p : nullptr;
-      a.tf_fold_off = text_local ? tf_fold_off : nullptr;
+      a.tf_words = text_local ? scr.tf_words.p : nullptr;
+      a.tf_off = text_local ? scr.tf_off.p : nullptr;
+      a.tf_wl = text_local ? scr.tf_wl : nullptr;
+      a.tf_fold = text_local ? scr.tf_fold.p : nullptr;
+      a.tf_fold_off = text_local ? scr.tf_fold_off : nullptr;
       a.filt_bits = fbits;
+      // two bits per key while there are at least 3 (at 4, 17% of windows pass in
+      // place of 22%)
       a.filt_two = fbits && 3 * nkeys <= (1ull << fbits);
       a.pre32 = !byte_scan && scan_mode == 1;
       a.filt2_words = f2words;
-      a.bfilt = byte_scan ? filt.p : nullptr;
+      a.bfilt = byte_scan ? scr.filt.p : nullptr;
       a.bfilt_bits = bbits;
       a.x32L = host_pow32(x32, a.Lmain);
       a.x32Lm1 = host_pow32(x32, a.Lmain ? a.Lmain - 1 : 0);
@@ -1266,8 +1325,8 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
         for (uint32_t to : ends) {
           if (from) {
             FillList f;
-            f.add(filt.p, (1ull << a.filt_bits) / 32, 0);
-            if (a.filt2_words) f.add(filt2.p, 2ull << a.filt2_words, 0);
+            f.add(scr.filt.p, (1ull << a.filt_bits) / 32, 0);
+            if (a.filt2_words) f.add(scr.filt2.p, 2ull << a.filt2_words, 0);
             hipError_t e = launch_fill_many(f, s);
             if (e == hipSuccess) e = launch_refilter(as, swoff, from, s);
             if (e != hipSuccess) return e;
@@ -1279,23 +1338,10 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
         }
         return hipSuccess;
       };
-      if (nkeys) {
-        FillList f;
-        f.add(tab.p, 4 * cap, ~0u);  // empty slots: fp = best = ~0
-        f.add(oddb.p, 16 * (uint64_t)T, 0);
-        f.add(vcnt.p, 4, 0);
-        f.add(filt.p, (1ull << (byte_scan ? bbits : fbits)) / 32, 0);
-        if (f2words) f.add(filt2.p, 2ull << f2words, 0);
-        if (text_local) {
-          f.add(tf_words.p, tf_total, 0);
-          f.add(span_ctr.p, 2, 0);
-        }
-        HIPCHK(ctx, launch_fill_many(f, s));
-      }
       HIPCHK(ctx, launch_keys(a, s));
       // no keys: the slots say so (kNoKey), and there is nothing to scan for
       if (nkeys == 0) return;
-      if (text_local) HIPCHK(ctx, launch_fold_filters(a, tf_big, nbig, s));
+      if (text_local) HIPCHK(ctx, launch_fold_filters(a, scr.tf_big, scr.nbig, s));
       PhaseArgs as = a;  // the scan walks segments in place of runs
       as.lv.rs = seg_ws.p;
       as.lv.re = seg_re.p;
@@ -1364,7 +1410,7 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
         timed(ctx, "probe_scan", 0, 0, wst, per_value * (1.0 + partner), [&] {
           // phase 2's segments (runs of blocks whose pairs do not occur
           // earlier) are short against a tile at the lowest levels
-          return text_local ? launch_probe_text(as, swoff, has_odd, c * b, span_chunks, span_ctr.p,
+          return text_local ? launch_probe_text(as, swoff, has_odd, c * b, span_chunks, scr.span_ctr.p,
                                                 span_info.p, phase == 2 && b <= 64, s)
                             : scan_rounds(as, swoff, rounds, tile_segs ? tseg.p : nullptr, !piece_segs);
         }, a.Lmain);
@@ -1385,21 +1431,24 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
     // marks and, from them, the shape of the next level: one read-back
     const uint64_t bn = b / prm.tau;
     Buf<uint64_t> uoff = alloc<uint64_t>(ctx, c + 1), cs = alloc<uint64_t>(ctx, c + 1);
-    HIPCHK(ctx, launch_marks(a, bn, marked.p, facts.p, uoff.p, cs.p, lvl_totals.p, next_scan(c), s));
+    Buf<uint32_t> rnum;
+    if (T == 1) rnum = alloc<uint32_t>(ctx, c);
     Buf<uint64_t> ntcount = alloc<uint64_t>(ctx, T), ntfirst = alloc<uint64_t>(ctx, T + 1),
                   d_woff = alloc<uint64_t>(ctx, T + 1);
     const TextStep ts{cs.p,      tfp,          tcp,       uoff.p,
                       d_estep,   step + 1,     bn,        ntcount.p,
                       ntfirst.p, d_woff.p,     lvl_totals.p, seen_read ? nullptr : d_seen.p,
                       d_lvl + kHostTotals, d_lvl + kHostTotals + T, d_lvl};
-    HIPCHK(ctx, launch_texts(tx, ts, next_scan(T), s));
+    HIPCHK(ctx, launch_marks(a, bn, marked.p, facts.p, uoff.p, cs.p, lvl_totals.p, rnum.p, ts, scr.fill,
+                             next_scan(c), s));
+    if (T > 1) HIPCHK(ctx, launch_texts(tx, ts, next_scan(T), s));
     HIPCHK(ctx, hipStreamSynchronize(s));
     ctx->h_stage_used = 0;  // every queued upload has completed
     collect_events(ctx);
     const uint64_t u = h_lvl[0];
     const uint32_t n_enter = id_first[step + 2] - id_first[step + 1];
     R_pred = h_lvl[1] + n_enter;  // runs of the next level: marked groups, entering texts
-    check_runs(h_lvl[2], R);
+    if (T > 1) check_runs(h_lvl[2], R);
     if (!seen_read) check_seen(h_lvl + 3);
     const std::vector<uint64_t> h_ntcount(h_lvl + kHostTotals, h_lvl + kHostTotals + T),
         h_tu(h_lvl + kHostTotals + T, h_lvl + kHostTotals + 2 * (uint64_t)T);
@@ -1423,16 +1472,33 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
     for (uint32_t t = 0; t < T; ++t) cn += h_ntcount[t];
     Buf<uint64_t> nst;
     Buf<uint32_t> ntext;
-    const NextLevel nl = alloc_next(cn, (c - u) + n_enter, nst, ntext);
+    // this level's scratch goes back before the next one's is taken (the split
+    // reads none of it), its run table is still read
+    Buf<uint32_t> lrun = std::move(run), lrtext = std::move(rtext);
+    Buf<uint64_t> lrs = std::move(rs), lre = std::move(re);
+    const bool next_leaf = step + 2 == H;
+    const NextLevel nl = alloc_next(cn, (c - u) + n_enter, nst, ntext, next_leaf);
     E_ent = (c - u) + n_enter;
-    HIPCHK(ctx, launch_split(a, facts.p, uoff.p, cs.p, tfp, ntfirst.p, bn, a.all_blocks, nl,
-                             prune ? nullptr : spb.p, spo.p, reinterpret_cast<uint32_t*>(d_err.p), s));
+    scr = LevelScratch{};
+    if (!next_leaf) scr = make_scratch(cn, bn, h_ntcount);
+    StoreMarks sm{T, uoff.p, tfp, tcp, d_woff.p, 0, nullptr, nullptr};
+    Buf<uint64_t> words, wrank;
+    if (!prune) {
+      for (uint32_t t = 0; t < T; ++t) sm.nwords += (h_tcount[t] + 63) / 64;
+      words = alloc<uint64_t>(ctx, sm.nwords);
+      wrank = alloc<uint64_t>(ctx, sm.nwords + 1);
+      sm.words = words.p;
+      sm.wrank = wrank.p;
+    }
+    HIPCHK(ctx, launch_split(a, facts.p, cs.p, ntfirst.p, bn, a.all_blocks, rnum.p, nl, sm,
+                             prune ? nullptr : spb.p, spo.p, reinterpret_cast<uint32_t*>(d_err.p),
+                             scr.fill, s));
     HIPCHK(ctx, launch_enter(d_ids + id_first[step + 1], n_enter, tx, bn, ntfirst.p, c - u, nl, s));
 
     // ---- outputs of this level: marks (word range per text) and pointers
     if (!prune)
       store_level(step, b, c, st.p, text.p, marked.p, uoff.p, spb, spo, u, h_tcount, h_tfirst,
-                  h_tu, tfp, tcp, d_woff.p);
+                  h_tu, tfp, tcp, std::move(words), std::move(wrank));
 
     if (prune) {
       PruneLevel& K = pl[step];
@@ -1440,7 +1506,7 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
       K.c = c;
       K.st = std::move(st);
       K.text = std::move(text);
-      K.run = std::move(run);
+      K.run = std::move(lrun);
       K.marked = std::move(marked);
       K.lm = std::move(klm);
       K.cs = std::move(cs);
@@ -1517,7 +1583,7 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
         Buf<uint64_t> spb = alloc<uint64_t>(ctx, u), spo = alloc<uint64_t>(ctx, u);
         if (c) HIPCHK(ctx, launch_pointers(pa, nmarked.p, nuoff.p, ntf.p, spb.p, spo.p, err, s));
         store_level(step, K.b, c, nst.p, ntext.p, nmarked.p, nuoff.p, spb, spo, u, tc, tf, tu,
-                    ntf.p, ntc.p, nullptr);
+                    ntf.p, ntc.p, {}, {});
       }
       K = PruneLevel{};
     };

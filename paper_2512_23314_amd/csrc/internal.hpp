@@ -195,8 +195,7 @@ struct SegOut {
 
 hipError_t launch_fill_u64(uint64_t* p, uint64_t v, uint64_t n, hipStream_t s);
 hipError_t launch_fill_u8(uint8_t* p, uint8_t v, uint64_t n, hipStream_t s);
-// Up to kFillJobs fills of 32-bit words in one launch (jobs with no words are
-// skipped by their blocks).
+// Up to kFillJobs fills of 32-bit words in one launch, or inside another kernel.
 constexpr int kFillJobs = 8;
 struct FillList {
   uint32_t* p[kFillJobs];
@@ -209,7 +208,26 @@ struct FillList {
     value[n] = v;
     ++n;
   }
+  uint64_t total() const {
+    uint64_t t = 0;
+    for (int k = 0; k < n; ++k) t += words[k];
+    return t;
+  }
 };
+// Thread tid of `stride` does its share of the fills (device), 16 bytes per store
+// where a buffer allows.
+__device__ __forceinline__ void fill_share(const FillList& f, uint64_t tid, uint64_t stride) {
+  for (int y = 0; y < f.n; ++y) {
+    uint32_t* p = f.p[y];
+    const uint64_t n = f.words[y];
+    const uint32_t v = f.value[y];
+    const uint64_t nq = (reinterpret_cast<uintptr_t>(p) & 15) == 0 ? n / 4 : 0;
+    uint4* q = reinterpret_cast<uint4*>(p);
+    const uint4 vv = make_uint4(v, v, v, v);
+    for (uint64_t i = tid; i < nq; i += stride) q[i] = vv;
+    for (uint64_t i = 4 * nq + tid; i < n; i += stride) p[i] = v;
+  }
+}
 hipError_t launch_fill_many(const FillList& f, hipStream_t s);
 
 // Exclusive scan of a[0..n) in place; a[n] receives the total.  tmp must hold
@@ -328,8 +346,13 @@ hipError_t launch_block_segs(const PhaseArgs& a, const uint8_t* pf, const SegOut
 // Step a5 from the phase-1 results: marks, pair facts, unmarked ranks and
 // children's ranks (exclusive, c + 1 words), totals = {unmarked, runs of the next
 // level among the children}.  bn: the next level's block length.
+// Also clears the buffers of `fill` (phase 2's).  With one text (tx.T == 1), also
+// what launch_texts does, and rnum[j] (not null then): the run of the next level
+// that block j's children belong to.
+struct TextStep;
 hipError_t launch_marks(const PhaseArgs& a, uint64_t bn, uint8_t* marked, uint8_t* pf, uint64_t* uoff,
-                        uint64_t* cs, uint64_t* totals, const ScanDev& sd, hipStream_t s);
+                        uint64_t* cs, uint64_t* totals, uint32_t* rnum, const TextStep& ts,
+                        const FillList& fill, const ScanDev& sd, hipStream_t s);
 // Per text, for the next level (h_*: pinned host memory).
 struct TextStep {
   const uint64_t *cs, *tfirst, *tcount, *uoff;  // this level
@@ -351,8 +374,10 @@ hipError_t launch_pointers(const PhaseArgs& a, const uint8_t* marked, const uint
                            const uint64_t* tfirst, uint64_t* ptr_block, uint64_t* ptr_off,
                            uint32_t* err, hipStream_t s);
 
-// Step a8: the next level's blocks, their parents' facts (PhaseArgs.cflag) and
-// its scan entries; and, with pb, this level's pointers as launch_pointers.
+// Step a8: the next level's blocks, their parents' facts (PhaseArgs.cflag), its
+// scan entries and, with run, its runs (one text); with pb, this level's pointers
+// as launch_pointers; with marks.nwords, its stored marks as launch_store_marks;
+// and the buffers of `fill` cleared.
 struct NextLevel {
   uint64_t* st;
   uint32_t* text;
@@ -360,11 +385,20 @@ struct NextLevel {
   uint64_t *ea, *ee;
   uint8_t* ef;
   uint64_t* echild;
+  uint32_t* run;
+  uint64_t *rs, *re;
+  uint32_t* rtext;
 };
-hipError_t launch_split(const PhaseArgs& a, const uint8_t* pf, const uint64_t* uoff,
-                        const uint64_t* cs, const uint64_t* tfirst, const uint64_t* ntfirst,
-                        uint64_t bn, uint32_t blocks, const NextLevel& o, uint64_t* pb, uint64_t* po,
-                        uint32_t* err, hipStream_t s);
+struct StoreMarks {
+  uint32_t T;
+  const uint64_t *uoff, *tfirst, *tcount, *woff;
+  uint64_t nwords;
+  uint64_t *words, *wrank;
+};
+hipError_t launch_split(const PhaseArgs& a, const uint8_t* pf, const uint64_t* cs,
+                        const uint64_t* ntfirst, uint64_t bn, uint32_t blocks, const uint32_t* rnum,
+                        const NextLevel& o, const StoreMarks& m, uint64_t* pb, uint64_t* po,
+                        uint32_t* err, const FillList& fill, hipStream_t s);
 // E texts that enter there (none empty), their entries from `base` on.
 hipError_t launch_enter(const uint32_t* ids, uint32_t E, const TextsDev& tx, uint64_t bn,
                         const uint64_t* ntfirst, uint64_t base, const NextLevel& o, hipStream_t s);
@@ -372,9 +406,7 @@ hipError_t launch_enter(const uint32_t* ids, uint32_t E, const TextsDev& tx, uin
 // Outputs.
 // Marks of each text in its own word range (from woff[t]) and the marks before
 // each word; tfirst/tcount give its blocks, uoff their unmarked ranks.
-hipError_t launch_store_marks(const uint8_t* marked, const uint64_t* uoff, uint32_t T,
-                              const uint64_t* tfirst, const uint64_t* tcount, const uint64_t* woff,
-                              uint64_t nwords, uint64_t* words, uint64_t* wrank, hipStream_t s);
+hipError_t launch_store_marks(const uint8_t* marked, const StoreMarks& m, hipStream_t s);
 // Leaves: bytes of every block of the last level, block after block.
 hipError_t launch_leaves(const uint8_t* T, const LevelDev& lv, const TextsDev& tx,
                          uint8_t* out, hipStream_t s);

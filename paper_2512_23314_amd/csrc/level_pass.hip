@@ -209,6 +209,14 @@ hipError_t launch_block_segs(const PhaseArgs& a, const uint8_t* pf, const SegOut
 
 // ---------------------------------------------------------------- marks (a5)
 
+__device__ __forceinline__ void host_totals(const TextStep& ts, uint64_t unmarked, uint64_t next_runs) {
+  ts.h_totals[0] = unmarked;
+  ts.h_totals[1] = next_runs;
+  ts.h_totals[2] = ts.totals[2];  // this level's runs
+  if (ts.seen)
+    for (int k = 0; k < 4; ++k) ts.h_totals[3 + k] = ts.seen[k];
+}
+
 // After phase 1: the marks (a block's pair or its left neighbour's pair is
 // leftmost, or it has no consecutive neighbour), the pair facts (bit 0 of pf[j]:
 // the pair (j, j+1) occurs earlier), the unmarked ranks that pointers are stored
@@ -220,6 +228,8 @@ struct MarkPass {
   uint64_t bn;
   uint8_t *marked, *pf;
   uint64_t *uoff, *cs, *totals;
+  uint32_t* rnum;
+  TextStep ts;
   __device__ bool leftmost(uint64_t q) const {
     return a.k.slot[q] != kNoKey && a.k.lm[q] == a.lv.st[q];
   }
@@ -240,24 +250,39 @@ struct MarkPass {
     v[1] = (m && (j == 0 || lv.run[j - 1] != lv.run[j] || !mark(j - 1))) ? 1 : 0;
     v[2] = m ? (block_len(lv, a.tx, j) + bn - 1) / bn : 0;
   }
-  __device__ void apply(uint64_t j, const uint64_t* ex, const uint64_t*) const {
+  __device__ void apply(uint64_t j, const uint64_t* ex, const uint64_t* v) const {
     uoff[j] = ex[0];
     cs[j] = ex[2];
+    if (rnum) rnum[j] = (uint32_t)(ex[1] + v[1] - 1);
   }
   __device__ void total(const uint64_t* sum) const {
     uoff[a.lv.c] = sum[0];
     cs[a.lv.c] = sum[2];
     totals[0] = sum[0];
     totals[1] = sum[1];
+    if (!rnum) return;
+    // one text: the step of TextPass (nothing enters below its first level)
+    ts.ncount[0] = sum[2];
+    ts.nfirst[0] = 0;
+    ts.nfirst[1] = sum[2];
+    ts.woff[0] = 0;
+    ts.woff[1] = (a.lv.c + 63) / 64;
+    ts.h_ncount[0] = sum[2];
+    ts.h_tu[0] = sum[0];
+    host_totals(ts, sum[0], sum[1]);
   }
 };
-__global__ __launch_bounds__(kPassThreads) void k_marks(MarkPass p, ScanDev sd) {
+__global__ __launch_bounds__(kPassThreads) void k_marks(MarkPass p, FillList f, ScanDev sd) {
   scan_pass<3, 3u>(p.a.lv.c, sd, p);
+  fill_share(f, (uint64_t)blockIdx.x * kPassThreads + threadIdx.x, (uint64_t)gridDim.x * kPassThreads);
 }
 
 hipError_t launch_marks(const PhaseArgs& a, uint64_t bn, uint8_t* marked, uint8_t* pf, uint64_t* uoff,
-                        uint64_t* cs, uint64_t* totals, const ScanDev& sd, hipStream_t s) {
-  k_marks<<<pass_grid(a.lv.c), kPassThreads, 0, s>>>(MarkPass{a, bn, marked, pf, uoff, cs, totals}, sd);
+                        uint64_t* cs, uint64_t* totals, uint32_t* rnum, const TextStep& ts,
+                        const FillList& fill, const ScanDev& sd, hipStream_t s) {
+  if (rnum && a.tx.T != 1) return hipErrorInvalidValue;
+  k_marks<<<pass_grid(a.lv.c), kPassThreads, 0, s>>>(
+      MarkPass{a, bn, marked, pf, uoff, cs, totals, rnum, ts}, fill, sd);
   return hipGetLastError();
 }
 
@@ -284,9 +309,7 @@ struct TextPass {
   __device__ void total(const uint64_t* sum) const {
     ts.nfirst[tx.T] = sum[0];
     ts.woff[tx.T] = sum[1];
-    for (int k = 0; k < 3; ++k) ts.h_totals[k] = ts.totals[k];  // unmarked, next runs, runs
-    if (ts.seen)
-      for (int k = 0; k < 4; ++k) ts.h_totals[3 + k] = ts.seen[k];
+    host_totals(ts, ts.totals[0], ts.totals[1]);
   }
 };
 __global__ __launch_bounds__(kPassThreads) void k_texts(TextPass p, ScanDev sd) {
@@ -342,46 +365,85 @@ hipError_t launch_pointers(const PhaseArgs& a, const uint8_t* marked, const uint
   return hipGetLastError();
 }
 
+// The marks of each text packed into its own words, one wave per word, and the
+// marks before each word: its first block's index in the text less the unmarked
+// blocks before it.  Wave gw of nw.
+__device__ __forceinline__ void store_marks(const uint8_t* marked, const StoreMarks& m, uint64_t gw,
+                                            uint64_t nw) {
+  const int lane = lane_id();
+  for (uint64_t wi = gw; wi < m.nwords; wi += nw) {
+    uint64_t lo = 0, hi = m.T;
+    while (hi - lo > 1) {
+      const uint64_t mid = (lo + hi) >> 1;
+      if (m.woff[mid] <= wi) lo = mid; else hi = mid;
+    }
+    // (texts with no words share an offset with the next: the last one is taken)
+    const uint64_t j = (wi - m.woff[lo]) * 64, f = m.tfirst[lo];
+    const uint64_t word = __ballot(j + lane < m.tcount[lo] && marked[f + j + lane]);
+    if (lane == 0) {
+      m.words[wi] = word;
+      m.wrank[wi] = j - (m.uoff[f + j] - m.uoff[f]);
+    }
+  }
+}
+
 // Marked blocks: their children (the next level's blocks, each with its parent's
-// facts) and their scan entry; unmarked ones (with pb): their pointer.  After a
-// phase 2 over all blocks (blocks != 0) a block's own earlier occurrence is a
-// fact too.
-__global__ void k_split(PhaseArgs a, const uint8_t* pf, const uint64_t* uoff, const uint64_t* cs,
-                        const uint64_t* tfirst, const uint64_t* ntfirst, uint64_t bn, uint32_t blocks,
-                        NextLevel o, uint64_t* pb, uint64_t* po, uint32_t* err) {
+// facts and, for one text, its run) and their scan entry; unmarked ones (with pb):
+// their pointer.  After a phase 2 over all blocks (blocks != 0) a block's own
+// earlier occurrence is a fact too.  Then the stored marks, and the next level's
+// scratch cleared: each took a launch of its own, with the runs and (one text) the
+// per-text counts five a level.
+__global__ __launch_bounds__(256) void k_split(PhaseArgs a, const uint8_t* pf, const uint64_t* cs,
+                                               const uint64_t* ntfirst, uint64_t bn, uint32_t blocks,
+                                               const uint32_t* rnum, NextLevel o, StoreMarks m,
+                                               uint64_t* pb, uint64_t* po, uint32_t* err, FillList f) {
   const LevelDev lv = a.lv;
   GRID_STRIDE(j, lv.c) {
     if (!a.marked[j]) {
-      if (pb) write_pointer(a, j, a.marked, uoff, tfirst, pb, po, err);
+      if (pb) write_pointer(a, j, a.marked, m.uoff, m.tfirst, pb, po, err);
       continue;
     }
     const uint32_t t = lv.text[j];
     const uint64_t c0 = cs[j], nk = cs[j + 1] - c0, st = lv.st[j], te = a.tx.tend[t];
-    const uint64_t base = ntfirst[t] + (c0 - cs[tfirst[t]]);
+    const uint64_t end = st + (te - st < lv.b ? te - st : lv.b);
+    const uint64_t base = ntfirst[t] + (c0 - cs[m.tfirst[t]]);
     const bool again = blocks && a.k.slot[j] != kNoKey && a.k.lm[j] < st;
-    uint8_t f = 0;
-    if (pf[j] & 1) f |= kSkipCross;
-    if (again || (j > 0 && (pf[j - 1] & 1))) f |= kSkipInterior;
+    uint8_t fl = 0;
+    if (pf[j] & 1) fl |= kSkipCross;
+    if (again || (j > 0 && (pf[j - 1] & 1))) fl |= kSkipInterior;
     for (uint64_t k = 0; k < nk; ++k) {
       o.st[base + k] = st + k * bn;
       o.text[base + k] = t;
-      o.cflag[base + k] = f ? f | (k + 1 == nk ? kLastChild : 0) : 0;
+      o.cflag[base + k] = fl ? fl | (k + 1 == nk ? kLastChild : 0) : 0;
     }
-    const uint64_t e = j - uoff[j];
+    const uint64_t e = j - m.uoff[j];
     o.ea[e] = st;
-    o.ee[e] = st + (te - st < lv.b ? te - st : lv.b);
-    o.ef[e] = f;
+    o.ee[e] = end;
+    o.ef[e] = fl;
     o.echild[e] = base;
+    if (o.run) {
+      const uint32_t r = rnum[j], here = lv.run[j];
+      for (uint64_t k = 0; k < nk; ++k) o.run[base + k] = r;
+      if (j == 0 || lv.run[j - 1] != here || !a.marked[j - 1]) {
+        o.rs[r] = st;
+        o.rtext[r] = t;
+      }
+      if (j + 1 == lv.c || lv.run[j + 1] != here || !a.marked[j + 1]) o.re[r] = end;
+    }
   }
+  store_marks(a.marked, m, (uint64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6),
+              (uint64_t)gridDim.x * 4);
+  fill_share(f, (uint64_t)blockIdx.x * 256 + threadIdx.x, (uint64_t)gridDim.x * 256);
 }
 
-hipError_t launch_split(const PhaseArgs& a, const uint8_t* pf, const uint64_t* uoff,
-                        const uint64_t* cs, const uint64_t* tfirst, const uint64_t* ntfirst,
-                        uint64_t bn, uint32_t blocks, const NextLevel& o, uint64_t* pb, uint64_t* po,
-                        uint32_t* err, hipStream_t s) {
-  if (!a.lv.c) return hipSuccess;
-  k_split<<<grid_for(a.lv.c, 256), 256, 0, s>>>(a, pf, uoff, cs, tfirst, ntfirst, bn, blocks, o, pb,
-                                                po, err);
+hipError_t launch_split(const PhaseArgs& a, const uint8_t* pf, const uint64_t* cs,
+                        const uint64_t* ntfirst, uint64_t bn, uint32_t blocks, const uint32_t* rnum,
+                        const NextLevel& o, const StoreMarks& m, uint64_t* pb, uint64_t* po,
+                        uint32_t* err, const FillList& fill, hipStream_t s) {
+  // (a level may be far larger than the one above where texts enter)
+  const uint64_t by_fill = fill.total() / (4 * 256 * 16);
+  const unsigned g = grid_for(a.lv.c, 256), gf = by_fill < 4096 ? (unsigned)by_fill : 4096u;
+  k_split<<<g > gf ? g : gf, 256, 0, s>>>(a, pf, cs, ntfirst, bn, blocks, rnum, o, m, pb, po, err, fill);
   return hipGetLastError();
 }
 
@@ -397,6 +459,14 @@ __global__ void k_enter(const uint32_t* ids, TextsDev tx, uint64_t bn, const uin
     o.st[first + k] = ts + k * bn;
     o.text[first + k] = t;
     o.cflag[first + k] = 0;
+  }
+  if (o.run) {  // one text: one run
+    for (uint64_t k = threadIdx.x; k < nb; k += blockDim.x) o.run[first + k] = 0;
+    if (threadIdx.x == 0) {
+      o.rs[0] = ts;
+      o.re[0] = te;
+      o.rtext[0] = t;
+    }
   }
   if (threadIdx.x == 0) {
     const uint64_t e = base + blockIdx.x;
@@ -416,40 +486,14 @@ hipError_t launch_enter(const uint32_t* ids, uint32_t E, const TextsDev& tx, uin
 
 // ---------------------------------------------------------------- outputs
 
-// The marks of each text packed into its own words, one wave per word, and the
-// marks before each word: its first block's index in the text less the unmarked
-// blocks before it.
-__global__ __launch_bounds__(256) void k_store_marks(const uint8_t* marked, const uint64_t* uoff,
-                                                     uint32_t T, const uint64_t* tfirst,
-                                                     const uint64_t* tcount, const uint64_t* woff,
-                                                     uint64_t nwords, uint64_t* words,
-                                                     uint64_t* wrank) {
-  const int lane = lane_id();
-  const uint64_t nw = (uint64_t)gridDim.x * 4;
-  for (uint64_t wi = (uint64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-       wi < nwords; wi += nw) {
-    uint64_t lo = 0, hi = T;
-    while (hi - lo > 1) {
-      const uint64_t mid = (lo + hi) >> 1;
-      if (woff[mid] <= wi) lo = mid; else hi = mid;
-    }
-    // (texts with no words share an offset with the next: the last one is taken)
-    const uint64_t j = (wi - woff[lo]) * 64, f = tfirst[lo];
-    const bool m = j + lane < tcount[lo] && marked[f + j + lane];
-    const uint64_t word = __ballot(m);
-    if (lane == 0) {
-      words[wi] = word;
-      wrank[wi] = j - (uoff[f + j] - uoff[f]);
-    }
-  }
+__global__ __launch_bounds__(256) void k_store_marks(const uint8_t* marked, StoreMarks m) {
+  store_marks(marked, m, (uint64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6),
+              (uint64_t)gridDim.x * 4);
 }
 
-hipError_t launch_store_marks(const uint8_t* marked, const uint64_t* uoff, uint32_t T,
-                              const uint64_t* tfirst, const uint64_t* tcount, const uint64_t* woff,
-                              uint64_t nwords, uint64_t* words, uint64_t* wrank, hipStream_t s) {
-  if (!nwords) return hipSuccess;
-  k_store_marks<<<grid_for(nwords, 4, 16384), 256, 0, s>>>(marked, uoff, T, tfirst, tcount, woff,
-                                                            nwords, words, wrank);
+hipError_t launch_store_marks(const uint8_t* marked, const StoreMarks& m, hipStream_t s) {
+  if (!m.nwords) return hipSuccess;
+  k_store_marks<<<grid_for(m.nwords, 4, 16384), 256, 0, s>>>(marked, m);
   return hipGetLastError();
 }
 

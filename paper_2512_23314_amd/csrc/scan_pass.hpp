@@ -64,9 +64,12 @@ __device__ __forceinline__ void scan_pass(uint64_t n, const ScanDev& sd, F&& f) 
   __shared__ uint64_t s_ex[NV];
   __shared__ uint64_t s_tile;
   const int lane = lane_id(), wv = threadIdx.x >> 6;
-  if (threadIdx.x == 0) s_tile = atomicAdd((unsigned long long*)sd.ticket, 1ull) - sd.base;
-  __syncthreads();
-  const uint64_t tile = s_tile;
+  uint64_t tile = 0;
+  if (gridDim.x > 1) {  // (a lone tile takes no ticket and looks at no other)
+    if (threadIdx.x == 0) s_tile = atomicAdd((unsigned long long*)sd.ticket, 1ull) - sd.base;
+    __syncthreads();
+    tile = s_tile;
+  }
   const uint64_t wbase = tile * kPassTile + (uint64_t)wv * (64 * kPassRows);
   uint64_t v[kPassRows][NV], ex[kPassRows][NV], run[NV];
 #pragma unroll
