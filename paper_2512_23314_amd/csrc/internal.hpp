@@ -243,8 +243,13 @@ struct ScanDev {
   uint64_t base;
   uint64_t epoch;    // 1 .. 2^22 - 1
 };
-constexpr uint64_t kPassTile = 2048;
-inline uint64_t scan_pass_tiles(uint64_t n) { return n ? (n + kPassTile - 1) / kPassTile : 1; }
+constexpr int kPassThreads = 256;
+// rows of 64 elements a wave takes of n (see scan_pass.hpp), and the tiles that makes
+inline int scan_pass_rows(uint64_t n) { return n <= (1ull << 18) ? 1 : n <= (1ull << 21) ? 2 : 8; }
+inline uint64_t scan_pass_tiles(uint64_t n) {
+  const uint64_t tile = (uint64_t)kPassThreads * scan_pass_rows(n);
+  return n ? (n + tile - 1) / tile : 1;
+}
 
 // The probe scan's tile: a wave takes this many consecutive window numbers at
 // a time (lanes step through them 64 apart).

@@ -17,6 +17,16 @@ static unsigned grid_for(uint64_t n, unsigned threads, unsigned cap = 8192) {
 }
 static unsigned pass_grid(uint64_t n) { return (unsigned)scan_pass_tiles(n); }
 
+// Launch kernel<ROWS> for n elements.
+#define BT_PASS(kernel, n, ...)                                                             \
+  do {                                                                                      \
+    const unsigned g_ = pass_grid(n);                                                       \
+    const int r_ = scan_pass_rows(n);                                                       \
+    if (r_ == 1) kernel<1><<<g_, kPassThreads, 0, s>>>(__VA_ARGS__);                        \
+    else if (r_ == 2) kernel<2><<<g_, kPassThreads, 0, s>>>(__VA_ARGS__);                   \
+    else kernel<8><<<g_, kPassThreads, 0, s>>>(__VA_ARGS__);                                \
+  } while (0)
+
 #define GRID_STRIDE(i, n)                                                        \
   for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < (n); \
        i += (uint64_t)gridDim.x * blockDim.x)
@@ -59,14 +69,16 @@ struct RunPass {
     if (total_out) *total_out = sum[0];
   }
 };
+template <int ROWS>
 __global__ __launch_bounds__(kPassThreads) void k_runs(RunPass p, ScanDev sd) {
-  scan_pass<1, 1u>(p.c, sd, p);
+  scan_pass<1, 1u, ROWS>(p.c, sd, p);
 }
 
 hipError_t launch_runs(const uint64_t* st, const uint32_t* text, uint64_t c, uint64_t b,
                        const TextsDev& tx, uint32_t* run, uint64_t* rs, uint64_t* re,
                        uint32_t* rtext, uint64_t* total, const ScanDev& sd, hipStream_t s) {
-  k_runs<<<pass_grid(c), kPassThreads, 0, s>>>(RunPass{st, text, c, b, tx, run, rs, re, rtext, total}, sd);
+  const RunPass p{st, text, c, b, tx, run, rs, re, rtext, total};
+  BT_PASS(k_runs, c, p, sd);
   return hipGetLastError();
 }
 
@@ -187,23 +199,25 @@ struct SegPass {
   }
 };
 
+template <int ROWS>
 __global__ __launch_bounds__(kPassThreads) void k_entry_segs(PhaseArgs a, SegDev sg, SegOut o,
                                                              uint64_t* wst, ScanDev sd) {
-  scan_pass<2, 2u>(sg.E, sd, SegPass<EntryPieces>{{a, sg}, o, wst});
+  scan_pass<2, 2u, ROWS>(sg.E, sd, SegPass<EntryPieces>{{a, sg}, o, wst});
 }
+template <int ROWS>
 __global__ __launch_bounds__(kPassThreads) void k_block_segs(PhaseArgs a, const uint8_t* pf, SegOut o,
                                                              uint64_t* wst, ScanDev sd) {
-  scan_pass<2, 2u>(a.lv.c, sd, SegPass<BlockPieces>{{a, pf}, o, wst});
+  scan_pass<2, 2u, ROWS>(a.lv.c, sd, SegPass<BlockPieces>{{a, pf}, o, wst});
 }
 
 hipError_t launch_entry_segs(const PhaseArgs& a, const SegDev& sg, const SegOut& o, uint64_t* wst,
                              const ScanDev& sd, hipStream_t s) {
-  k_entry_segs<<<pass_grid(sg.E), kPassThreads, 0, s>>>(a, sg, o, wst, sd);
+  BT_PASS(k_entry_segs, sg.E, a, sg, o, wst, sd);
   return hipGetLastError();
 }
 hipError_t launch_block_segs(const PhaseArgs& a, const uint8_t* pf, const SegOut& o, uint64_t* wst,
                              const ScanDev& sd, hipStream_t s) {
-  k_block_segs<<<pass_grid(a.lv.c), kPassThreads, 0, s>>>(a, pf, o, wst, sd);
+  BT_PASS(k_block_segs, a.lv.c, a, pf, o, wst, sd);
   return hipGetLastError();
 }
 
@@ -272,8 +286,9 @@ struct MarkPass {
     host_totals(ts, sum[0], sum[1]);
   }
 };
+template <int ROWS>
 __global__ __launch_bounds__(kPassThreads) void k_marks(MarkPass p, FillList f, ScanDev sd) {
-  scan_pass<3, 3u>(p.a.lv.c, sd, p);
+  scan_pass<3, 3u, ROWS>(p.a.lv.c, sd, p);
   fill_share(f, (uint64_t)blockIdx.x * kPassThreads + threadIdx.x, (uint64_t)gridDim.x * kPassThreads);
 }
 
@@ -281,8 +296,8 @@ hipError_t launch_marks(const PhaseArgs& a, uint64_t bn, uint8_t* marked, uint8_
                         uint64_t* cs, uint64_t* totals, uint32_t* rnum, const TextStep& ts,
                         const FillList& fill, const ScanDev& sd, hipStream_t s) {
   if (rnum && a.tx.T != 1) return hipErrorInvalidValue;
-  k_marks<<<pass_grid(a.lv.c), kPassThreads, 0, s>>>(
-      MarkPass{a, bn, marked, pf, uoff, cs, totals, rnum, ts}, fill, sd);
+  const MarkPass p{a, bn, marked, pf, uoff, cs, totals, rnum, ts};
+  BT_PASS(k_marks, a.lv.c, p, fill, sd);
   return hipGetLastError();
 }
 
@@ -312,12 +327,14 @@ struct TextPass {
     host_totals(ts, ts.totals[0], ts.totals[1]);
   }
 };
+template <int ROWS>
 __global__ __launch_bounds__(kPassThreads) void k_texts(TextPass p, ScanDev sd) {
-  scan_pass<2, 0u>(p.tx.T, sd, p);
+  scan_pass<2, 0u, ROWS>(p.tx.T, sd, p);
 }
 
 hipError_t launch_texts(const TextsDev& tx, const TextStep& ts, const ScanDev& sd, hipStream_t s) {
-  k_texts<<<pass_grid(tx.T), kPassThreads, 0, s>>>(TextPass{tx, ts}, sd);
+  const TextPass p{tx, ts};
+  BT_PASS(k_texts, tx.T, p, sd);
   return hipGetLastError();
 }
 

@@ -19,10 +19,13 @@
 
 namespace bt {
 
-constexpr int kPassThreads = 256;
-constexpr int kPassRows = 8;  // rows of 64 consecutive elements per wave
-static_assert(kPassTile == (uint64_t)kPassThreads * kPassRows, "host and device agree on the tile");
+// A wave takes ROWS rows of 64 consecutive elements, one after another, each a
+// chain of dependent loads: one row up to 2^18 elements, so that a small level is
+// spread over the chip (marks of levels of 2 to 65536 blocks: 15.5 -> 7.1 us each,
+// against eight rows), two up to 2^21, eight beyond, where the chip is full anyway
+// and fewer tiles mean a shorter look-back.
 constexpr int kPassWaves = kPassThreads / 64;
+static_assert(kPassThreads == 256, "four waves");
 constexpr uint64_t kPassSum = (1ull << 40) - 1;
 
 // Sum of the tiles before `tile`; publishes this tile's own (whole wave calls it).
@@ -56,9 +59,10 @@ __device__ __forceinline__ uint64_t pass_look_back(uint64_t* status, uint64_t ep
   return excl;
 }
 
-// The whole grid (one workgroup of kPassThreads per tile) scans n elements.
+// The whole grid (one workgroup of kPassThreads per tile of kPassThreads * ROWS)
+// scans n elements.
 // Values whose bit is set in FLAGS are 0 or 1.  f.total(sums) runs once.
-template <int NV, uint32_t FLAGS, class F>
+template <int NV, uint32_t FLAGS, int ROWS, class F>
 __device__ __forceinline__ void scan_pass(uint64_t n, const ScanDev& sd, F&& f) {
   __shared__ uint64_t s_w[NV][kPassWaves];
   __shared__ uint64_t s_ex[NV];
@@ -70,12 +74,12 @@ __device__ __forceinline__ void scan_pass(uint64_t n, const ScanDev& sd, F&& f) 
     __syncthreads();
     tile = s_tile;
   }
-  const uint64_t wbase = tile * kPassTile + (uint64_t)wv * (64 * kPassRows);
-  uint64_t v[kPassRows][NV], ex[kPassRows][NV], run[NV];
+  const uint64_t wbase = (tile * kPassWaves + wv) * (64 * ROWS);
+  uint64_t v[ROWS][NV], ex[ROWS][NV], run[NV];
 #pragma unroll
   for (int q = 0; q < NV; ++q) run[q] = 0;
 #pragma unroll
-  for (int k = 0; k < kPassRows; ++k) {
+  for (int k = 0; k < ROWS; ++k) {
     const uint64_t i = wbase + 64ull * k + lane;
 #pragma unroll
     for (int q = 0; q < NV; ++q) v[k][q] = 0;
@@ -129,7 +133,7 @@ __device__ __forceinline__ void scan_pass(uint64_t n, const ScanDev& sd, F&& f) 
     }
   }
 #pragma unroll
-  for (int k = 0; k < kPassRows; ++k) {
+  for (int k = 0; k < ROWS; ++k) {
     const uint64_t i = wbase + 64ull * k + lane;
 #pragma unroll
     for (int q = 0; q < NV; ++q) ex[k][q] += before[q];

@@ -1,5 +1,5 @@
-"""The level passes' one-launch prefix sums at the edges of their tiles of 2048
-elements: levels of 2047 to 4097 blocks, batches of 1 to 2049 texts, and empty
+"""The level passes' one-launch prefix sums at the edges of their tiles (256, 512
+and 2048 elements by the level's size): levels of 1 to 2^21 + 1 blocks, batches of 1 to 2049 texts, and empty
 texts that enter a level with the others (root_block_len)."""
 import numpy as np
 import pytest
@@ -49,4 +49,17 @@ def test_texts_at_tile_edges(count):
         for T, t in zip(texts, trees):
             assert t.serialize() == oracle.build_tree(T, tau, leaf, b1=b1).canonical
         bt.free_trees(trees)
+    ctx.close()
+
+
+@pytest.mark.parametrize("blocks", [255, 256, 257, 511, 65537, (1 << 18) - 1, (1 << 18) + 1, (1 << 21) - 3, (1 << 21) + 1])
+def test_blocks_at_row_edges(blocks):
+    torch_cuda()
+    import paper_2512_23314_amd as bt
+    T = synth.random_text(4 * blocks - 1, 250, blocks)
+    T[blocks:blocks + blocks // 3] = T[:blocks // 3]
+    ctx = bt.Context(0)
+    t = ctx.build(to_device(T), tau=2, leaf_len=2)
+    assert t.serialize() == oracle.build_tree_par(T, 2, 2).canonical
+    t.free()
     ctx.close()
