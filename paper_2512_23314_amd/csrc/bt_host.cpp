@@ -805,7 +805,7 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
     Buf<uint8_t> byte_of = alloc<uint8_t>(ctx, S);
     upload(ctx, byte_of.p, h_byte_of.data(), S);
     const uint64_t K = (N + kRankQ - 1) / kRankQ;
-    const uint64_t nblk = (K + 1023) / 1024;
+    const uint64_t nblk = (K + kRankColRows - 1) / kRankColRows;
     Buf<uint32_t> H = alloc<uint32_t>(ctx, std::max<uint64_t>(K, 1) * S);
     Buf<uint64_t> B = alloc<uint64_t>(ctx, std::max<uint64_t>(nblk, 1) * S);
     d_G = alloc<uint64_t>(ctx, (K + 1) * S);

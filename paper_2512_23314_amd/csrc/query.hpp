@@ -46,6 +46,7 @@ struct QTree {
 
 // Rank support construction.
 constexpr uint64_t kRankQ = 1024;  // sampling interval of the count table
+constexpr uint64_t kRankColRows = 64;  // its rows per block of the column scan
 struct RankCtx {
   const uint8_t* T;        // the build's buffer
   uint64_t o0;             // first position covered by the table
