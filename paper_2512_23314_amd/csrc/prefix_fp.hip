@@ -23,8 +23,9 @@
 //      folds of step 1) goes to LDS; then, row by row (16 bytes per thread), each
 //      thread runs 16 Horner steps from one of them (one multiply-add per
 //      output), and each wave stages its outputs in LDS so that its stores are
-//      lane-contiguous.  The sampled form stores every 16th value only:
-//      P[16 q] for 16 q <= n (and, with sampled hashes, H[16 q] likewise).
+//      lane-contiguous.  The every-4th form runs them from the thread's own
+//      values, staged the same way.  The sampled form stores every 16th value
+//      only: P[16 q] for 16 q <= n (and, with sampled hashes, H[16 q] likewise).
 // Tile order comes from the counter, so a tile waits only on tiles that
 // running workgroups hold.  The text is read once for both results.
 #include "common.hpp"
@@ -300,21 +301,38 @@ __global__ __launch_bounds__(kPfThreads) __attribute__((amdgpu_waves_per_eu(2)))
           if (pos + kPfBytes == n) P[n >> 4] = mad61(C, tb->t61[1], h61);
         }
       } else if (Q4) {
-        // every 4th: from each P[pos + 16 c], four Horner steps at a time
-        if (pos <= n) {
+        // every 4th: from each P[pos + 16 c], four Horner steps at a time, eight
+        // values (32 bytes of text) per thread staged in LDS so that the wave
+        // stores runs of eight (64 bytes).  Stored by the threads themselves, 128
+        // bytes apart, every store instruction was 64 part-line writes (a 2 GiB
+        // build: 89.3 -> 87.4 ms)
+        uint64_t* so = s_out + wv * 64 * 9;
+        const uint64_t w0 = (tile * kPfTile + 4096 * (uint64_t)wv) >> 2;  // the wave's first
 #pragma unroll
-          for (int c = 0; c < 4; ++c) {
+        for (int h = 0; h < 2; ++h) {
+#pragma unroll
+          for (int e = 0; e < 2; ++e) {
+            const int c = 2 * h + e;
             uint64_t val = v[c];
 #pragma unroll
             for (int d = 0; d < 4; ++d) {
-              const uint64_t q = pos + 16 * c + 4 * d;
-              if (q <= n) P[q >> 2] = val;
+              so[lane * 9 + 4 * e + d] = val;
               if (d < 3) {
 #pragma unroll
-                for (int e = 0; e < 4; ++e) val = mad61(val, x1, byte_at(16 * c + 4 * d + e));
+                for (int k = 0; k < 4; ++k) val = mad61(val, x1, byte_at(16 * c + 4 * d + k));
               }
             }
           }
+          wave_sync();
+#pragma unroll
+          for (int m = 0; m < 8; ++m) {
+            const int e = 64 * m + lane;  // row e / 8, value e % 8
+            const uint64_t i = w0 + 16 * (uint64_t)(e >> 3) + 8 * h + (e & 7);
+            if (4 * i <= n) P[i] = so[(e >> 3) * 9 + (e & 7)];
+          }
+          wave_sync();
+        }
+        if (pos <= n) {
           if (pos + kPfBytes == n) P[n >> 2] = mad61(C, tb->t61[1], h61);
         }
       } else {
