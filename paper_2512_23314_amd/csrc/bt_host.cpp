@@ -1160,7 +1160,7 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
   }
 
   // Runs of the first level: one per non-empty text that enters there.  Each
-  // later level's count comes from the level before it (k_mark_facts), so no
+  // later level's count comes from the level before it (k_marks), so no
   // level waits for its own count; the device's count is checked against it
   // at the level's first read-back.
   uint64_t R_pred = 0;
@@ -1215,12 +1215,12 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
     Buf<uint32_t> tseg;
     Buf<uint8_t> facts = alloc<uint8_t>(ctx, c);
     Buf<uint32_t> vlist = alloc<uint32_t>(ctx, c),
-                  vmis = alloc<uint32_t>(ctx, 2 * b > kSettleMax ? c : 0);
+                  kdone = alloc<uint32_t>(ctx, 2 * b > kSettleMax ? c : 0);
     Buf<uint64_t> vbest = alloc<uint64_t>(ctx, c);
     Buf<uint8_t> marked = alloc<uint8_t>(ctx, c);
     int scan_mode = 1;
     uint32_t fbits = 12;
-    VerifyBufs vb{vlist.p, vbest.p, vmis.p, scr.vcnt.p};
+    VerifyBufs vb{vlist.p, vbest.p, scr.vcnt.p};
     uint64_t* const oddb = scr.oddb.p;
 
     PhaseArgs a{};
@@ -1236,7 +1236,7 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
     a.x32inv = host_inv32(x32);
     a.tx = tx;
     a.lv = lv;
-    a.k = KeysDev{kfp.p, klen.p, kslot.p, klm.p, nullptr};
+    a.k = KeysDev{kfp.p, klen.p, kslot.p, klm.p, nullptr, nullptr};
     a.odd = OddDev{oddb,         oddb + T,     oddb + 2 * T, oddb + 3 * T,
                    oddb + 4 * T, oddb + 5 * T, oddb + 6 * T, oddb + 7 * T};
     a.x32 = x32;
@@ -1259,6 +1259,7 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
       if (phase == 2 && nkeys == 0) return;  // nothing of the phase is read
       a.Lmain = phase == 1 ? 2 * b : b;
       a.xLmain = host_pow61(x, a.Lmain);
+      a.k.done = a.Lmain > kSettleMax ? kdone.p : nullptr;
       // The scan tests the 32-bit pre-filter hash against the LDS filter and
       // queues its candidates (mode 1); from 2^14 keys on, where the LDS filter
       // starts to pass a sizeable share of the windows, those also test a blocked
@@ -1415,13 +1416,7 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
                             : scan_rounds(as, swoff, rounds, tile_segs ? tseg.p : nullptr, !piece_segs);
         }, a.Lmain);
       }
-      if (a.Lmain <= kSettleMax) {
-        timed(ctx, "verify", 0, 0, nullptr, 0, [&] { return launch_settle(a, vb, a.Lmain, s); });
-      } else {
-        HIPCHK(ctx, launch_resolve(a, vb, s));
-        timed(ctx, "verify", 0, 0, nullptr, 0, [&] { return launch_verify(a, vb, a.Lmain, s); });
-        HIPCHK(ctx, launch_finish(a, vb, s));
-      }
+      timed(ctx, "verify", 0, 0, nullptr, 0, [&] { return launch_settle(a, vb, a.Lmain, s); });
       if (a.pc) HIPCHK(ctx, launch_phase_record(a.pc, wst, vb, s));
     };
 

@@ -71,6 +71,7 @@ struct KeysDev {
   uint32_t* slot;   // [c] table slot, kNoKey, kOddKey or kCopyKey
   uint64_t* lm;     // [c] leftmost occurrence (result)
   uint32_t* h32;    // [c] 32-bit hash of a main-length key, for launch_refilter; or null
+  uint32_t* done;   // [c] chunks compared (low half) and differing (high), or null; 0 at first
 };
 
 // Keys whose length differs from the phase's main length (at most one per
@@ -318,24 +319,18 @@ hipError_t launch_fold_filters(const PhaseArgs& a, const uint32_t* big, uint32_t
 // room for the filter and the queues in the CU's 160 KiB).
 constexpr uint32_t kTextFilterLdsLog2 = 15;
 
-// Phases of keys of at most this many bytes: resolved, verified and settled in
-// one launch (launch_settle); longer ones through a list (launch_resolve, _verify,
-// _finish).
+// Phases of keys of at most this many bytes are verified a key at a time; longer
+// ones in chunks of at least this size (KeysDev.done counts a key's).
 constexpr uint64_t kSettleMax = 4096;
 struct VerifyBufs {
   uint32_t* vlist;  // [c]
   uint64_t* vbest;  // [c]
-  uint32_t* vmis;   // [c] (longer keys only)
-  uint64_t* counts; // [2]: keys verified (profiling only in launch_settle), collisions
+  uint64_t* counts; // [2]: keys verified (profiling only), collisions
 };
 hipError_t launch_settle(const PhaseArgs& a, const VerifyBufs& v, uint64_t max_len, hipStream_t s);
-hipError_t launch_resolve(const PhaseArgs& a, const VerifyBufs& v, hipStream_t s);
 // Profiling: copy the phase's window count and verification counts into pc.
 hipError_t launch_phase_record(uint64_t* pc, const uint64_t* windows, const VerifyBufs& v,
                                hipStream_t s);
-hipError_t launch_verify(const PhaseArgs& a, const VerifyBufs& v, uint64_t max_len,
-                         hipStream_t s);
-hipError_t launch_finish(const PhaseArgs& a, const VerifyBufs& v, hipStream_t s);
 
 // The passes over a level's blocks (level_pass.hip).
 // Runs of a level: run ids, the run table, and the number of runs (or null).

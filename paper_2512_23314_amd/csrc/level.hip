@@ -104,6 +104,7 @@ __global__ void k_keys(PhaseArgs a) {
     const uint64_t fp = finish_fp(win61_any(a, st, L, xp), a.tx.tsalt[t], a.fpmask);
     a.k.fp[j] = fp;
     a.k.len[j] = L;
+    if (a.k.done) a.k.done[j] = 0;
     // (a flag: written once, not by every key of the text into one word)
     if (!a.odd.nkeys[t]) a.odd.nkeys[t] = 1;
     if (L == a.Lmain) {
@@ -969,7 +970,7 @@ hipError_t launch_byte_scan(const PhaseArgs& a, const uint64_t* woff, bool has_o
   return hipGetLastError();
 }
 
-// ---------------------------------------------------------------- resolve / verify / retry
+// ---------------------------------------------------------------- verification
 //
 // A key whose slot minimum is its own position is its own leftmost occurrence;
 // any other compares its bytes with the slot's position (verification), and a
@@ -991,10 +992,24 @@ hipError_t launch_phase_record(uint64_t* pc, const uint64_t* windows, const Veri
   return hipGetLastError();
 }
 
-// One wave compares up to 4 KiB of a key with the candidate occurrence.
+// One wave compares bytes [off, end) of a key with the candidate occurrence, 4 KiB
+// requested together.
 __device__ __forceinline__ bool wave_bytes_differ(const uint8_t* __restrict__ T, uint64_t a0,
                                                   uint64_t b0, uint64_t off, uint64_t end) {
   bool diff = false;
+  for (; off + 4096 <= end; off += 4096) {
+    const uint64_t o = off + (uint64_t)lane_id() * 16;
+    uint4 x[4], y[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      x[e] = load16(T + a0 + o + 1024 * e);
+      y[e] = load16(T + b0 + o + 1024 * e);
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      diff |= (x[e].x != y[e].x) | (x[e].y != y[e].y) | (x[e].z != y[e].z) | (x[e].w != y[e].w);
+    if (__any(diff)) return true;
+  }
   for (uint64_t o = off + (uint64_t)lane_id() * 16; o < end; o += 64 * 16) {
     if (o + 16 <= end) {
       const uint4 x = load16(T + a0 + o);
@@ -1039,6 +1054,16 @@ __device__ uint64_t wave_walk(const PhaseArgs& a, uint64_t j, uint64_t lb) {
 
 __device__ __forceinline__ uint64_t slot_best(const PhaseArgs& a, uint64_t j, uint32_t s) {
   return s == kOddKey ? a.odd.best[a.lv.text[j]] : a.tab.slots[s].best;
+}
+
+// Profiling: add each wave's count n to *p, one update per workgroup (they serialize).
+__device__ __forceinline__ void block_count(uint64_t* p, uint64_t n) {
+  __shared__ unsigned long long s_n;
+  if (threadIdx.x == 0) s_n = 0;
+  __syncthreads();
+  if (lane_id() == 0 && n) atomicAdd(&s_n, (unsigned long long)n);
+  __syncthreads();
+  if (threadIdx.x == 0 && s_n) atomicAdd((unsigned long long*)p, s_n);
 }
 
 // Keys of at most kVChunk bytes: resolved, verified and settled in one launch
@@ -1132,14 +1157,7 @@ __global__ __launch_bounds__(256) void k_settle(PhaseArgs a, VerifyBufs v) {
       v.vbest[at] = best;
     }
   }
-  if (a.pc) {  // profiling: one update per workgroup (they serialize)
-    __shared__ unsigned long long s_n;
-    if (threadIdx.x == 0) s_n = 0;
-    __syncthreads();
-    if (lane == 0 && verified) atomicAdd(&s_n, (unsigned long long)verified);
-    __syncthreads();
-    if (threadIdx.x == 0 && s_n) atomicAdd((unsigned long long*)&v.counts[0], s_n);
-  }
+  if (a.pc) block_count(&v.counts[0], verified);
 }
 
 // The walks of the keys that failed (counts[1] of them listed), one wave each.
@@ -1154,8 +1172,76 @@ __global__ __launch_bounds__(256) void k_walk(PhaseArgs a, VerifyBufs v) {
   }
 }
 
+// Longer keys, in chunks of at least kVChunk bytes: item (j, chunk) is one wave's, and
+// the wave that ends a key's last chunk (KeysDev.done) settles it, or walks.  A lane
+// looks its item up and the wave then takes those to compare in turn, so keys that
+// are their own first occurrence cost a lane only; items of a wave are a grid apart,
+// which spreads runs of keys to compare over the chip.  At most kMaxChunks chunks a
+// key: its waves' counter updates serialize.  Bound by the launch at these lengths (few
+// keys).  One launch in place of a list of the keys, its comparison and its results:
+// 1 MiB build 1.44 -> 1.32 ms; from 16 MiB on, where the host is behind on these
+// levels anyway, 0 to 1%.
+constexpr uint64_t kMaxChunks = 2048;  // below 2^16: KeysDev.done counts in 16 bits
+
+__global__ __launch_bounds__(256) void k_settle_long(PhaseArgs a, VerifyBufs v, uint64_t cpk,
+                                                     uint64_t chunk) {
+  const int lane = lane_id();
+  const uint64_t items = a.lv.c * cpk;
+  const uint64_t gw = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+  const uint64_t nw = ((uint64_t)gridDim.x * blockDim.x) >> 6;
+  uint64_t verified = 0;
+  for (uint64_t i0 = gw; i0 < items; i0 += nw * 64) {
+    const uint64_t it = i0 + (uint64_t)lane * nw;
+    bool need = false, other = false;
+    uint64_t j = 0, off = 0, best = 0, pos = 0, L = 0;
+    if (it < items) {
+      j = it / cpk;
+      off = (it - j * cpk) * chunk;
+      const uint32_t s = a.k.slot[j];
+      if (s != kNoKey && s != kCopyKey) {
+        pos = a.lv.st[j];
+        L = a.k.len[j];
+        best = slot_best(a, j, s);
+        other = best < a.tx.tstart[a.lv.text[j]];  // hit in another text: a collision
+        need = best != pos && off < L;
+        if (best == pos && off == 0) a.k.lm[j] = pos;
+      }
+    }
+    verified += (uint64_t)__popcll(__ballot(need && off == 0));
+    for (uint64_t m = __ballot(need); m; m &= m - 1) {
+      const uint32_t src = (uint32_t)(__ffsll((unsigned long long)m) - 1);
+      const uint64_t kj = shfl64(j, src), ko = shfl64(off, src), kl = shfl64(L, src);
+      const uint64_t kb = shfl64(best, src), kp = shfl64(pos, src);
+      bool bad = __shfl((int)other, (int)src) != 0;
+      if (!bad) bad = wave_bytes_differ(a.T, kb, kp, ko, kl - ko < chunk ? kl : ko + chunk);
+      const uint32_t nch = (uint32_t)((kl + chunk - 1) / chunk);
+      if (nch > 1) {
+        uint32_t old = 0;
+        if (lane == 0) old = atomicAdd(&a.k.done[kj], bad ? 0x10001u : 1u);
+        old = __shfl(old, 0);
+        if ((old & 0xFFFFu) + 1 < nch) continue;
+        bad |= (old >> 16) != 0;
+      }
+      uint64_t found = kb;
+      if (bad) {
+        const uint64_t ts = a.tx.tstart[a.lv.text[kj]];
+        found = wave_walk(a, kj, kb + 1 > ts ? kb + 1 : ts);
+        if (lane == 0) atomicAdd((unsigned long long*)&v.counts[1], 1ull);
+      }
+      if (lane == 0) a.k.lm[kj] = found;
+    }
+  }
+  if (a.pc) block_count(&v.counts[0], verified);
+}
+
 hipError_t launch_settle(const PhaseArgs& a, const VerifyBufs& v, uint64_t max_len, hipStream_t s) {
-  if (max_len > kVChunk) return hipErrorInvalidValue;
+  if (max_len > kVChunk) {
+    const uint64_t chunk = ((max_len + kMaxChunks - 1) / kMaxChunks + kVChunk - 1) / kVChunk * kVChunk;
+    const uint64_t cpk = (max_len + chunk - 1) / chunk;
+    if (!a.k.done) return hipErrorInvalidValue;
+    k_settle_long<<<grid_for(a.lv.c * cpk * 64, 256, 2048), 256, 0, s>>>(a, v, cpk, chunk);
+    return hipGetLastError();
+  }
   const unsigned g = grid_for(a.lv.c, 256, 8192);
   // lanes per key: about one 16-byte word per lane, at least 4 lanes
   if (max_len <= 64) k_settle<4><<<g, 256, 0, s>>>(a, v);
@@ -1164,115 +1250,6 @@ hipError_t launch_settle(const PhaseArgs& a, const VerifyBufs& v, uint64_t max_l
   else if (max_len <= 512) k_settle<32><<<g, 256, 0, s>>>(a, v);
   else k_settle<64><<<g, 256, 0, s>>>(a, v);
   k_walk<<<grid_for(a.lv.c * 64, 256, 1024), 256, 0, s>>>(a, v);
-  return hipGetLastError();
-}
-
-// Longer keys: the ones to verify go to a list first, so that their bytes can be
-// shared out in chunks.  Returning atomics on one address serialize (about 10 ns
-// apart), so a 1024-thread workgroup claims its whole share of the list with a
-// single update.
-constexpr int kResolveThreads = 1024;
-
-__global__ __launch_bounds__(kResolveThreads) void k_resolve(PhaseArgs a, VerifyBufs v) {
-  __shared__ uint32_t s_w[kResolveThreads / 64];
-  __shared__ unsigned long long s_base;
-  const int lane = lane_id();
-  const int wv = threadIdx.x >> 6;
-  const uint64_t c = a.lv.c;
-  for (uint64_t j0 = (uint64_t)blockIdx.x * kResolveThreads; j0 < c;
-       j0 += (uint64_t)gridDim.x * kResolveThreads) {
-    const uint64_t j = j0 + threadIdx.x;
-    bool need = false;
-    uint64_t best = 0;
-    if (j < c) {
-      const uint32_t s = a.k.slot[j];
-      if (s != kNoKey && s != kCopyKey) {
-        const uint64_t pos = a.lv.st[j];
-        best = slot_best(a, j, s);
-        if (best == pos) a.k.lm[j] = pos;
-        else need = true;
-      }
-    }
-    const uint64_t bal = __ballot(need);
-    if (lane == 0) s_w[wv] = (uint32_t)__popcll(bal);
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      uint32_t tot = 0;
-      for (int q = 0; q < kResolveThreads / 64; ++q) {
-        const uint32_t n = s_w[q];
-        s_w[q] = tot;
-        tot += n;
-      }
-      s_base = tot ? atomicAdd((unsigned long long*)&v.counts[0], (unsigned long long)tot) : 0ull;
-    }
-    __syncthreads();
-    if (need) {
-      const uint64_t idx = s_base + s_w[wv] + __popcll(bal & ((1ull << lane) - 1));
-      v.vlist[idx] = (uint32_t)j;
-      v.vbest[idx] = best;
-      v.vmis[idx] = 0;
-    }
-    __syncthreads();  // s_w and s_base are reused
-  }
-}
-
-hipError_t launch_resolve(const PhaseArgs& a, const VerifyBufs& v, hipStream_t s) {
-  k_resolve<<<grid_for(a.lv.c, kResolveThreads, 2048), kResolveThreads, 0, s>>>(a, v);
-  return hipGetLastError();
-}
-
-// Items are (key, 4 KiB chunk) pairs; one wave compares one, 16 bytes per lane
-// per step.
-__global__ __launch_bounds__(256) void k_verify(PhaseArgs a, VerifyBufs v, uint64_t cpk) {
-  const uint64_t items = v.counts[0] * cpk;
-  const uint64_t gw = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-  const uint64_t nw = ((uint64_t)gridDim.x * blockDim.x) >> 6;
-  for (uint64_t it = gw; it < items; it += nw) {
-    const uint64_t idx = it / cpk;
-    const uint64_t off = (it - idx * cpk) * kVChunk;
-    const uint32_t j = v.vlist[idx];
-    const uint64_t best = v.vbest[idx];
-    const uint64_t L = a.k.len[j];
-    bool diff;
-    if (best < a.tx.tstart[a.lv.text[j]]) diff = true;  // hit in another text: a collision
-    else if (off >= L) continue;
-    else diff = wave_bytes_differ(a.T, best, a.lv.st[j], off, L - off < kVChunk ? L : off + kVChunk);
-    if (diff && lane_id() == 0) v.vmis[idx] = 1;
-  }
-}
-
-hipError_t launch_verify(const PhaseArgs& a, const VerifyBufs& v, uint64_t max_len,
-                         hipStream_t s) {
-  const uint64_t cpk = (max_len + kVChunk - 1) / kVChunk;
-  k_verify<<<grid_for(a.lv.c * cpk * 64, 256, 2048), 256, 0, s>>>(a, v, cpk);
-  return hipGetLastError();
-}
-
-// The list's results: a wave takes 64 keys, one per lane, and walks for each of
-// those that failed in turn.
-__global__ __launch_bounds__(256) void k_finish(PhaseArgs a, VerifyBufs v) {
-  const uint64_t cnt = v.counts[0];
-  for (uint64_t i0 = ((uint64_t)blockIdx.x * 256 + (threadIdx.x & ~63u)); i0 < cnt;
-       i0 += (uint64_t)gridDim.x * 256) {
-    const uint64_t idx = i0 + lane_id();
-    bool bad = false;
-    if (idx < cnt) {
-      bad = v.vmis[idx] != 0;
-      if (!bad) a.k.lm[v.vlist[idx]] = v.vbest[idx];
-    }
-    uint64_t m = __ballot(bad);
-    if (m && lane_id() == 0) atomicAdd((unsigned long long*)&v.counts[1], (unsigned long long)__popcll(m));
-    for (; m; m &= m - 1) {
-      const uint64_t i = i0 + (uint64_t)__ffsll((unsigned long long)m) - 1;
-      const uint64_t j = v.vlist[i], ts = a.tx.tstart[a.lv.text[j]], lb = v.vbest[i] + 1;
-      const uint64_t found = wave_walk(a, j, lb > ts ? lb : ts);
-      if (lane_id() == 0) a.k.lm[j] = found;
-    }
-  }
-}
-
-hipError_t launch_finish(const PhaseArgs& a, const VerifyBufs& v, hipStream_t s) {
-  k_finish<<<grid_for(a.lv.c, 256), 256, 0, s>>>(a, v);
   return hipGetLastError();
 }
 
