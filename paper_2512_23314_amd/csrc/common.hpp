@@ -127,9 +127,10 @@ __device__ __forceinline__ uint32_t tfilter_has(uint32_t w, uint32_t p, uint32_t
 
 // Filter bit of a string's first eight bytes (lo = bytes 0..3, hi = bytes
 // 4..7, little endian) in a filter of 2^bits bits: equal strings of length 8 or
-// more share it.  The top bits of each product depend on every bit of its word.
+// more share it.  The rotation puts the bits in which DNA letters differ (0 to 2 and
+// 4) on others for hi than for lo, so that such strings stay apart in the sum.
 __device__ __forceinline__ uint32_t prefix8_bit(uint32_t lo, uint32_t hi, uint32_t bits) {
-  return ((lo * 0x9E3779B1u) ^ (hi * 0x85EBCA77u)) >> (32 - bits);
+  return ((lo ^ (hi << 13 | hi >> 19)) * 0x9E3779B1u) >> (32 - bits);
 }
 
 // P[i] from prefix fingerprints sampled every 2^sh positions (Ps[q] = P[base +

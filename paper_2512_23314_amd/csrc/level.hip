@@ -757,11 +757,16 @@ hipError_t launch_probe_scan(const PhaseArgs& a, const uint64_t* woff, bool has_
 // first eight bytes) go to the per-wave LDS queue of the probe scan and form
 // their 61-bit fingerprints 64 at a time.
 //
-// A wave takes 1024 consecutive window numbers; lane l takes 16 consecutive
-// ones.  When they lie in one segment the lane loads the 28 aligned bytes that
-// cover them and takes each window's eight bytes with byte-aligns.
+// A wave takes 2048 consecutive window numbers; lane l takes 32 consecutive
+// ones.  When they lie in one segment the lane loads the 44 aligned bytes that
+// cover them and takes each window's eight bytes with byte-aligns.  Bound by the
+// bytes in flight (a segment search, a load and 32 tests per wave and round) and
+// by the candidates: with 16 windows per lane, and the candidates queued in a step
+// per window, 2 GiB of DNA took 1.02 / 1.37 / 1.83 ms with 4 / 16 / 64 keys
+// (now 0.67 / 0.85 / 1.07); one multiplication per test in place of two, and one search per wave
+// in place of one per lane, changed nothing by themselves.
 constexpr int kByteThreads = 1024;
-constexpr int kByteK = 16;  // windows per lane
+constexpr int kByteK = 32;  // windows per lane
 // Queue entries: position in bits 0..39, text in bits 40..62, and bit 63 set
 // when the main-length window does not fit its run.
 constexpr uint64_t kByteTextMask = (1ull << 23) - 1;
@@ -783,8 +788,8 @@ void k_byte_scan(PhaseArgs a, const uint64_t* __restrict__ woff) {
   uint64_t* q = s_lds + (1ull << (bits - 6)) + (uint64_t)(threadIdx.x >> 6) * kQueue;
   uint32_t qn = 0;  // wave-uniform queue length
   const uint64_t R = a.segn[0], W = a.segn[1];
-  const uint64_t gw = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-  const uint64_t nw = ((uint64_t)gridDim.x * blockDim.x) >> 6;
+  const uint32_t gw = __builtin_amdgcn_readfirstlane((blockIdx.x * blockDim.x + threadIdx.x) >> 6);
+  const uint32_t nw = (gridDim.x * blockDim.x) >> 6;
   const uint8_t* __restrict__ T = a.T;
   const uint64_t* __restrict__ P = a.P;
   const uint64_t L = a.Lmain, xL = a.xLmain, fmask = a.fpmask;
@@ -843,15 +848,21 @@ void k_byte_scan(PhaseArgs a, const uint64_t* __restrict__ woff) {
   for (uint64_t ch = gw; ch * (64ull * kByteK) < W; ch += nw) {
     const uint64_t w0 = ch * (64ull * kByteK) + (uint64_t)lane * kByteK;
     const bool any = w0 < W;  // lanes past the last window hold no segment
-    uint64_t r = 0, wo = 0, wn = 0, rs = 0, re = 0;
-    uint32_t t = 0;
-    if (any) {
-      uint64_t lo = 0, hi = R;
-      while (hi - lo > 1) {
-        const uint64_t mid = (lo + hi) >> 1;
-        if (woff[mid] <= w0) lo = mid; else hi = mid;
+    // the segment of the chunk's first window, once for the wave; lanes look for
+    // their own from there on only where the chunk does not lie in it
+    const uint64_t c0 = ch * (64ull * kByteK);
+    uint64_t r = 0;
+    for (uint64_t hi = R; hi - r > 1;) {
+      const uint64_t mid = (r + hi) >> 1;
+      if (woff[mid] <= c0) r = mid; else hi = mid;
+    }
+    uint64_t wo = woff[r], wn = woff[r + 1], rs = a.lv.rs[r], re = a.lv.re[r];
+    uint32_t t = a.lv.rtext[r];
+    if (c0 + 64ull * kByteK > wn && any) {
+      for (uint64_t hi = R; hi - r > 1;) {
+        const uint64_t mid = (r + hi) >> 1;
+        if (woff[mid] <= w0) r = mid; else hi = mid;
       }
-      r = lo;
       wo = woff[r];
       wn = woff[r + 1];
       rs = a.lv.rs[r];
@@ -859,24 +870,24 @@ void k_byte_scan(PhaseArgs a, const uint64_t* __restrict__ woff) {
       t = a.lv.rtext[r];
     }
     const uint64_t i0 = rs + (w0 - wo);
-    // the lane's 16 windows in one segment, all of main length inside the run
+    // the lane's 32 windows in one segment, all of main length inside the run
     const bool fast = any && w0 + (kByteK - 1) < wn && i0 + (kByteK - 1) + L <= re;
     uint32_t m = 0;  // bit k: window w0 + k passes
     if (fast) {
-      // The 28 bytes from the 4-byte aligned address at or below T + i0 cover
-      // [i0, i0 + 23).  They end inside the lane's last window, which ends at
-      // or before the run end (L >= 16 > 12: keys of the byte scan are blocks
-      // or pairs of blocks of b >= 16), and they start no lower than the
-      // aligned base of the allocation holding the text.
+      // The 44 bytes from the 4-byte aligned address at or below T + i0 cover
+      // [i0, i0 + 39).  They end inside the lane's last window, which starts 31
+      // bytes on and ends at or before the run end (31 + L >= 47: keys of the byte
+      // scan are pairs of blocks of b >= 16, or longer than one), and they start no
+      // lower than the aligned base of the allocation holding the text.
       const uintptr_t ad = reinterpret_cast<uintptr_t>(T + i0);
       const uint32_t* wp = reinterpret_cast<const uint32_t*>(ad & ~(uintptr_t)3);
-      uint32_t w[7];
+      uint32_t w[kByteK / 4 + 3];
 #pragma unroll
-      for (int k = 0; k < 7; ++k) w[k] = wp[k];
+      for (int k = 0; k < kByteK / 4 + 3; ++k) w[k] = wp[k];
       const uint32_t sh = (uint32_t)(ad & 3);
-      uint32_t x[6];  // x[k] = bytes [i0 + 4k, i0 + 4k + 4)
+      uint32_t x[kByteK / 4 + 2];  // x[k] = bytes [i0 + 4k, i0 + 4k + 4)
 #pragma unroll
-      for (int k = 0; k < 6; ++k) x[k] = __builtin_amdgcn_alignbyte(w[k + 1], w[k], sh);
+      for (int k = 0; k < kByteK / 4 + 2; ++k) x[k] = __builtin_amdgcn_alignbyte(w[k + 1], w[k], sh);
 #pragma unroll
       for (int k = 0; k < kByteK; ++k) {
         const int qq = k >> 2, o = k & 3;
@@ -898,22 +909,20 @@ void k_byte_scan(PhaseArgs a, const uint64_t* __restrict__ woff) {
         }
         // every window of a segment has at least 8 bytes before the run end
         const uint64_t i = rs2 + (wi - wo2);
-        uint32_t l4 = 0, h4 = 0;
-        for (int b = 0; b < 4; ++b) {
-          l4 |= (uint32_t)T[i + b] << (8 * b);
-          h4 |= (uint32_t)T[i + 4 + b] << (8 * b);
-        }
-        m |= (has(l4, h4) ? 1u : 0u) << k;
+        uint64_t v;
+        __builtin_memcpy(&v, T + i, 8);
+        m |= (has((uint32_t)v, (uint32_t)(v >> 32)) ? 1u : 0u) << k;
       }
     }
-    if (!__ballot(m != 0)) continue;  // most chunks hold no candidate
-    // queue the candidates, 16 wave-wide steps; lanes that walked segments
-    // walk them again, now with the run end and text of each window
-    for (int k = 0; k < kByteK; ++k) {
+    // queue the candidates, each lane's next one in a step: as many steps as the
+    // lane with the most has, one or two; lanes that walked segments walk them
+    // again, now with the run end and text of each window
+    while (__ballot(m != 0)) {
       uint64_t e = 0;
-      const bool c = (m >> k) & 1u;
+      const bool c = m != 0;
       if (c) {
-        const uint64_t wi = w0 + k;
+        const uint64_t wi = w0 + (uint32_t)__builtin_ctz(m);
+        m &= m - 1;
         if (!fast) {
           while (wi >= wn) {
             ++r;
