@@ -567,7 +567,7 @@ def summarize_stats(stats_dir, bench_json, cmd, out, top=20):
              "launch %.4f ms (HIP events on the library stream), %d launches per step." % (
                  b["value"], b["unit"], b["ms_per_step"], rf["avg_launch_ms"], rf["launches_per_step"]),
              "",
-             "rocprofv3: the probe scan (k_probe_scan and k_probe_text, all instantiations) %d "
+             "rocprofv3: the probe scan (k_probe_dense, k_probe_scan and k_probe_text) %d "
              "calls, average %.4f ms "
              "(ratio to the HIP-event average %.3f); warmup and timed steps launch the same "
              "kernels, so the averages compare." % (calls, pns / max(calls, 1) / 1e6,
@@ -583,8 +583,9 @@ def summarize_stats(stats_dir, bench_json, cmd, out, top=20):
     print("wrote", out)
 
 
-# the probe scan's kernels: the shared-filter scan and the per-text scan of batches
-PROBE_KERNELS = ("k_probe_scan<", "k_probe_text<")
+# the probe scan's kernels: the scans with one filter (single texts; lean and
+# unqueued ones) and the per-text scan of batches
+PROBE_KERNELS = ("k_probe_dense<", "k_probe_scan<", "k_probe_text<")
 
 
 def _counter_per_launch(d, needles):
