@@ -224,7 +224,7 @@ __device__ __forceinline__ void fill_share(const FillList& f, uint64_t tid, uint
     const uint32_t v = f.value[y];
     const uint64_t nq = (reinterpret_cast<uintptr_t>(p) & 15) == 0 ? n / 4 : 0;
     uint4* q = reinterpret_cast<uint4*>(p);
-    const uint4 vv = make_uint4(v, v, v, v);
+    const uint4 vv{v, v, v, v};
     for (uint64_t i = tid; i < nq; i += stride) q[i] = vv;
     for (uint64_t i = 4 * nq + tid; i < n; i += stride) p[i] = v;
   }
