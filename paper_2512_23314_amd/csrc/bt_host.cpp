@@ -1398,7 +1398,15 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
         // the tile must fetch are those of the union, so the partner read is
         // counted only for the part beyond the tile.
         const double per_value = a.pre32 ? 4.0 : 8.0;
-        const double partner = (double)std::min<uint64_t>(a.Lmain, kProbeTile) / (double)kProbeTile;
+        double partner = (double)std::min<uint64_t>(a.Lmain, kProbeTile) / (double)kProbeTile;
+        // a column walk reads the partner once per column (the widest part's rows: no
+        // launch reads less)
+        if (!text_local && scan_mode == 1 && a.P32) {
+          uint32_t part = 0, from = 0;
+          for (uint32_t to : rounds) part = std::max(part, to - from), from = to;
+          const uint64_t tiles = ((c * b + kProbeTile - 1) / kProbeTile * part + 63) / 64;
+          partner = std::min(partner, 1.0 / (double)probe_scan_rows(a.Lmain, tiles));
+        }
         // spans: at least four per resident workgroup (256) for the level's
         // window bound, 16 to 256 chunks, a multiple of the 16 waves
         uint64_t span_chunks = (c * b) / kProbeTile / (4 * 256);

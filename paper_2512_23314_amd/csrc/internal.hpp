@@ -291,6 +291,9 @@ constexpr uint64_t kTileSegsPiece = 32;
 hipError_t launch_probe_scan(const PhaseArgs& a, const uint64_t* woff, bool has_odd,
                              bool has_salt, uint64_t max_windows, int mode, uint32_t* tseg,
                              uint32_t f0, uint32_t f1, bool find_segs, hipStream_t s);
+// The rows of its column walk for windows of length L in that many tiles (1: none);
+// a launch reads (rows + 1) / rows values per window.
+uint64_t probe_scan_rows(uint64_t L, uint64_t tiles);
 // Between rounds (filters cleared by the caller): sets the filter bits of the
 // keys that windows from tile 64ths f0 on can still improve.
 hipError_t launch_refilter(const PhaseArgs& a, const uint64_t* woff, uint32_t f0, hipStream_t s);

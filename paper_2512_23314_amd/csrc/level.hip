@@ -693,7 +693,9 @@ static hipError_t allow_lds(const void* fn, size_t bytes) {
 
 // Rows of a column walk: as many as leave every resident wave (256 workgroups of
 // 16) four units, at most 16 (17/16 streams).
-static uint64_t column_rows(uint64_t tiles, uint64_t stride) {
+uint64_t probe_scan_rows(uint64_t L, uint64_t tiles) {
+  const uint64_t stride = L / kScanChunk;
+  if (L % kScanChunk || !stride || (stride >= tiles && stride > 1)) return 1;
   uint64_t rows = tiles / (4 * 256 * (kProbeThreads / 64));
   if (rows > 16) rows = 16;
   if (rows * stride > tiles) rows = tiles / stride;
@@ -725,8 +727,8 @@ hipError_t launch_probe_scan(const PhaseArgs& a, const uint64_t* woff, bool has_
   };
   if (mode == 1 && !lean) {
     if (tseg && f0 == 0 && find_segs) k_tile_segs<<<grid_for(all, 256), 256, 0, s>>>(woff, a.segn, tseg);
+    const uint64_t rows = probe_scan_rows(a.Lmain, tiles);
     const uint64_t stride = a.Lmain % kScanChunk == 0 && a.Lmain / kScanChunk < tiles ? a.Lmain / kScanChunk : 1;
-    const uint64_t rows = stride * kScanChunk == a.Lmain ? column_rows(tiles, stride) : 1;
     const unsigned grid = grid_for(tiles * 64, kProbeThreads, 256);
     const uint32_t* ts = tseg;
     if (has_odd)
