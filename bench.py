@@ -629,7 +629,7 @@ def summarize_traffic(fetch_dir, write_dir, cfetch_dir, cwrite_dir, copy_mib, be
               "| FETCH_SIZE, scaled | %.4g |" % fetch, "| WRITE_SIZE, scaled | %.4g |" % write,
               "| traffic (fetch + write) | %.4g |" % (fetch + write)]
     if algo:
-        lines += ["| algorithmic (the two prefix values per window: 8 B pre-filtered, 16 B "
+        lines += ["| algorithmic (the prefix values per window: 4 to 8 B pre-filtered, 16 B "
                   "otherwise) | %.4g |" % algo,
                   "| traffic / algorithmic | %.3f |" % ((fetch + write) / algo)]
     lines += ["", "Source hash (SHA-256 of %s, in that order): %s" % (", ".join(sources),
