@@ -824,16 +824,20 @@ void k_byte_scan(PhaseArgs a, const uint64_t* __restrict__ woff) {
       }
     }
   };
-  // whole wave: append the lanes' candidates; check 64 once 64 are waiting.
-  // Bit 63 of an entry: the main-length window does not fit the run.
+  // whole wave: append the lanes' candidates; check 64 once 64 are waiting, a full
+  // wave of them at once.  Bit 63 of an entry: the main-length window does not fit the run.
   uint64_t ncand = 0;  // wave-uniform: windows that passed the filter
   const auto push = [&](bool cand, uint64_t e) {
     const uint64_t bal = __ballot(cand);
     if (!bal) return;
+    ncand += (uint64_t)__popcll(bal);
+    if (bal == ~0ull) {
+      check(e);
+      return;
+    }
     const uint32_t my = (uint32_t)__popcll(bal & ((1ull << lane) - 1));
     if (cand) q[qn + my] = e;
     qn += (uint32_t)__popcll(bal);
-    ncand += (uint64_t)__popcll(bal);
     if (qn >= 64) {
       wave_sync();
       const uint64_t e0 = q[lane];
@@ -860,7 +864,9 @@ void k_byte_scan(PhaseArgs a, const uint64_t* __restrict__ woff) {
     }
     uint64_t wo = woff[r], wn = woff[r + 1], rs = a.lv.rs[r], re = a.lv.re[r];
     uint32_t t = a.lv.rtext[r];
-    if (c0 + 64ull * kByteK > wn && any) {
+    const bool whole = c0 + 64ull * kByteK <= wn;  // the chunk lies in that segment
+    const uint64_t e0 = ((uint64_t)t << kQPosBits) | (rs + (c0 - wo));  // its first window's entry
+    if (!whole && any) {
       for (uint64_t hi = R; hi - r > 1;) {
         const uint64_t mid = (r + hi) >> 1;
         if (woff[mid] <= w0) r = mid; else hi = mid;
@@ -915,6 +921,22 @@ void k_byte_scan(PhaseArgs a, const uint64_t* __restrict__ woff) {
         __builtin_memcpy(&v, T + i, 8);
         m |= (has((uint32_t)v, (uint32_t)(v >> 32)) ? 1u : 0u) << k;
       }
+    }
+    if (!__ballot(m != 0)) continue;  // most chunks hold no candidate
+    // Where many windows pass (runs and other strings that a key's first eight
+    // bytes repeat), a step takes windows one sample of the prefix fingerprints
+    // apart: the lanes read consecutive samples and add the same number of bytes to
+    // them.  (The lanes' next candidates lie 32 bytes apart, two to eight samples.)
+    // In chunks of one segment, from 16 lanes with a quarter of their windows each;
+    // below that the other order takes fewer steps.  64 MiB with one byte in 256 not
+    // zero: 8 launches at tau 2 13.4 -> 6.4 ms, 4 memory-lean ones 7.8 -> 6.0.
+    if (whole && __popcll(__ballot(fast && __popc(m) >= kByteK / 4)) >= 16) {
+      const uint32_t sh = LEAN ? a.pshift : 0;
+      for (uint32_t step = 0; step < kByteK; ++step) {
+        const uint32_t w = ((step >> sh) << (6 + sh)) + ((uint32_t)lane << sh) + (step & ((1u << sh) - 1));
+        push((__shfl(fast ? m : 0u, (int)(w / kByteK)) >> (w % kByteK)) & 1, e0 + w);
+      }
+      if (fast) m = 0;
     }
     // queue the candidates, each lane's next one in a step: as many steps as the
     // lane with the most has, one or two; lanes that walked segments walk them
