@@ -1,0 +1,75 @@
+"""Memory-lean scans for a text's short final key whose first bytes repeat all over the
+text (runs): lanes with at most two and with more such starts, with occurrences of the
+whole key, near-occurrences and none, in one text and in a batch."""
+import numpy as np
+import pytest
+
+import oracle
+import synth
+from tests.gpu_util import to_device, torch_cuda
+
+pytestmark = pytest.mark.gpu
+
+
+def _text(n, tail, run, copies, seed):
+    """Runs of `run` zeros and `run` random bytes; the last `tail` bytes and what is
+    before them start with zeros, and occur `copies` times before, once changed."""
+    rng = np.random.default_rng(seed)
+    T = synth.random_text(n, 250, seed)
+    T[np.arange(n) // run % 2 == 0] = 0
+    T[n - tail - 300:n - tail // 2] = 0
+    end = T[n - tail - 300:].copy()
+    for k in range(copies):
+        at = int(rng.integers(0, n - 3 * end.size))
+        T[at:at + end.size] = end
+        if k == 1:
+            T[at + end.size - 1] ^= 1
+    return T
+
+
+@pytest.mark.parametrize("run", [3, 10, 100, 3000])
+@pytest.mark.parametrize("tail", [5, 40, 700])
+def test_runs(run, tail):
+    torch_cuda()
+    import paper_2512_23314_amd as bt
+    ctx = bt.Context(0)
+    tau, leaf = 4, 64
+    b = leaf * tau ** 2
+    texts = [_text(60 * b + tail, tail, run, c, run + tail + c) for c in (0, 1, 3)]
+    want = [oracle.build_tree(T, tau, leaf).canonical for T in texts]
+    for flags in (0, bt.BT_DBG_WEAK_HASH, bt.BT_DBG_NO_BYTE_SCAN):
+        for T, w in zip(texts, want):
+            t = ctx.build(to_device(T), tau=tau, leaf_len=leaf, lean=True, debug_flags=flags)
+            assert t.serialize() == w
+            t.free()
+        off = np.concatenate([[0], np.cumsum([T.size for T in texts])]).astype(np.uint64)
+        trees = ctx.build_batch(to_device(np.concatenate(texts)), off, tau=tau, leaf_len=leaf, lean=True,
+                                debug_flags=flags)
+        assert [t.serialize() for t in trees] == want
+        bt.free_trees(trees)
+    ctx.close()
+
+
+def test_time_of_runs():
+    """The scans' time on a text that is zero but for every 256th byte, with a short
+    final key over without: LOW; with every start that shares the key's first eight bytes
+    tested by itself it was HIGH."""
+    torch_cuda()
+    import paper_2512_23314_amd as bt
+    n = (64 << 20) + 12345
+    rng = np.random.default_rng(1)
+    T = np.zeros(n, np.uint8)
+    T[rng.integers(0, n, n // 256)] = rng.integers(1, 255, n // 256)
+    ctx = bt.Context(0)
+    ms = []
+    for text in (T, T[:64 << 20]):
+        d, best = to_device(text), 1e9
+        for _ in range(4):
+            ctx.profile(True)
+            ctx.reset_stats()
+            ctx.build(d, tau=4, leaf_len=16, lean=True).free()
+            best = min(best, ctx.kernel_stats("probe_scan")["ms"])
+        ms.append(best)
+    ctx.close()
+    print("with, without a short key: %.2f %.2f ms, ratio %.2f" % (ms[0], ms[1], ms[0] / ms[1]))
+    assert ms[0] < 1.9 * ms[1]
