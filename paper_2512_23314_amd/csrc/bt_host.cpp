@@ -688,6 +688,7 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
   };
   std::vector<uint64_t> h_n(T), h_tcount(T, 0), h_tfirst(T + 1, 0);
   std::vector<uint32_t> id_first(H + 1, 0);  // entering texts of step k: ids [id_first[k], id_first[k+1])
+  std::vector<uint64_t> enter_most(H, 0);    // and the blocks of the longest
   const uint64_t tx_words = 5 * (uint64_t)T + 1 + (T + 1);
   Buf<uint64_t> d_tx = alloc<uint64_t>(ctx, tx_words);
   {
@@ -704,6 +705,7 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
       if (estep[t] == 0) h_tcount[t] = (h_n[t] + b_at(0) - 1) / b_at(0);
       h_tfirst[t + 1] = h_tfirst[t] + h_tcount[t];
       if (h_n[t]) ++id_first[estep[t] + 1];
+      enter_most[estep[t]] = std::max(enter_most[estep[t]], (h_n[t] + plan[t].b1 - 1) / plan[t].b1);
     }
     for (uint32_t k = 0; k < H; ++k) id_first[k + 1] += id_first[k];
     std::vector<uint32_t> at(id_first.begin(), id_first.end());
@@ -1152,7 +1154,7 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
   LevelScratch scr;
   {
     const NextLevel nl = alloc_next(c, E_ent, st, text, H == 1);
-    HIPCHK(ctx, launch_enter(d_ids, id_first[1], tx, b_at(0), tfp, 0, nl, s));
+    HIPCHK(ctx, launch_enter(d_ids, id_first[1], enter_most[0], tx, b_at(0), tfp, 0, nl, s));
     if (H > 1) {
       scr = make_scratch(c, b_at(0), h_tcount);
       HIPCHK(ctx, launch_fill_many(scr.fill, s));
@@ -1497,7 +1499,8 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
     HIPCHK(ctx, launch_split(a, facts.p, cs.p, ntfirst.p, bn, a.all_blocks, rnum.p, nl, sm,
                              prune ? nullptr : spb.p, spo.p, reinterpret_cast<uint32_t*>(d_err.p),
                              scr.fill, s));
-    HIPCHK(ctx, launch_enter(d_ids + id_first[step + 1], n_enter, tx, bn, ntfirst.p, c - u, nl, s));
+    HIPCHK(ctx, launch_enter(d_ids + id_first[step + 1], n_enter, enter_most[step + 1], tx, bn, ntfirst.p,
+                             c - u, nl, s));
 
     // ---- outputs of this level: marks (word range per text) and pointers
     if (!prune)

@@ -402,8 +402,9 @@ hipError_t launch_split(const PhaseArgs& a, const uint8_t* pf, const uint64_t* c
                         const uint64_t* ntfirst, uint64_t bn, uint32_t blocks, const uint32_t* rnum,
                         const NextLevel& o, const StoreMarks& m, uint64_t* pb, uint64_t* po,
                         uint32_t* err, const FillList& fill, hipStream_t s);
-// E texts that enter there (none empty), their entries from `base` on.
-hipError_t launch_enter(const uint32_t* ids, uint32_t E, const TextsDev& tx, uint64_t bn,
+// E texts that enter there (none empty, the longest of `most` blocks), their
+// entries from `base` on.
+hipError_t launch_enter(const uint32_t* ids, uint32_t E, uint64_t most, const TextsDev& tx, uint64_t bn,
                         const uint64_t* ntfirst, uint64_t base, const NextLevel& o, hipStream_t s);
 
 // Outputs.
