@@ -256,23 +256,28 @@ __global__ void k_select(QTree q, const uint8_t* __restrict__ cs, const uint64_t
         const uint64_t j0 = mk.before * q.tau;
         uint64_t nch = N.c - j0;
         if (nch > q.tau) nch = q.tau;
-        uint64_t x = 1, before = 0;
-        // four children at a time: their counts leave together
-        while (x < nch) {
-          uint64_t v[4];
+        // the last child with fewer than k before it, by quarters: a round's three
+        // counts leave together.  (Four counts at a time from the first child on
+        // took lines in proportion to the arity: 2^18 queries on 16 MiB, 250 symbols,
+        // tau 16 0.130 ms, now 0.093; tau 64, 200 symbols 0.30, now 0.107.)
+        uint64_t x = 0, before = 0;
+        while (nch > 1) {
+          const uint64_t step = (nch + 3) / 4;
+          uint64_t v[3];
 #pragma unroll
-          for (int e = 0; e < 4; ++e) v[e] = x + e < nch ? child_count(N, j0, x + e, S, s) : ~0ull;
-          int e = 0;
+          for (int e = 0; e < 3; ++e)
+            v[e] = (e + 1) * step < nch ? child_count(N, j0, x + (e + 1) * step, S, s) : ~0ull;
+          uint64_t skip = 0;
 #pragma unroll
-          for (int g = 0; g < 4; ++g)
-            if (e == g && v[g] < k) {
-              before = v[g];
-              e = g + 1;
+          for (int e = 0; e < 3; ++e)
+            if (v[e] < k) {  // (counts do not decrease)
+              before = v[e];
+              skip = (e + 1) * step;
             }
-          x += e;
-          if (e < 4) break;
+          x += skip;
+          nch = nch - skip < step ? nch - skip : step;
         }
-        j = j0 + x - 1;
+        j = j0 + x;
         k -= before;
       } else {
         const uint64_t u = j - mk.before;
