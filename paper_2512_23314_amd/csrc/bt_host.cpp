@@ -1173,6 +1173,11 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
     const bool leaf_step = (step == H - 1);
 
     if (leaf_step) {
+      // nothing scans the leaves: the memory of their facts and entries goes back
+      // before the outputs and the pruning take theirs
+      cflag.reset();
+      ent_f.reset();
+      for (auto* e : {&ent_a, &ent_e, &ent_child}) e->reset();
       if (!prune) {
         store_leaf_level(step, b, c, st.p, text.p, h_tcount, h_tfirst, tfp, tcp);
       } else {
