@@ -180,13 +180,12 @@ void k_probe_text(PhaseArgs a, const uint64_t* __restrict__ woff, uint64_t span_
       return LDS ? s_filt[block_word(p, lwl)] : tfw[toff + block_word(p, twl)];
     };
     // the text's short final key, if any (kept in registers while t holds):
-    // its length, the length, hash and power of its anchor
+    // its length, the hash and power of its anchor
     uint64_t oL = 0, opos = 0;
-    uint32_t oA = 0, oh = 0, ox = 0;
+    uint32_t oh = 0, ox = 0;
     const auto load_odd = [&]() {
       oL = a.odd.L[t];
       if (oL) {
-        oA = (uint32_t)(oL < kOddAnchor ? oL : kOddAnchor);
         opos = a.odd.pos[t];
         const uint64_t hx = a.odd.anc[t];
         oh = (uint32_t)hx;
@@ -194,6 +193,8 @@ void k_probe_text(PhaseArgs a, const uint64_t* __restrict__ woff, uint64_t span_
       }
     };
     if (ODD && w0 < W) load_odd();
+    // (the anchor's length is formed where it is used: held, it spilled two registers)
+    const auto anchor = [&]() { return oL < kOddAnchor ? oL : kOddAnchor; };
     // a window at i that matches the anchor: the whole key's 32-bit hash, then
     // its 61-bit fingerprint (text t)
     const auto odd61 = [&](uint64_t i, uint64_t sl) {
@@ -218,14 +219,14 @@ void k_probe_text(PhaseArgs a, const uint64_t* __restrict__ woff, uint64_t span_
           // together: the scheduler would otherwise pair each load with its
           // use and wait out every latency in turn
           uint32_t ha[kTlGroup], hb[kTlGroup], hc[kTlGroup];
-          // (and the short key's anchor's, H[i + oA], where the text has one)
+          // (and the short key's anchor's where the text has one)
           const bool oddk = ODD && oL;
 #pragma unroll
           for (int k = 0; k < kTlGroup; ++k) {
             const uint64_t i = i0 + 64ull * (k0 + k);
             hb[k] = H[i + L];
             ha[k] = H[i];
-            if (oddk) hc[k] = H[i + oA];
+            if (oddk) hc[k] = H[i + anchor()];
           }
           __builtin_amdgcn_sched_barrier(0);
           uint32_t hv[kTlGroup];
@@ -341,7 +342,7 @@ void k_probe_text(PhaseArgs a, const uint64_t* __restrict__ woff, uint64_t span_
         for (int k = 0; k < kTlSlowGroup; ++k) {
           hb[k] = ((vm >> k) & 1) ? H[ik[k] + L] : 0u;
           ha[k] = (((vm | om) >> k) & 1) ? H[ik[k]] : 0u;
-          if (ODD) hc[k] = ((om >> k) & 1) ? H[ik[k] + oA] : 0u;
+          if (ODD) hc[k] = ((om >> k) & 1) ? H[ik[k] + anchor()] : 0u;
         }
         __builtin_amdgcn_sched_barrier(0);
         if (ODD) {
@@ -412,7 +413,7 @@ void k_probe_text(PhaseArgs a, const uint64_t* __restrict__ woff, uint64_t span_
       // the short key: its anchor's hash first (equal strings always agree),
       // the whole key only where that matches
       if (ODD && live && oL && i + oL <= re && i < opos) {
-        const uint32_t ho = H[i + oA] - H[i] * ox + (uint32_t)salt;
+        const uint32_t ho = H[i + anchor()] - H[i] * ox + (uint32_t)salt;
         if (ho == oh) odd61(i, salt);
       }
     }
