@@ -831,24 +831,21 @@ void k_byte_scan(PhaseArgs a, const uint64_t* __restrict__ woff) {
     const uint64_t bal = __ballot(cand);
     if (!bal) return;
     ncand += (uint64_t)__popcll(bal);
-    if (bal == ~0ull) {
-      check(e);
-      return;
-    }
-    const uint32_t my = (uint32_t)__popcll(bal & ((1ull << lane) - 1));
-    if (cand) q[qn + my] = e;
-    qn += (uint32_t)__popcll(bal);
-    if (qn >= 64) {
+    if (bal != ~0ull) {
+      const uint32_t my = (uint32_t)__popcll(bal & ((1ull << lane) - 1));
+      if (cand) q[qn + my] = e;
+      qn += (uint32_t)__popcll(bal);
+      if (qn < 64) return;
       wave_sync();
-      const uint64_t e0 = q[lane];
+      e = q[lane];
       const bool mv = (uint32_t)lane < qn - 64;
       const uint64_t e2 = mv ? q[64 + lane] : 0;
       wave_sync();
       if (mv) q[lane] = e2;
       qn -= 64;
-      check(e0);
-      wave_sync();
     }
+    check(e);
+    wave_sync();
   };
 
   for (uint64_t ch = gw; ch * (64ull * kByteK) < W; ch += nw) {
@@ -865,7 +862,6 @@ void k_byte_scan(PhaseArgs a, const uint64_t* __restrict__ woff) {
     uint64_t wo = woff[r], wn = woff[r + 1], rs = a.lv.rs[r], re = a.lv.re[r];
     uint32_t t = a.lv.rtext[r];
     const bool whole = c0 + 64ull * kByteK <= wn;  // the chunk lies in that segment
-    const uint64_t e0 = ((uint64_t)t << kQPosBits) | (rs + (c0 - wo));  // its first window's entry
     if (!whole && any) {
       for (uint64_t hi = R; hi - r > 1;) {
         const uint64_t mid = (r + hi) >> 1;
@@ -930,8 +926,9 @@ void k_byte_scan(PhaseArgs a, const uint64_t* __restrict__ woff) {
     // In chunks of one segment, from 16 lanes with a quarter of their windows each;
     // below that the other order takes fewer steps.  64 MiB with one byte in 256 not
     // zero: 8 launches at tau 2 13.4 -> 6.4 ms, 4 memory-lean ones 7.8 -> 6.0.
-    if (whole && __popcll(__ballot(fast && __popc(m) >= kByteK / 4)) >= 16) {
+    if (__builtin_expect(whole && __popcll(__ballot(fast && __popc(m) >= kByteK / 4)) >= 16, 0)) {
       const uint32_t sh = LEAN ? a.pshift : 0;
+      const uint64_t e0 = ((uint64_t)t << kQPosBits) | (rs + (c0 - wo));  // the first window's entry
       for (uint32_t step = 0; step < kByteK; ++step) {
         const uint32_t w = ((step >> sh) << (6 + sh)) + ((uint32_t)lane << sh) + (step & ((1u << sh) - 1));
         push((__shfl(fast ? m : 0u, (int)(w / kByteK)) >> (w % kByteK)) & 1, e0 + w);
