@@ -412,8 +412,8 @@ __device__ __forceinline__ void store_marks(const uint8_t* marked, const StoreMa
 // per-text counts five a level.
 // WIDE (an arity of kWideSplit or more): a wave writes the children of one of its
 // blocks after another, 64 together; with fewer children a thread writes its own
-// block's.  A 16 MiB text, tau 65536: 2.92 -> 1.03 ms; tau 1024: 0.71 -> 0.30;
-// tau 64: 0.48 -> 0.43.
+// block's.  A 16 MiB text, tau 65536: 2.92 -> 1.1 ms; tau 1024: 0.71 -> 0.31;
+// tau 64: 0.47 -> 0.44.
 constexpr uint64_t kWideSplit = 64;
 template <bool WIDE>
 __global__ __launch_bounds__(256) void k_split(PhaseArgs a, const uint8_t* pf, const uint64_t* cs,
@@ -421,55 +421,72 @@ __global__ __launch_bounds__(256) void k_split(PhaseArgs a, const uint8_t* pf, c
                                                const uint32_t* rnum, NextLevel o, StoreMarks m,
                                                uint64_t* pb, uint64_t* po, uint32_t* err, FillList f) {
   const LevelDev lv = a.lv;
-  const int lane = lane_id();
-  // child k of a block at st, whose children start at `base`
-  const auto child = [&](uint64_t base, uint64_t k, uint64_t nk, uint64_t st, uint32_t t, uint32_t fl, uint32_t r) {
+  // block j: its pointer, or its entry and what `children` and `runs` do with its nk
+  // children from `base` on
+  const auto block = [&](uint64_t j, auto&& children, auto&& runs) {
+    if (!a.marked[j]) {
+      if (pb) write_pointer(a, j, a.marked, m.uoff, m.tfirst, pb, po, err);
+      return;
+    }
+    const uint32_t t = lv.text[j];
+    const uint64_t c0 = cs[j], nk = cs[j + 1] - c0, st = lv.st[j], te = a.tx.tend[t];
+    const uint64_t end = st + (te - st < lv.b ? te - st : lv.b);
+    const uint64_t base = ntfirst[t] + (c0 - cs[m.tfirst[t]]);
+    const bool again = blocks && a.k.slot[j] != kNoKey && a.k.lm[j] < st;
+    uint8_t fl = 0;
+    if (pf[j] & 1) fl |= kSkipCross;
+    if (again || (j > 0 && (pf[j - 1] & 1))) fl |= kSkipInterior;
+    children(base, nk, st, t, fl);
+    const uint64_t e = j - m.uoff[j];
+    o.ea[e] = st;
+    o.ee[e] = end;
+    o.ef[e] = fl;
+    o.echild[e] = base;
+    if (o.run) {
+      const uint32_t r = rnum[j], here = lv.run[j];
+      runs(base, nk, r);
+      if (j == 0 || lv.run[j - 1] != here || !a.marked[j - 1]) {
+        o.rs[r] = st;
+        o.rtext[r] = t;
+      }
+      if (j + 1 == lv.c || lv.run[j + 1] != here || !a.marked[j + 1]) o.re[r] = end;
+    }
+  };
+  const auto child = [&](uint64_t base, uint64_t k, uint64_t nk, uint64_t st, uint32_t t, uint8_t fl) {
     o.st[base + k] = st + k * bn;
     o.text[base + k] = t;
-    o.cflag[base + k] = (uint8_t)(fl ? fl | (k + 1 == nk ? kLastChild : 0) : 0);
-    if (o.run) o.run[base + k] = r;
+    o.cflag[base + k] = fl ? fl | (k + 1 == nk ? kLastChild : 0) : 0;
   };
-  for (uint64_t j0 = (uint64_t)blockIdx.x * 256 + (threadIdx.x & ~63u); j0 < lv.c; j0 += (uint64_t)gridDim.x * 256) {
-    const uint64_t j = j0 + lane;
-    uint64_t nk = 0, base = 0, st = 0;
-    uint32_t t = 0, fl = 0, r = 0;
-    if (j < lv.c && !a.marked[j]) {
-      if (pb) write_pointer(a, j, a.marked, m.uoff, m.tfirst, pb, po, err);
-    } else if (j < lv.c) {
-      t = lv.text[j];
-      st = lv.st[j];
-      const uint64_t c0 = cs[j], te = a.tx.tend[t];
-      nk = cs[j + 1] - c0;
-      base = ntfirst[t] + (c0 - cs[m.tfirst[t]]);
-      const uint64_t end = st + (te - st < lv.b ? te - st : lv.b);
-      const bool again = blocks && a.k.slot[j] != kNoKey && a.k.lm[j] < st;
-      if (pf[j] & 1) fl |= kSkipCross;
-      if (again || (j > 0 && (pf[j - 1] & 1))) fl |= kSkipInterior;
-      const uint64_t e = j - m.uoff[j];
-      o.ea[e] = st;
-      o.ee[e] = end;
-      o.ef[e] = (uint8_t)fl;
-      o.echild[e] = base;
-      if (o.run) {
-        r = rnum[j];
-        const uint32_t here = lv.run[j];
-        if (j == 0 || lv.run[j - 1] != here || !a.marked[j - 1]) {
-          o.rs[r] = st;
-          o.rtext[r] = t;
-        }
-        if (j + 1 == lv.c || lv.run[j + 1] != here || !a.marked[j + 1]) o.re[r] = end;
-      }
-    }
-    if (WIDE) {
+  if (WIDE) {
+    const uint64_t lane = lane_id();
+    for (uint64_t j0 = (uint64_t)blockIdx.x * 256 + (threadIdx.x & ~63u); j0 < lv.c; j0 += (uint64_t)gridDim.x * 256) {
+      uint64_t base = 0, nk = 0, st = 0;
+      uint32_t t = 0, fl = 0, r = 0;
+      if (j0 + lane < lv.c)
+        block(j0 + lane,
+              [&](uint64_t base_, uint64_t nk_, uint64_t st_, uint32_t t_, uint8_t fl_) {
+                base = base_, nk = nk_, st = st_, t = t_, fl = fl_;
+              },
+              [&](uint64_t, uint64_t, uint32_t r_) { r = r_; });
       for (uint64_t bal = __ballot(nk != 0); bal; bal &= bal - 1) {
         const uint32_t src = (uint32_t)(__ffsll((unsigned long long)bal) - 1);
-        const uint64_t bn_ = shfl64(nk, src), bb = shfl64(base, src), bs = shfl64(st, src);
-        const uint32_t bt = __shfl(t, (int)src), bf = __shfl(fl, (int)src), br = __shfl(r, (int)src);
-        for (uint64_t k = lane; k < bn_; k += 64) child(bb, k, bn_, bs, bt, bf, br);
+        const uint64_t sb = shfl64(base, src), sn = shfl64(nk, src), ss = shfl64(st, src);
+        const uint32_t tt = __shfl(t, (int)src), ff = __shfl(fl, (int)src), rr = __shfl(r, (int)src);
+        for (uint64_t k = lane; k < sn; k += 64) {
+          child(sb, k, sn, ss, tt, (uint8_t)ff);
+          if (o.run) o.run[sb + k] = rr;
+        }
       }
-    } else {
-      for (uint64_t k = 0; k < nk; ++k) child(base, k, nk, st, t, fl, r);
     }
+  } else {
+    GRID_STRIDE(j, lv.c)
+      block(j,
+            [&](uint64_t base, uint64_t nk, uint64_t st, uint32_t t, uint8_t fl) {
+              for (uint64_t k = 0; k < nk; ++k) child(base, k, nk, st, t, fl);
+            },
+            [&](uint64_t base, uint64_t nk, uint32_t r) {
+              for (uint64_t k = 0; k < nk; ++k) o.run[base + k] = r;
+            });
   }
   store_marks(a.marked, m, (uint64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6),
               (uint64_t)gridDim.x * 4);
