@@ -64,11 +64,11 @@ __device__ __forceinline__ void lean_chunk(const PhaseArgs& a, const uint64_t* _
   const auto load_odd = [&]() {
     oL = a.odd.L[t];
     if (oL) {
+      opos = a.odd.best[t];
       omask = oL < 8 ? (1ull << (8 * oL)) - 1 : ~0ull;
       uint64_t hi;
       bytes16_at(T, end, a.odd.pos[t], okey, hi);
       okey &= omask;
-      opos = a.odd.best[t];
     }
   };
   if (ODD && w0 < W) load_odd();
@@ -107,27 +107,29 @@ __device__ __forceinline__ void lean_chunk(const PhaseArgs& a, const uint64_t* _
           const uint64_t w = sh ? (lo >> sh) | (hi << (64 - sh)) : lo;
           if (i0 + k < opos && (w & omask) == okey) om |= 1u << k;
         }
-        // Runs can repeat those bytes: where a lane has more than two such starts,
-        // roll the whole key's 32-bit hash along them too.  (Each formed from the
-        // samples, 64 MiB with one byte in 256 not zero took 5.7 ms in place of
-        // 3.4, and a batch of 64 1 MiB texts 7.4 in place of 4.0.)
-        if (__popc(om) > 2) {
-          const uint64_t hx = a.odd.h32[t];
-          const uint32_t ox = (uint32_t)(hx >> 32), oxm1 = ox * a.x32inv;
-          uint32_t ho = h32(i0 + oL) - hA * ox, hm = 0;
-          uint64_t plo, phi;
-          bytes16_at(T, end, i0 + oL, plo, phi);
+        if (om) {
+          // Runs can repeat those bytes: with more than two such starts, roll the
+          // whole key's 32-bit hash along them too.  (Each formed from the samples,
+          // 64 MiB with one byte in 256 not zero took 5.7 ms in place of 3.4, and a
+          // batch of 64 1 MiB texts 7.4 in place of 4.0.)
+          if (__popc(om) > 2) {
+            const uint64_t hx = a.odd.h32[t];
+            const uint32_t ox = (uint32_t)(hx >> 32), oxm1 = ox * a.x32inv;
+            uint32_t ho = h32(i0 + oL) - hA * ox, hm = 0;
+            uint64_t plo, phi;
+            bytes16_at(T, end, i0 + oL, plo, phi);
 #pragma unroll
-          for (int k = 0; k < kLeanK; ++k) {
-            if (k) ho = roll32(ho, byte_of16(olo, ohi, k - 1), byte_of16(plo, phi, k - 1), oxm1, x32);
-            if (ho + s32 == (uint32_t)hx) hm |= 1u << k;
+            for (int k = 0; k < kLeanK; ++k) {
+              if (k) ho = roll32(ho, byte_of16(olo, ohi, k - 1), byte_of16(plo, phi, k - 1), oxm1, x32);
+              if (ho + s32 == (uint32_t)hx) hm |= 1u << k;
+            }
+            om &= hm;
           }
-          om &= hm;
-        }
-        while (om) {
-          const int k = __builtin_ctz(om);
-          om &= om - 1;
-          odd61(i0 + k);
+          while (om) {
+            const int k = __builtin_ctz(om);
+            om &= om - 1;
+            odd61(i0 + k);
+          }
         }
       }
       uint32_t h = h32(i0 + L) - hA * x32L;
