@@ -112,7 +112,7 @@ __device__ __forceinline__ void lean_chunk(const PhaseArgs& a, const uint64_t* _
           // whole key's 32-bit hash along them too.  (Each formed from the samples,
           // 64 MiB with one byte in 256 not zero took 5.7 ms in place of 3.4, and a
           // batch of 64 1 MiB texts 7.4 in place of 4.0.)
-          if (__popc(om) > 2) {
+          if (__builtin_popcount(om) > 2) {
             const uint64_t hx = a.odd.h32[t];
             const uint32_t ox = (uint32_t)(hx >> 32), oxm1 = ox * a.x32inv;
             uint32_t ho = h32(i0 + oL) - hA * ox, hm = 0;
