@@ -1,5 +1,6 @@
 // libbt host side: the C ABI of include/bt.h, the device memory pool, and the
-// level loop that drives the kernels of level.hip.
+// level loop that drives the scans of level.hip and probe_text.hip and the passes of
+// level_pass.hip.
 //
 // Build, for one or many texts (a single text is a batch of one):
 //   - plan every text: b1 = leaf * tau^k (k from s_hint or root_block_len),
@@ -614,6 +615,11 @@ uint64_t pow2_at_least(uint64_t v) {
 // keys, below 2^28 windows) rounds lost, 12.0 -> 12.1 ms per build against 10.5
 // without; at 2 GiB (2^19 to 2^24 keys) they took the scans of L = 2048, 512, 256,
 // 128 and 64 from 12.2, 36.8, 18.0, 15.3 and 6.5 ms to 8.6, 14.0, 6.4, 7.5 and 3.0.
+// Between, builds without and with rounds (tau 4): random DNA 384 MiB 15.4 and 14.7 ms,
+// 512 MiB 25.6 and 22.6, 1 GiB 75.2 and 62.5; copies of 8 MiB (0.1% changed), whose
+// lower levels have fewer windows, 9.6 and 9.9, 12.9 and 13.1, 29.4 and 29.2.  With
+// 2^17 keys and 2^26 windows the copies lost 8 to 11% at 128 and 256 MiB and 4 to 5%
+// at 384 and 512.
 constexpr uint64_t kRoundKeys = 1ull << 19;
 constexpr uint64_t kRoundWindows = 1ull << 28;
 
@@ -874,7 +880,7 @@ int build_many(bt_ctx* ctx, const uint8_t* d_base, const std::vector<uint64_t>& 
     if (tiles > 1) pass_tickets += tiles;
     return sd;
   };
-  // pinned words the level's counts are written to (k_texts)
+  // pinned words the level's counts are written to (one text: k_marks, else k_texts)
   constexpr uint64_t kHostTotals = 8;
   uint64_t* const h_lvl = small_host(ctx, kHostTotals + 2 * (uint64_t)T);
   uint64_t* d_lvl = nullptr;

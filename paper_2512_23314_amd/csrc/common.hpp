@@ -53,12 +53,6 @@ __device__ inline uint64_t pow61(uint64_t x, uint64_t e) {
   return r;
 }
 
-// Fingerprint of T[i .. i+L) from prefix fingerprints: P[i+L] - P[i] * x^L.
-__device__ __forceinline__ uint64_t window_fp(const uint64_t* __restrict__ P, uint64_t i,
-                                              uint64_t L, uint64_t xL) {
-  return sub61(P[i + L], mul61(P[i], xL));
-}
-
 // Final key of a window: add the per-text salt (batched builds keep texts
 // apart), then apply the debug truncation mask (all ones normally).
 __device__ __forceinline__ uint64_t finish_fp(uint64_t fp, uint64_t salt, uint64_t mask) {

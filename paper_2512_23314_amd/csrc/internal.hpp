@@ -134,7 +134,7 @@ struct PhaseArgs {
   const uint32_t* Hs;   // Hs[q] = H[pbase + 16 q] (memory-lean builds)
   uint32_t x32L;        // x32^Lmain mod 2^32
   uint32_t x32Lm1;      // x32^(Lmain - 1): the weight of the byte that leaves a rolled window
-  uint32_t x32inv;      // x32^-1 mod 2^32 (x32 is odd)
+  uint32_t x32inv;      // x32^-1 mod 2^32 (x32 is odd), for the rolled short key
   uint32_t x32;         // the 32-bit hash's base
   uint32_t pre32;
   // With pre32: a second, blocked bit filter of the keys' 32-bit hashes in
@@ -174,7 +174,7 @@ struct PhaseArgs {
 constexpr int kPcKeys = 0, kPcCand = 1, kPcWindows = 2, kPcVerified = 3, kPcCollisions = 4;
 constexpr int kPcWords = 8;
 
-// Scan entries and segments (level.hip, "scan segments").
+// Scan entries and segments (level_pass.hip, "scan segments").
 constexpr uint8_t kSkipInterior = 1;  // windows ending inside the entry are copies
 constexpr uint8_t kSkipCross = 2;     // every window starting in the entry is a copy
 constexpr uint8_t kLastChild = 4;     // (per block) the last child of its parent
@@ -277,9 +277,11 @@ hipError_t launch_sort_groups(const PhaseArgs& a, const uint64_t* fp, const uint
 hipError_t launch_byte_scan(const PhaseArgs& a, const uint64_t* woff, bool has_odd, bool has_salt,
                             uint64_t max_windows, hipStream_t s);
 // From this many segments on (a search of eight dependent loads) a dense scan
-// gets its tiles' segments beforehand: from the segment pass where a piece (an
-// entry, a block) spans at most kTileSegsPiece tiles, which one thread writes,
-// else from a launch of its own (find_segs), one thread per tile.
+// gets its tiles' segments beforehand: from the segment pass where a piece (a
+// parent's entry, a block) spans at most kTileSegsPiece tiles, which one thread
+// writes, else from a launch of its own (find_segs), one thread per tile.  (Longer
+// pieces than the rule reckons with are texts that enter a batch that scans with
+// shared filters, a debug mode: one thread writes theirs too.)
 constexpr uint64_t kTileSegsMin = 256;
 constexpr uint64_t kTileSegsPiece = 32;
 // The sliding-window probe.  max_windows bounds the grid; mode 1: LDS key filter
